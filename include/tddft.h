@@ -368,7 +368,7 @@ tddft_status tddft_batch_propagate(tddft_batch *b, int32_t nsteps, const double 
 tddft_ctx *tddft_batch_cell(tddft_batch *b, int32_t cell);
 /* Mean device time per batch step of the last propagate (ms). */
 tddft_status tddft_batch_last_timing(tddft_batch *b, double *ms_per_step);
-/* JSON text of the plan (per group: grid, cells, items, column split,
+/* JSON text of the plan (per group: grid, cells, items, z points per thread,
  * persistent workgroups, whether the step's ends run per group) and the
  * tuner's measurements, NUL-terminated in buf. */
 tddft_status tddft_batch_report(tddft_batch *b, char *buf, size_t len);

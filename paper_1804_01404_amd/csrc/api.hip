@@ -404,11 +404,11 @@ FusedArgs<T> fused_args(tddft_ctx* c);
 tddft_status enqueue_coef(tddft_ctx* c) {
   if (!c->fused) {
     if (c->mixed)
-      LAUNCH(launch_coef_table<float>(c->kappa, c->cfg.n_k, c->dh, c->cdiag, reinterpret_cast<float*>(c->coef),
+      LAUNCH(launch_coef_table<float>(c->kappa, c->cfg.n_k, c->lap, c->dh, c->cdiag, reinterpret_cast<float*>(c->coef),
                                       c->stream),
              "stage coefficients");
     else
-      LAUNCH(launch_coef_table<double>(c->kappa, c->cfg.n_k, c->dh, c->cdiag, c->coef, c->stream),
+      LAUNCH(launch_coef_table<double>(c->kappa, c->cfg.n_k, c->lap, c->dh, c->cdiag, c->coef, c->stream),
              "stage coefficients");
     return TDDFT_OK;
   }
@@ -454,10 +454,7 @@ FusedArgs<T> fused_args(tddft_ctx* c) {
   f.coef = reinterpret_cast<T*>(c->coef);
   f.phkA = c->phkA;
   for (int mu = 0; mu < 3; ++mu)
-    for (int m = 0; m < 4; ++m) {
-      f.lapc[mu][m] = (T)c->lap[mu][m + 1];
-      f.dhc[mu][m] = (T)c->dh[mu][m];
-    }
+    for (int m = 0; m < 4; ++m) f.dhc[mu][m] = (T)c->dh[mu][m];
   return f;
 }
 
@@ -1784,7 +1781,7 @@ struct BatchGroup {
   int* d_queue = nullptr;
   size_t lds = 0;
   int zs = 1, wgs = 0;
-  std::vector<std::pair<int, int>> cand;  // (zs, workgroups)
+  std::vector<std::pair<int, int>> cand;  // (z points per thread, workgroups)
   std::vector<double> cand_ms;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   // the end of the step (current, density, Poisson, xc) as one launch per
@@ -1893,9 +1890,9 @@ tddft_status batch_plan(tddft_batch* b) {
     g.d_queue = static_cast<int*>(p);
     BHIP(hipMemcpyAsync(g.d_args, args.data(), args.size() * sizeof(FusedArgs<T>), hipMemcpyHostToDevice, b->stream));
     BHIP(hipMemcpyAsync(g.d_items, items.data(), items.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream));
-    // the tuner only sizes the persistent grid: the column split is fixed per
+    // the tuner only sizes the persistent grid: the threads' tiles are fixed per
     // grid size, so no tuning decision changes a single bit of the result
-    g.zs = fused_column_split(g.n);
+    g.zs = fused_rows(g.n, sizeof(typename Vec2<T>::type));
     for (int per_cu : {1, 2, 3, 4}) g.cand.push_back({g.zs, per_cu * b->n_cu});
     g.wgs = b->n_cu;
     BHIP(hipEventCreate(&g.e0));
@@ -1977,6 +1974,7 @@ tddft_status batch_tail_upload(tddft_batch* b) {
       q.phA = c->phA;
       q.phAJ = c->phAJ;
       q.Alast = c->Alast;
+      std::memcpy(q.lap, c->lap, sizeof(q.lap));
       std::memcpy(q.dh, c->dh, sizeof(q.dh));
       q.cdiag = c->cdiag;
       q.coef = c->coef;
@@ -2071,7 +2069,7 @@ tddft_status batch_step(tddft_batch* b, bool timing) {
     BHIP(hipStreamWaitEvent(s, b->fork, 0));
     BHIP(launch_set_int(g.d_queue, 0, s));
     if (timing) BHIP(hipEventRecord(g.e0, s));
-    BHIP(launch_fused_persistent<T>(g.n, g.zs, g.periodic, static_cast<const FusedArgs<T>*>(g.d_args), g.d_items,
+    BHIP(launch_fused_persistent<T>(g.n, g.periodic, static_cast<const FusedArgs<T>*>(g.d_args), g.d_items,
                                     g.n_items, g.d_queue, g.wgs, g.lds, s));
     if (timing) BHIP(hipEventRecord(g.e1, s));
     if (g.tail_ok) {

@@ -24,7 +24,11 @@ constexpr int kHaloSlots = 3;
 __host__ __device__ inline bool halo_fits(int TX, int TY) {
   return 8 * (TX + TY) <= kHaloSlots * ((TX * TY + 63) / 64) * 64;
 }
-constexpr int kCoef = 16;  // per k-point: kappa_mu d_m / h_mu for x, y, z (3 x 4), diagonal, padding
+// per k-point row of stencil coefficients: for x, y, z the four weights
+// -1/2 c_m / h_mu^2 and the four kappa_mu d_m / h_mu (3 x 8), the diagonal, padding
+constexpr int kCoef = 32;
+constexpr int kCoefB = 4;      // place of an axis's kappa weights in its eight
+constexpr int kCoefDiag = 24;
 
 enum StageMode { kFirst = 0, kMid = 1, kLast = 2 };
 enum BcKind { kPeriodicPlane = 0, kPeriodicTile = 1, kIsolatedTile = 2 };
@@ -90,7 +94,7 @@ struct StageArgs {
   double cdiag;            // sum_mu -1/2 c_0 / h_mu^2
   double tau;              // dt / s: u_{s-1} = w + (tau_re - i tau) h u_s
   double tau_re;           // 0 in real time; -tau_imag / s for imaginary time
-  const T* coef;           // [n_k][kCoef] kappa_mu d_m / h_mu and the diagonal, stage precision
+  const T* coef;           // [n_k][kCoef] stencil coefficients, stage precision
   T lapc[3][4];            // off-centre Laplacian weights -1/2 c_m / h_mu^2, stage precision
 };
 
@@ -163,7 +167,6 @@ struct FusedArgs {
   double* jnl;             // [n_orb_tot][4]
   T* coef;                 // [n_k][kCoef] stencil coefficients of the step, stage precision
   double2* phkA;           // [n_k][S] exp(i kappa . x_e) at the step midpoint (set with coef)
-  T lapc[3][4];            // off-centre Laplacian weights -1/2 c_m / h_mu^2, stage precision
   T dhc[3][4];             // first-derivative weights d_m / h_mu, stage precision
 };
 
@@ -189,13 +192,13 @@ hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s);
 template <typename T>
 hipError_t launch_fused_coef(const FusedArgs<T>& a, hipStream_t s);
 template <typename T>
-hipError_t launch_coef_table(const double* kappa, int n_k, const double dh[3][4], double cdiag, T* coef,
+hipError_t launch_coef_table(const double* kappa, int n_k, const double lap[3][5], const double dh[3][4], double cdiag, T* coef,
                              hipStream_t s);
 bool fused_supported(const Geometry& g, int n_atoms, size_t elem);
 size_t fused_lds_bytes(const Geometry& g, int n_atoms, size_t elem);
-int fused_column_split(int n);
+int fused_rows(int n, size_t elem);  // z points of a thread's tile
 template <typename T>
-hipError_t launch_fused_persistent(int n, int zs, bool periodic, const FusedArgs<T>* cells, const int2* items,
+hipError_t launch_fused_persistent(int n, bool periodic, const FusedArgs<T>* cells, const int2* items,
                                    int n_items, int* queue, int wgs, size_t lds, hipStream_t s);
 
 hipError_t launch_step_params(const double* A, const int* counter, int use_counter,
@@ -266,9 +269,10 @@ struct ParamCell {
   double2* phA;
   double2* phAJ;
   double* Alast;
+  double lap[3][5];
   double dh[3][4];
   double cdiag;
-  void* coef;             // [n_k][16] stage precision
+  void* coef;             // [n_k][kCoef] stage precision
   const double2* phk;     // [n_k][S]
   double2* phkA;          // [n_k][S]
 };

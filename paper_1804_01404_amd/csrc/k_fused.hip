@@ -5,9 +5,10 @@
 // runs all four Horner stages u_{s-1} = w + (-i dt / s) h u_s, s = 4..1
 // (Program Summary: fourth-order truncated Taylor expansion; Sec. 4.1,
 // Eq. TDKS_solid for h), with
-//   * u_s in LDS; w and u_{s-1} in registers. A thread owns one (x, y)
-//     column, or one half of it (ZS = 2: the two halves sit in different
-//     wavefronts, which halves the register arrays and doubles the waves);
+//   * u_s in LDS; u_{s-1} in registers. A thread owns a tile of four
+//     consecutive x by ZR consecutive z points (see stencil_tile), so that
+//     every LDS access is a 16-byte one and a value read once serves up to
+//     nine outputs;
 //   * the Kleinman-Bylander projections u_p = <beta_p^kappa|u_s> of every atom
 //     formed in the workgroup before each stage (one wavefront per atom,
 //     fixed-order shuffle reductions, FP64) and added back by a scatter over
@@ -17,6 +18,8 @@
 //     w_new that the current needs (norm and momentum, FP64 accumulation) and
 //     the moment projections for the nonlocal current at t_{n+1}.
 // HBM traffic per orbital point and step: read w once, write w_new once.
+#include <cstring>
+
 #include "internal.h"
 
 namespace td {
@@ -40,201 +43,496 @@ __device__ __forceinline__ gp<X> G(X* p) {
   return (gp<X>)p;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+// Cross-lane moves without LDS. A shuffle is an LDS instruction with an LDS
+// round trip in its dependent chain, and the nonlocal phases are such chains:
+// six reduction steps per atom and stage. gfx950 exchanges wavefront halves
+// and rows of 16 lanes with a register swap; the steps inside a row are DPP
+// moves.
+struct Pair64 {
+  double x, y;
+};
+__device__ __forceinline__ Pair64 join2(unsigned xl, unsigned xh, unsigned yl, unsigned yh) {
+  return Pair64{__hiloint2double((int)xh, (int)xl), __hiloint2double((int)yh, (int)yl)};
 }
+// x = (a's lower half, b's lower half), y = (a's upper half, b's upper half)
+__device__ __forceinline__ Pair64 swap32(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return join2(l[0], h[0], l[1], h[1]);
+#else
+  return Pair64{a, b};
+#endif
+}
+// the same for the even and odd rows of 16 lanes
+__device__ __forceinline__ Pair64 swap16(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return join2(l[0], h[0], l[1], h[1]);
+#else
+  return Pair64{a, b};
+#endif
+}
+// DPP controls: lane ^ 1, lane ^ 2 (quad permutations), lane ^ 7 (mirror of
+// eight lanes), lane ^ 8 (rotation of a row by eight)
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor7 = 0x141, kXor8 = 0x128;
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int l = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int h = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(h, l);
+#else
+  return v;
+#endif
+}
+// sum over the lanes that differ in bit 5 / in bit 4
+__device__ __forceinline__ double sum32(double v) {
+  const Pair64 p = swap32(v, v);
+  return p.x + p.y;
+}
+__device__ __forceinline__ double sum16(double v) {
+  const Pair64 p = swap16(v, v);
+  return p.x + p.y;
+}
+// sum over groups of eight / of four lanes
+__device__ __forceinline__ double sum_quad(double v) {
+  v += dpp<kXor2>(v);
+  return v + dpp<kXor1>(v);
+}
+__device__ __forceinline__ double sum_oct(double v) { return sum_quad(v + dpp<kXor7>(v)); }
 
-// Wavefront sums of 16 values by recursive halving over lane bits 5..2 (8 +
-// 4 + 2 + 1 shuffles, then two over bits 1 and 0): every lane returns the full
-// sum of value lane >> 2.
-__device__ __forceinline__ double wave_sum16(const double (&v)[16], int lane) {
-  double a[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const bool hi = lane & 32;
-    const double send = hi ? v[i] : v[i + 8], keep = hi ? v[i + 8] : v[i];
-    a[i] = keep + __shfl_xor(send, 32, 64);
-  }
-#pragma unroll
-  for (int w = 4, bit = 16; w >= 1; w >>= 1, bit >>= 1) {
-#pragma unroll
-    for (int i = 0; i < w; ++i) {
-      const bool hi = lane & bit;
-      const double send = hi ? a[i] : a[i + w], keep = hi ? a[i + w] : a[i];
-      a[i] = keep + __shfl_xor(send, bit, 64);
-    }
-  }
-  a[0] += __shfl_xor(a[0], 2, 64);
-  return a[0] + __shfl_xor(a[0], 1, 64);
+__device__ __forceinline__ double wave_sum(double v) {
+  v = sum16(sum32(v));
+  return sum_oct(v + dpp<kXor8>(v));
 }
 
 // Wavefront sums of eight values at once by recursive halving: at each of the
 // exchanges over lane bits 5, 4, 3 a lane keeps half of its values and sends
-// the other half, so 4 + 2 + 1 shuffles leave value j = (lane >> 3) & 7
-// summed over those bits; three more finish the sum over bits 2..0. Every lane
-// returns the full sum of value (lane >> 3) & 7 (11 shuffles instead of 48).
+// the other half; three more steps finish the sum over bits 2..0. Every lane
+// returns the full sum of value (lane >> 3) & 7.
 __device__ __forceinline__ double wave_sum8(const double (&v)[8], int lane) {
-  double a[4];
-  const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8;
+  double a[4], b[2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const double send = b5 ? v[i] : v[i + 4], keep = b5 ? v[i + 4] : v[i];
-    a[i] = keep + __shfl_xor(send, 32, 64);
+    const Pair64 p = swap32(v[i], v[i + 4]);
+    a[i] = p.x + p.y;
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const double send = b4 ? a[i] : a[i + 2], keep = b4 ? a[i + 2] : a[i];
-    a[i] = keep + __shfl_xor(send, 16, 64);
+    const Pair64 p = swap16(a[i], a[i + 2]);
+    b[i] = p.x + p.y;
   }
-  {
-    const double send = b3 ? a[0] : a[1], keep = b3 ? a[1] : a[0];
-    a[0] = keep + __shfl_xor(send, 8, 64);
-  }
-  a[0] += __shfl_xor(a[0], 4, 64);
-  a[0] += __shfl_xor(a[0], 2, 64);
-  a[0] += __shfl_xor(a[0], 1, 64);
-  return a[0];
+  const bool hi = lane & 8;
+  const double keep = hi ? b[1] : b[0], send = hi ? b[0] : b[1];
+  return sum_oct(keep + dpp<kXor8>(send));
 }
 
-// in-plane neighbour offsets of one column (periodic wrap) and its own offset
-struct Nbr {
-  int xp[4], xm[4], yp[4], ym[4];
-  int c;
-};
+// Wavefront sums of 16 values in the same way over lane bits 5..2 (the last
+// exchange goes to lane ^ 7: its low bits are summed over next anyway): every
+// lane returns the full sum of value lane >> 2.
+__device__ __forceinline__ double wave_sum16(const double (&v)[16], int lane) {
+  double a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const Pair64 p = swap32(v[i], v[i + 8]);
+    a[i] = p.x + p.y;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const Pair64 p = swap16(a[i], a[i + 4]);
+    b[i] = p.x + p.y;
+  }
+  const bool h8 = lane & 8, h4 = lane & 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double keep = h8 ? b[i + 2] : b[i], send = h8 ? b[i] : b[i + 2];
+    c[i] = keep + dpp<kXor8>(send);
+  }
+  const double keep = h4 ? c[1] : c[0], send = h4 ? c[0] : c[1];
+  return sum_quad(keep + dpp<kXor7>(send));
+}
 
 struct FusedCoefIn {
+  double lap[3][5];
   double dh[3][4];
   double cdiag;
 };
 
+// E . r of the length gauge at the tile's first point and its steps along x and z
 template <typename T>
-struct Coef {
-  T cx[4], cy[4], cz[4], bx[4], by[4], bz[4];
-  T diag, ext, ez;
+struct FieldE {
+  T ext, ex, ez;
 };
 
-// A copy of the offsets that the compiler cannot see through: rebuilding the
-// addresses per stage keeps the unrolled column loop from holding every one
-// of them live across the stage loop.
-__device__ __forceinline__ float opaque_t(float v) {
+// The k-point's row of coefficients. Each part of the stencil reads the eight
+// weights of its axis with scalar loads where it needs them: all 25 held at
+// once (50 scalar registers in FP64) were spilled into vector lanes and read
+// back lane by lane.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class X>
+using cp = const __attribute__((address_space(4))) X*;
+#else
+template <class X>
+using cp = const X*;
+#endif
+template <typename T>
+__device__ __forceinline__ cp<T> fresh(cp<T> p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+template <typename T>
+struct Axis {
+  T c[4], b[4];
+};
+template <typename T>
+__device__ __forceinline__ Axis<T> axis_coef(cp<T> row, int axis) {
+  const cp<T> p = fresh<T>(row) + 8 * axis;
+  Axis<T> a;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    a.c[m] = p[m];
+    a.b[m] = p[kCoefB + m];
+  }
+  return a;
+}
+
+__device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// four consecutive x points, moved as 16-byte accesses
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef double d4_t __attribute__((ext_vector_type(4)));
+typedef double d2_t __attribute__((ext_vector_type(2)));
+template <typename T> struct Four;
+template <> struct Four<float> { using type = f4_t; };
+template <> struct Four<double> { using type = d4_t; };
+template <typename T>
+struct Quad {
+  typename Four<T>::type re, im;
+};
+
+template <typename P>
+__device__ __forceinline__ Quad<float> load_quad(P p, float) {
+  const f4_t a = p[0], b = p[1];
+  return Quad<float>{f4_t{a.x, a.z, b.x, b.z}, f4_t{a.y, a.w, b.y, b.w}};
+}
+template <typename P>
+__device__ __forceinline__ Quad<double> load_quad(P p, double) {
+  const d2_t a = p[0], b = p[1], c = p[2], d = p[3];
+  return Quad<double>{d4_t{a.x, b.x, c.x, d.x}, d4_t{a.y, b.y, c.y, d.y}};
+}
+template <typename P>
+__device__ __forceinline__ void store_quad(P p, const Quad<float>& q) {
+  p[0] = f4_t{q.re.x, q.im.x, q.re.y, q.im.y};
+  p[1] = f4_t{q.re.z, q.im.z, q.re.w, q.im.w};
+}
+template <typename P>
+__device__ __forceinline__ void store_quad(P p, const Quad<double>& q) {
+  p[0] = d2_t{q.re.x, q.im.x};
+  p[1] = d2_t{q.re.y, q.im.y};
+  p[2] = d2_t{q.re.z, q.im.z};
+  p[3] = d2_t{q.re.w, q.im.w};
+}
+template <typename V, typename T>
+__device__ __forceinline__ V fma4(T a, V b, V c) {
+  // element by element: a splat of a scalar-register weight would be copied
+  return V{fmad(a, b.x, c.x), fmad(a, b.y, c.y), fmad(a, b.z, c.z), fmad(a, b.w, c.w)};
+}
+// 16-byte elements of the arrays: two complex FP32 or one complex FP64
+template <typename T> struct Wide;
+template <> struct Wide<float> { using type = f4_t; };
+template <> struct Wide<double> { using type = d2_t; };
+
+// Places (in quads of four x points) a thread's tile reads: its own first quad, the quads
+// left and right of it, the rows y +- m, and the groups of ZR planes that hold
+// the planes z0 - 4 .. z0 - 1 and z0 + ZR .. z0 + ZR + 3. All wrap (periodic);
+// the *ok bits are clear where an isolated box has nothing (read as zero).
+template <int ZR>
+struct TileAt {
+  static constexpr int kGroups = 4 / ZR;  // plane groups on either side
+  int own, xl, xr, yp[4], ym[4], zl[kGroups], zr[kGroups];
+  unsigned ok;  // bit 0 xl, 1 xr, 2..5 yp, 6..9 ym, 10.. zl, 14.. zr
+};
+
+template <int N, int ZR>
+__device__ __forceinline__ TileAt<ZR> tile_at(int t) {
+  constexpr int Q = N / 4, plane = N * Q;
+  TileAt<ZR> a;
+  const int qx = t % Q, r = t / Q, y = r % N, zb = r / N, z0 = zb * ZR;
+  const int col = y * Q + qx;
+  unsigned ok = 0;
+  a.own = z0 * plane + col;
+  a.xl = a.own + (qx > 0 ? -1 : Q - 1);
+  a.xr = a.own + (qx < Q - 1 ? 1 : 1 - Q);
+  ok |= (qx > 0 ? 1u : 0u) | (qx < Q - 1 ? 2u : 0u);
+#pragma unroll
+  for (int m = 1; m <= 4; ++m) {
+    const int yp = y + m, ym = y - m;
+    a.yp[m - 1] = a.own + (yp < N ? m : m - N) * Q;
+    a.ym[m - 1] = a.own + (ym >= 0 ? -m : N - m) * Q;
+    ok |= (yp < N ? 1u : 0u) << (1 + m) | (ym >= 0 ? 1u : 0u) << (5 + m);
+  }
+#pragma unroll
+  for (int g = 0; g < TileAt<ZR>::kGroups; ++g) {
+    const int zl = z0 - 4 + g * ZR, zr = z0 + ZR + g * ZR;
+    a.zl[g] = (zl >= 0 ? zl : zl + N) * plane + col;
+    a.zr[g] = (zr < N ? zr : zr - N) * plane + col;
+    ok |= (zl >= 0 ? 1u : 0u) << (10 + g) | (zr < N ? 1u : 0u) << (14 + g);
+  }
+  a.ok = ok;
+  return a;
+}
+
+// A copy of a thread's tile number that the compiler cannot see through: the
+// places are rebuilt from it per stage instead of being held in registers
+// across the nonlocal phases.
+__device__ __forceinline__ int opaque_i(int v) {
   asm volatile("" : "+v"(v));
   return v;
 }
-__device__ __forceinline__ double opaque_t(double v) {
-  asm volatile("" : "+v"(v));
-  return v;
+
+// The orbital in LDS. A quad's 16-byte words (real parts, then imaginary
+// parts) lie in arrays of their own, so that a wavefront's access to one word
+// of neighbouring quads is contiguous; interleaved quads (a 32- or 64-byte
+// stride between lanes) conflicted on every second access: 205 M conflict
+// cycles per launch of the 20^3 x 512-k cell, more than half of the LDS time.
+// Every array ends with a zero word: the quad read where an isolated box ends.
+template <typename T, int N>
+struct LdsOrb {
+  using V = typename Wide<T>::type;
+  static constexpr int kQuads = N * N * N / 4;
+  static constexpr int kStride = kQuads + 1;
+  static constexpr int kWords = (int)(2 * sizeof(T) / 4);
+  static constexpr size_t kBytes = (size_t)kWords * kStride * 16;
+  V* w;
+
+  template <bool PERIODIC>
+  __device__ __forceinline__ Quad<T> quad(int place, bool in) const {
+    // opaque: the compiler would otherwise load both and select every value
+    if (!PERIODIC) place = opaque_i(in ? place : kQuads);
+    return get(place, T(0));
+  }
+  __device__ __forceinline__ Quad<float> get(int q, float) const { return Quad<float>{w[q], w[kStride + q]}; }
+  __device__ __forceinline__ Quad<double> get(int q, double) const {
+    const d2_t a = w[q], b = w[kStride + q], c = w[2 * kStride + q], d = w[3 * kStride + q];
+    return Quad<double>{d4_t{a.x, a.y, b.x, b.y}, d4_t{c.x, c.y, d.x, d.y}};
+  }
+  __device__ __forceinline__ void set(int q, const Quad<float>& v) const {
+    w[q] = v.re;
+    w[kStride + q] = v.im;
+  }
+  __device__ __forceinline__ void set(int q, const Quad<double>& v) const {
+    w[q] = d2_t{v.re.x, v.re.y};
+    w[kStride + q] = d2_t{v.re.z, v.re.w};
+    w[2 * kStride + q] = d2_t{v.im.x, v.im.y};
+    w[3 * kStride + q] = d2_t{v.im.z, v.im.w};
+  }
+  // one point: its real part; the imaginary part lies kImag further on
+  static constexpr int kImag = (kWords / 2) * kStride * (int)(16 / sizeof(T));
+  __device__ __forceinline__ T* point(int i) const {
+    T* p = reinterpret_cast<T*>(w);
+    return sizeof(T) == 4 ? p + i : p + 2 * ((i >> 2) + ((i >> 1) & 1) * kStride) + (i & 1);
+  }
+};
+
+// the four points starting m (0 < m <= 4) right of a's first, out of eight
+template <int M, typename V>
+__device__ __forceinline__ V window(V a, V b) {
+  return __builtin_shufflevector(a, b, M, M + 1, M + 2, M + 3);
 }
 
-__device__ __forceinline__ Nbr opaque(const Nbr& n) {
-  Nbr r = n;
-#pragma unroll
-  for (int m = 0; m < 4; ++m) asm volatile("" : "+v"(r.xp[m]), "+v"(r.xm[m]), "+v"(r.yp[m]), "+v"(r.ym[m]));
-  asm volatile("" : "+v"(r.c));
-  return r;
+// acc += c (p + n) + b (...): the pair of neighbours at one distance of an
+// axis, weights c of the Laplacian and b of the kappa term
+template <typename T>
+__device__ __forceinline__ void add_pair(Quad<T>& t, T c, T b, const Quad<T>& p, const Quad<T>& n) {
+  t.re = fma4(c, p.re + n.re, t.re);
+  t.re = fma4(b, p.im - n.im, t.re);
+  t.im = fma4(c, p.im + n.im, t.im);
+  t.im = fma4(-b, p.re - n.re, t.im);
+}
+template <int M, typename T>
+__device__ __forceinline__ void add_x_pair(Quad<T>& t, T c, T b, const Quad<T>& l, const Quad<T>& o, const Quad<T>& r) {
+  add_pair<T>(t, c, b, Quad<T>{window<M>(o.re, r.re), window<M>(o.im, r.im)},
+              Quad<T>{window<4 - M>(l.re, o.re), window<4 - M>(l.im, o.im)});
 }
 
-template <typename T, bool PERIODIC>
-__device__ __forceinline__ typename Vec2<T>::type lds_xy(const typename Vec2<T>::type* pl, int off, bool valid) {
-  typename Vec2<T>::type v = pl[off];
-  if (!PERIODIC && !valid) v.x = v.y = 0;
-  return v;
-}
-
-// h u_s (local part) and the Horner update for the planes Z0 .. Z0 + ZN - 1
-template <typename T, int N, int ZN, int Z0, bool PERIODIC>
-__device__ __forceinline__ void stencil_part(const typename Vec2<T>::type* u, gp<const T> V,
-                                             const Coef<T>& cf, const Nbr& nb, const bool (&ok)[16],
-                                             gp<const typename Vec2<T>::type> wg,
-                                             typename Vec2<T>::type (&un)[ZN], T tau, bool length) {
-  using T2 = typename Vec2<T>::type;
-  constexpr int plane = N * N;
-  const T ez = opaque_t(cf.ez);
+// h u_s (local part) and the Horner update of one tile of 4 x ZR points.
+// Along z each plane's quad is read once and added to every output row it
+// reaches; per row the y rows come in pairs and the x neighbours from three
+// quads: 14, 16 and 19 quads read per row of four points for ZR = 4, 2 and 1,
+// where point by point it would be 25 reads a point. The far (small) weights
+// are added first and the diagonal last, so few roundings fall on the large
+// partial sums (errors against 64 bits as before: 4.0e-8 of the density after
+// 20 mixed steps of 20^3 x 512 k).
+// Bound: vector issue in complex FP32 (632 M wave instructions per launch of
+// the 20^3 x 512-k cell, 0.86 of one per CU and clock), LDS and issue together
+// in complex128. A launch took 1.53 ms (FP32; 817 M instructions) and 0.44 ms
+// (complex128, 64 k) when a thread owned a whole column of points read one by
+// one with the last wavefronts idle; now 1.21 and 0.32 ms; 16^3 x 64 k 0.136 ->
+// 0.122 and 0.290 -> 0.183 ms, 24^3 x 27 k (FP32) 0.229 -> 0.144 ms.
+template <typename T, int N, int ZR, bool PERIODIC>
+__device__ __forceinline__ void stencil_tile(const LdsOrb<T, N> u, gp<const T> V, cp<T> row, const FieldE<T>& fe,
+                                             const TileAt<ZR>& at, gp<const typename Vec2<T>::type> wg,
+                                             Quad<T> (&un)[ZR], T tau) {
+  constexpr int plane = N * N / 4;  // quads
+  using V16 = typename Wide<T>::type;
+  using V4 = typename Four<T>::type;
+  const V4 zero = (V4)(T(0));
 #pragma unroll
-  for (int zz = 0; zz < ZN; ++zz) {
-    const int z = Z0 + zz;
-    const T2* pl = u + z * plane;
-    const T2 c = pl[nb.c];
-    T dg = cf.diag + V[z * plane + nb.c];
-    if (!PERIODIC && length) dg += cf.ext + ez * (T)z;
-    T hr = dg * c.x, hi = dg * c.y;
+  for (int r = 0; r < ZR; ++r) un[r].re = un[r].im = zero;
+  const Axis<T> az = axis_coef<T>(row, 2);
+  // planes z0 - 4 .. z0 + ZR + 3 in order
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      T2 p = lds_xy<T, PERIODIC>(pl, nb.xp[m], ok[m]);
-      T2 n = lds_xy<T, PERIODIC>(pl, nb.xm[m], ok[4 + m]);
-      hr += cf.cx[m] * (p.x + n.x) + cf.bx[m] * (p.y - n.y);
-      hi += cf.cx[m] * (p.y + n.y) - cf.bx[m] * (p.x - n.x);
-      p = lds_xy<T, PERIODIC>(pl, nb.yp[m], ok[8 + m]);
-      n = lds_xy<T, PERIODIC>(pl, nb.ym[m], ok[12 + m]);
-      hr += cf.cy[m] * (p.x + n.x) + cf.by[m] * (p.y - n.y);
-      hi += cf.cy[m] * (p.y + n.y) - cf.by[m] * (p.x - n.x);
-      const int zp = z + m + 1, zm = z - m - 1;
-      T2 q, r;
-      q.x = q.y = r.x = r.y = 0;
-      if (PERIODIC || zp < N) q = u[(zp % N) * plane + nb.c];
-      if (PERIODIC || zm >= 0) r = u[((zm + N) % N) * plane + nb.c];
-      hr += cf.cz[m] * (q.x + r.x) + cf.bz[m] * (q.y - r.y);
-      hi += cf.cz[m] * (q.y + r.y) - cf.bz[m] * (q.x - r.x);
+  for (int p = -4; p < ZR + 4; ++p) {
+    if (ZR == 1 && p == 0) continue;
+    int place;
+    bool in = true;
+    if (p < 0) {
+      const int g = (p + 4) / ZR;
+      place = at.zl[g] + ((p + 4) % ZR) * plane;
+      in = at.ok >> (10 + g) & 1;
+    } else if (p < ZR) {
+      place = at.own + p * plane;
+    } else {
+      const int g = (p - ZR) / ZR;
+      place = at.zr[g] + ((p - ZR) % ZR) * plane;
+      in = at.ok >> (14 + g) & 1;
     }
-    // w is re-read (from cache) rather than held in registers for all stages
-    const T2 wv = wg[z * plane + nb.c];
-    un[zz].x = wv.x + tau * hi;
-    un[zz].y = wv.y - tau * hr;
-    // one plane at a time: bounds the loads in flight and so the registers
+    const Quad<T> q = u.template quad<PERIODIC>(place, in);
+#pragma unroll
+    for (int r = 0; r < ZR; ++r) {
+      const int d = p - r;
+      if (d == 0 || d > 4 || d < -4) continue;
+      const int m = (d > 0 ? d : -d) - 1;
+      const T b = d > 0 ? az.b[m] : -az.b[m];
+      un[r].re = fma4(b, q.im, fma4(az.c[m], q.re, un[r].re));
+      un[r].im = fma4(-b, q.re, fma4(az.c[m], q.im, un[r].im));
+    }
+    if ((p & 1) || sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+  }
+  Axis<T> ax, ay;
+  if (sizeof(T) == 4) {
+    ay = axis_coef<T>(row, 1);
+    ax = axis_coef<T>(row, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < ZR; ++r) {
+    const int off = at.own + r * plane;
+    V4 v;
+    Quad<T> w;
+    // w is re-read (from cache) rather than held in registers for all stages;
+    // in FP64 it is loaded after the neighbours, for the registers' sake
+    auto load_w = [&]() __attribute__((always_inline)) {
+      v = *(gp<const V4>)(V + 4 * off);
+      w = load_quad((gp<const V16>)(wg + 4 * off), T(0));
+    };
+    if (sizeof(T) == 4) load_w();
+    Quad<T> t{zero, zero};
+    if (sizeof(T) == 8) ay = axis_coef<T>(row, 1);
+#pragma unroll
+    for (int m = 3; m >= 0; --m) {
+      const Quad<T> p = u.template quad<PERIODIC>(at.yp[m] + r * plane, at.ok >> (2 + m) & 1);
+      const Quad<T> n = u.template quad<PERIODIC>(at.ym[m] + r * plane, at.ok >> (6 + m) & 1);
+      add_pair<T>(t, ay.c[m], ay.b[m], p, n);
+      if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+    }
+    const Quad<T> c = u.template quad<true>(off, true);
+    const Quad<T> xl = u.template quad<PERIODIC>(at.xl + r * plane, at.ok & 1);
+    const Quad<T> xr = u.template quad<PERIODIC>(at.xr + r * plane, at.ok >> 1 & 1);
+    if (sizeof(T) == 8) ax = axis_coef<T>(row, 0);
+    add_x_pair<4>(t, ax.c[3], ax.b[3], xl, c, xr);
+    add_x_pair<3>(t, ax.c[2], ax.b[2], xl, c, xr);
+    add_x_pair<2>(t, ax.c[1], ax.b[1], xl, c, xr);
+    add_x_pair<1>(t, ax.c[0], ax.b[0], xl, c, xr);
+    if (sizeof(T) == 8) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_w();
+    }
+    V4 dg = v + row[kCoefDiag];
+    if (!PERIODIC) dg += (V4)(fe.ext + fe.ez * (T)r) + V4{T(0), fe.ex, 2 * fe.ex, 3 * fe.ex};
+    const V4 hr = __builtin_elementwise_fma(dg, c.re, un[r].re + t.re);
+    const V4 hi = __builtin_elementwise_fma(dg, c.im, un[r].im + t.im);
+    un[r].re = fma4(tau, hi, w.re);
+    un[r].im = fma4(-tau, hr, w.im);
+    // one row at a time: bounds the loads in flight and so the registers
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// norm and momentum sums of w_new for the planes Z0 .. Z0 + ZN - 1: the
-// weighted neighbour sums in the stage precision, their products with w and
-// the running sums in FP64 (as in the streaming observables kernel)
-template <typename T, int N, int ZN, int Z0, bool PERIODIC>
-__device__ __forceinline__ void observe_part(const typename Vec2<T>::type* u, const T (&dw)[3][4],
-                                             const Nbr& nb, const bool (&ok)[16], double (&sv)[4]) {
+// norm and momentum sums of w_new over one tile: the weighted neighbour sums
+// in the stage precision, their products with w and the running sums in FP64
+// (as in the streaming observables kernel)
+template <typename T, int N, int ZR, bool PERIODIC>
+__device__ __forceinline__ void observe_tile(const LdsOrb<T, N> u, const T (&dw)[3][4],
+                                             const TileAt<ZR>& at, double (&sv)[4]) {
   // Summed over the whole grid, Im(conj(w) D w) with the antisymmetric
   // difference D = sum_m d_m (S_m - S_-m) equals 2 sum_m d_m Im(conj(w) S_m w)
   // (shift r -> r - m in the backward half; zero outside an isolated box), so
   // each point needs only its forward neighbours.
-  using T2 = typename Vec2<T>::type;
-  constexpr int plane = N * N;
+  constexpr int plane = N * N / 4;  // quads
+  using V4 = typename Four<T>::type;
+  const V4 zero = (V4)(T(0));
 #pragma unroll
-  for (int zz = 0; zz < ZN; ++zz) {
-    const int z = Z0 + zz;
-    const T2* pl = u + z * plane;
-    const T2 cv = pl[nb.c];
-    const double cr = (double)cv.x, ci = (double)cv.y;
-    T sxr = 0, sxi = 0, syr = 0, syi = 0, szr = 0, szi = 0;
+  for (int r = 0; r < ZR; ++r) {
+    const int off = at.own + r * plane;
+    const Quad<T> c = u.template quad<true>(off, true);
+    Quad<T> s{zero, zero};
+    auto add = [&](T d, V4 re, V4 im) __attribute__((always_inline)) {
+      s.re = fma4(d, re, s.re);
+      s.im = fma4(d, im, s.im);
+    };
+    auto take = [&](int axis) __attribute__((always_inline)) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const T2 p = lds_xy<T, PERIODIC>(pl, nb.xp[m], ok[m]);
-      const T2 q = lds_xy<T, PERIODIC>(pl, nb.yp[m], ok[8 + m]);
-      const int zp = z + m + 1;
-      T2 r;
-      r.x = r.y = 0;
-      if (PERIODIC || zp < N) r = u[(zp % N) * plane + nb.c];
-      sxr += dw[0][m] * p.x;
-      sxi += dw[0][m] * p.y;
-      syr += dw[1][m] * q.x;
-      syi += dw[1][m] * q.y;
-      szr += dw[2][m] * r.x;
-      szi += dw[2][m] * r.y;
+      for (int i = 0; i < 4; ++i)
+        sv[1 + axis] = fmad((double)c.re[i], (double)s.im[i], fmad(-(double)c.im[i], (double)s.re[i], sv[1 + axis]));
+      s.re = s.im = zero;
+    };
+    const Quad<T> xr = u.template quad<PERIODIC>(at.xr + r * plane, at.ok >> 1 & 1);
+    add(dw[0][3], xr.re, xr.im);
+    add(dw[0][2], window<3>(c.re, xr.re), window<3>(c.im, xr.im));
+    add(dw[0][1], window<2>(c.re, xr.re), window<2>(c.im, xr.im));
+    add(dw[0][0], window<1>(c.re, xr.re), window<1>(c.im, xr.im));
+    take(0);
+#pragma unroll
+    for (int m = 3; m >= 0; --m) {
+      const Quad<T> q = u.template quad<PERIODIC>(at.yp[m] + r * plane, at.ok >> (2 + m) & 1);
+      add(dw[1][m], q.re, q.im);
+      if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
     }
-    sv[0] += cr * cr + ci * ci;
-    sv[1] += 2.0 * (cr * (double)sxi - ci * (double)sxr);
-    sv[2] += 2.0 * (cr * (double)syi - ci * (double)syr);
-    sv[3] += 2.0 * (cr * (double)szi - ci * (double)szr);
+    take(1);
+#pragma unroll
+    for (int m = 3; m >= 0; --m) {
+      const int p = r + m + 1;
+      if (p < ZR) {
+        const Quad<T> q = u.template quad<true>(at.own + p * plane, true);
+        add(dw[2][m], q.re, q.im);
+      } else {
+        const int g = (p - ZR) / ZR;
+        const Quad<T> q = u.template quad<PERIODIC>(at.zr[g] + ((p - ZR) % ZR) * plane, at.ok >> (14 + g) & 1);
+        add(dw[2][m], q.re, q.im);
+      }
+      if (sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+    }
+    take(2);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double cr = (double)c.re[i], ci = (double)c.im[i];
+      sv[0] = fmad(cr, cr, fmad(ci, ci, sv[0]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
 // ITEMS: the body runs once per item of a loop (the persistent form)
-template <typename T, int N, int ZS, bool PERIODIC, bool ITEMS = false>
+template <typename T, int N, int ZR, bool PERIODIC, bool ITEMS = false>
 __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, unsigned char* smem_raw) {
   using T2 = typename Vec2<T>::type;
-  constexpr int plane = N * N;
-  constexpr int NP = plane * N;
-  constexpr int ZN = N / ZS;                      // planes per thread
-  constexpr int HALF = ((plane + 63) / 64) * 64;  // threads per column half (whole waves)
+  using V16 = typename Wide<T>::type;
+  constexpr int plane = N * N / 4;  // quads
+  constexpr int NP = N * N * N;
+  constexpr int TILES = NP / (4 * ZR);
   const int n_atoms = a.nl.n_atoms;
   const int S = a.nl.n_ent;
   const gp<const int> atom_start = G(a.nl.atom_start);
@@ -245,11 +543,10 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
   const gp<const int> color_start = G(a.color_start);
   const gp<const int> color_atoms = G(a.color_atoms);
   const gp<const double2> phAJ = G(a.phAJ);
-  T2* u = reinterpret_cast<T2*>(smem_raw);
-  constexpr size_t ubytes = ((size_t)NP * sizeof(T2) + 15) & ~(size_t)15;
-  double2* eu = reinterpret_cast<double2*>(smem_raw + ubytes);               // [n_atoms][4]
-  double* red = reinterpret_cast<double*>(eu + (size_t)n_atoms * kMaxProj);  // [16][8]
-  double* ja = red + 16 * 8;                                                 // [n_atoms][4]
+  const LdsOrb<T, N> u{reinterpret_cast<V16*>(smem_raw)};
+  double2* eu = reinterpret_cast<double2*>(smem_raw + LdsOrb<T, N>::kBytes);  // [n_atoms][4]
+  double* red = reinterpret_cast<double*>(eu + (size_t)n_atoms * kMaxProj);   // [16][4]
+  double* ja = red + 16 * 4;                                                  // [n_atoms][4]
 
   const int k = o / a.g.n_orb;
   // in the persistent form the thread index is opaque to the compiler, so
@@ -258,62 +555,29 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
   int tid = threadIdx.x;
   if (ITEMS) asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
-  const int half = (ZS == 2 && tid >= HALF) ? 1 : 0;  // uniform per wavefront
-  const int ctid = tid - half * HALF;
-  const int tx = ctid % N, ty = ctid / N;
-  const bool active = ctid < plane;
+  const bool active = tid < TILES;
+  const int tile = active ? tid : 0;
 
-  Nbr nb;
-  bool ok[16];
-#pragma unroll
-  for (int m = 1; m <= 4; ++m) {
-    const int xp = tx + m, xm = tx - m, yp = ty + m, ym = ty - m;
-    ok[m - 1] = PERIODIC || xp < N;
-    ok[4 + m - 1] = PERIODIC || xm >= 0;
-    ok[8 + m - 1] = PERIODIC || yp < N;
-    ok[12 + m - 1] = PERIODIC || ym >= 0;
-    nb.xp[m - 1] = ty * N + (xp % N);
-    nb.xm[m - 1] = ty * N + ((xm + N) % N);
-    nb.yp[m - 1] = (yp % N) * N + tx;
-    nb.ym[m - 1] = ((ym + N) % N) * N + tx;
-  }
-  nb.c = active ? ctid : 0;
-
+  if (!PERIODIC && tid == 0) u.set(LdsOrb<T, N>::kQuads, Quad<T>{});
   const gp<T2> wg = G(a.w) + (size_t)o * NP;
-  T2 un[ZN];
-  const int z0 = half * ZN;
+  if (active) {
+    const int own = tile_at<N, ZR>(tile).own;
 #pragma unroll
-  for (int zz = 0; zz < ZN; ++zz) {
-    T2 v;
-    v.x = v.y = 0;
-    if (active) v = wg[(z0 + zz) * plane + nb.c];
-    if (active) u[(z0 + zz) * plane + nb.c] = v;
+    for (int r = 0; r < ZR; ++r)
+      u.set(own + r * plane, load_quad((gp<const V16>)(wg + 4 * (own + r * plane)), T(0)));
   }
 
-  Coef<T> cf;
-  {
-    // wave-uniform: the k-point table is read with scalar loads
-    const gp<const T> ck = G(a.coef) + (size_t)k * kCoef;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      cf.cx[m] = a.lapc[0][m];
-      cf.cy[m] = a.lapc[1][m];
-      cf.cz[m] = a.lapc[2][m];
-      cf.bx[m] = ck[m];
-      cf.by[m] = ck[4 + m];
-      cf.bz[m] = ck[8 + m];
-    }
-    cf.diag = ck[12];
-    cf.ext = cf.ez = 0;
-    if (!PERIODIC && a.efield) {
-      // E . r with r from the box centre; the z part is added per plane
-      const gp<const double> ef = G(a.efield);
-      cf.ext = (T)(ef[0] * (tx - 0.5 * (N - 1)) * a.g.h1 + ef[1] * (ty - 0.5 * (N - 1)) * a.g.h2 -
-                   ef[2] * a.g.h3 * 0.5 * (N - 1));
-      cf.ez = (T)(ef[2] * a.g.h3);
-    }
+  const cp<T> row = (cp<T>)(a.coef) + (size_t)k * kCoef;
+  FieldE<T> fe{0, 0, 0};
+  if (!PERIODIC && a.efield) {
+    // E . r with r from the box centre; the steps inside the tile are added per point
+    const gp<const double> ef = G(a.efield);
+    const int qx = tile % (N / 4), y = tile / (N / 4) % N, z0 = tile / (N / 4 * N) * ZR;
+    fe.ext = (T)(ef[0] * (4 * qx - 0.5 * (N - 1)) * a.g.h1 + ef[1] * (y - 0.5 * (N - 1)) * a.g.h2 +
+                 ef[2] * (z0 - 0.5 * (N - 1)) * a.g.h3);
+    fe.ex = (T)(ef[0] * a.g.h1);
+    fe.ez = (T)(ef[2] * a.g.h3);
   }
-  const bool length = !PERIODIC && a.efield != nullptr;
   const gp<const double2> phk = G(a.nl.phk) + (size_t)k * S;
   const gp<const double2> phkA = G(a.phkA) + (size_t)k * S;  // exp(i kappa . x_e) of this step
   __syncthreads();
@@ -324,11 +588,12 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
       const int e0 = atom_start[at], e1 = atom_start[at + 1];
       double acc[2 * kMaxProj] = {0, 0, 0, 0, 0, 0, 0, 0};
       for (int e = e0 + lane; e < e1; e += 64) {
-        const T2 v = u[ent_idx[e]];
+        const T* const pt = u.point(ent_idx[e]);
+        const T vx = pt[0], vy = pt[LdsOrb<T, N>::kImag];
         const double2 ph = phkA[e];
         const double pr = ph.x, pim = ph.y;
-        const double gr = pr * (double)v.x - pim * (double)v.y;
-        const double gi = pr * (double)v.y + pim * (double)v.x;
+        const double gr = pr * (double)vx - pim * (double)vy;
+        const double gi = pr * (double)vy + pim * (double)vx;
 #pragma unroll
         for (int p = 0; p < kMaxProj; ++p) {
           const double b = ent_beta[(size_t)e * kMaxProj + p];
@@ -338,7 +603,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
       }
       // value 2p (real) sits in lanes 16p.., value 2p + 1 (imaginary) 8 lanes up
       const double tot = wave_sum8(acc, lane);
-      const double im = __shfl_down(tot, 8, 64);
+      const double im = dpp<kXor8>(tot);
       if ((lane & 15) == 0) {
         const int p = lane >> 4;
         const double E = atom_E[at * kMaxProj + p] * a.dV;
@@ -358,19 +623,13 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
   for (int s = 4; s >= 1; --s) {
     // ---- local part of h u_s and the Horner update
     const T tau = (T)(a.dt / s);
-    {
-      const Nbr sb = opaque(nb);
-      if (active) {
-        if (ZS == 1 || half == 0)
-          stencil_part<T, N, ZN, 0, PERIODIC>(u, G(a.V), cf, sb, ok, wg, un, tau, length);
-        else
-          stencil_part<T, N, ZN, (ZS == 2 ? ZN : 0), PERIODIC>(u, G(a.V), cf, sb, ok, wg, un, tau, length);
-      }
-    }
+    Quad<T> un[ZR];
+    const int own = tile_at<N, ZR>(tile).own;
+    if (active) stencil_tile<T, N, ZR, PERIODIC>(u, G(a.V), row, fe, tile_at<N, ZR>(opaque_i(tile)), wg, un, tau);
     __syncthreads();
     if (active) {
 #pragma unroll
-      for (int zz = 0; zz < ZN; ++zz) u[(z0 + zz) * plane + nb.c] = un[zz];
+      for (int r = 0; r < ZR; ++r) u.set(own + r * plane, un[r]);
     }
     __syncthreads();
     // ---- nonlocal part of the stage, scattered over each atom's sphere:
@@ -381,46 +640,42 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
       if (one_colour) {
         for (int at = wave; at < n_atoms; at += nwaves) {
           const int e0 = atom_start[at], e1 = atom_start[at + 1];
-          {
-            double2 E4[kMaxProj];
+          double2 E4[kMaxProj];
 #pragma unroll
-            for (int p = 0; p < kMaxProj; ++p) E4[p] = eu[at * kMaxProj + p];
-            for (int e = e0 + lane; e < e1; e += 64) {
-              const int idx = ent_idx[e];
-              const double2 ph = phkA[e];
-              const double pr = ph.x, pim = ph.y;
-              double sr = 0.0, si = 0.0;
+          for (int p = 0; p < kMaxProj; ++p) E4[p] = eu[at * kMaxProj + p];
+          // the completed value of a point goes straight into the next
+          // stage's projection (not needed after the last one): one read of
+          // the tables serves both
+          double acc[2 * kMaxProj] = {0, 0, 0, 0, 0, 0, 0, 0};
+          for (int e = e0 + lane; e < e1; e += 64) {
+            const int idx = ent_idx[e];
+            const double2 ph = phkA[e];
+            const double pr = ph.x, pim = ph.y;
+            double b[kMaxProj];
 #pragma unroll
-              for (int p = 0; p < kMaxProj; ++p) {
-                const double b = ent_beta[(size_t)e * kMaxProj + p];
-                sr += b * E4[p].x;
-                si += b * E4[p].y;
-              }
-              const double cr = pr * sr + pim * si, ci = pr * si - pim * sr;
-              T2 v = u[idx];
-              v.x += (T)(taud * ci);
-              v.y -= (T)(taud * cr);
-              u[idx] = v;
+            for (int p = 0; p < kMaxProj; ++p) b[p] = ent_beta[(size_t)e * kMaxProj + p];
+            double sr = 0.0, si = 0.0;
+#pragma unroll
+            for (int p = 0; p < kMaxProj; ++p) {
+              sr += b[p] * E4[p].x;
+              si += b[p] * E4[p].y;
+            }
+            const double cr = pr * sr + pim * si, ci = pr * si - pim * sr;
+            T* const pt = u.point(idx);
+            const T vx = pt[0] + (T)(taud * ci), vy = pt[LdsOrb<T, N>::kImag] - (T)(taud * cr);
+            pt[0] = vx;
+            pt[LdsOrb<T, N>::kImag] = vy;
+            const double gr = pr * (double)vx - pim * (double)vy;
+            const double gi = pr * (double)vy + pim * (double)vx;
+#pragma unroll
+            for (int p = 0; p < kMaxProj; ++p) {
+              acc[2 * p] += b[p] * gr;
+              acc[2 * p + 1] += b[p] * gi;
             }
           }
-          // the same lanes read back the same points: no barrier needed
           if (s > 1) {
-            double acc[2 * kMaxProj] = {0, 0, 0, 0, 0, 0, 0, 0};
-            for (int e = e0 + lane; e < e1; e += 64) {
-              const T2 v = u[ent_idx[e]];
-              const double2 ph = phkA[e];
-              const double pr = ph.x, pim = ph.y;
-              const double gr = pr * (double)v.x - pim * (double)v.y;
-              const double gi = pr * (double)v.y + pim * (double)v.x;
-#pragma unroll
-              for (int p = 0; p < kMaxProj; ++p) {
-                const double b = ent_beta[(size_t)e * kMaxProj + p];
-                acc[2 * p] += b * gr;
-                acc[2 * p + 1] += b * gi;
-              }
-            }
             const double tot = wave_sum8(acc, lane);
-            const double im = __shfl_down(tot, 8, 64);
+            const double im = dpp<kXor8>(tot);
             if ((lane & 15) == 0) {
               const int p = lane >> 4;
               const double E = atom_E[at * kMaxProj + p] * a.dV;
@@ -449,10 +704,10 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
                 si += b * E4[p].y;
               }
               const double cr = pr * sr + pim * si, ci = pr * si - pim * sr;
-              T2 v = u[idx];
-              v.x += (T)(taud * ci);
-              v.y -= (T)(taud * cr);
-              u[idx] = v;
+              T* const pt = u.point(idx);
+              const T vx = pt[0] + (T)(taud * ci), vy = pt[LdsOrb<T, N>::kImag] - (T)(taud * cr);
+              pt[0] = vx;
+              pt[LdsOrb<T, N>::kImag] = vy;
             }
           }
           __syncthreads();
@@ -465,26 +720,25 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
   // ---- w_new to HBM, observables for the current
   double sv[4] = {0, 0, 0, 0};
   {
-    const Nbr fb = opaque(nb);
     if (active) {
+      const TileAt<ZR> at = tile_at<N, ZR>(opaque_i(tile));
 #pragma unroll
-      for (int zz = 0; zz < ZN; ++zz) wg[(z0 + zz) * plane + fb.c] = u[(z0 + zz) * plane + fb.c];
-      // whole columns, by the threads of the first column half: the summation
-      // order is the same for either column split
-      if (half == 0) observe_part<T, N, N, 0, PERIODIC>(u, a.dhc, fb, ok, sv);
+      for (int r = 0; r < ZR; ++r)
+        store_quad((gp<V16>)(wg + 4 * (at.own + r * plane)), u.get(at.own + r * plane, T(0)));
+      observe_tile<T, N, ZR, PERIODIC>(u, a.dhc, at, sv);
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) sv[i] = wave_sum(sv[i]);
+  for (int i = 0; i < 4; ++i) sv[i] = wave_sum(i == 0 ? sv[0] : 2.0 * sv[i]);
   if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[wave * 8 + i] = sv[i];
+    for (int i = 0; i < 4; ++i) red[wave * 4 + i] = sv[i];
   }
   __syncthreads();
   if (tid < 6) {
     double acc = 0;
     if (tid < 4)
-      for (int wv = 0; wv < nwaves; ++wv) acc += red[wv * 8 + tid];
+      for (int wv = 0; wv < nwaves; ++wv) acc += red[wv * 4 + tid];
     G(a.obs)[(size_t)o * 8 + tid] = acc;  // slots 4, 5 (kinetic, local) stay 0 here
   }
   __syncthreads();
@@ -507,11 +761,12 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = 0.0;
         for (int e = e0 + lane; e < e1; e += 64) {
-          const T2 v = u[ent_idx[e]];
+          const T* const pt = u.point(ent_idx[e]);
+          const T vx = pt[0], vy = pt[LdsOrb<T, N>::kImag];
           const double2 p1 = phk[e], p2 = phAJ[e];
           const double pr = p1.x * p2.x - p1.y * p2.y, pim = p1.x * p2.y + p1.y * p2.x;
-          const double gr = pr * (double)v.x - pim * (double)v.y;
-          const double gi = pr * (double)v.y + pim * (double)v.x;
+          const double gr = pr * (double)vx - pim * (double)vy;
+          const double gi = pr * (double)vy + pim * (double)vx;
           const double m0 = pass == 0 ? 1.0 : ent_x[3 * (size_t)e + 1];
           const double m1 = ent_x[3 * (size_t)e + 2 * pass];
 #pragma unroll
@@ -525,16 +780,17 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
           }
         }
         const double tot = wave_sum16(acc, lane) * a.dV;
-        const double im = __shfl_down(tot, 4, 64);
-        if (pass == 0) {
-          ur = __shfl(tot, 8 * pl, 64);
-          ui = __shfl(im, 8 * pl, 64);
+        // every quad holds its full sum, so lane ^ 7 is the other part's quad
+        const double im = dpp<kXor7>(tot);
+        if (pass == 0) {  // u_p of the lower half's moment 0, for both halves
+          ur = swap32(tot, tot).x;
+          ui = swap32(im, im).x;
         }
         // E_p |u_p|^2 for m = 0, 2 E_p Im(conj(v_p) u_p) for m = 1..3, summed over p
         const int m = 2 * pass + mml;
         double c = (m == 0) ? E * (ur * ur + ui * ui) : 2.0 * E * (tot * ui - im * ur);
-        c += __shfl_xor(c, 8, 64);
-        c += __shfl_xor(c, 16, 64);
+        c += dpp<kXor8>(c);
+        c = sum16(c);
         if ((lane & 31) == 0) ja[at * 4 + (m == 0 ? 3 : m - 1)] = c;
       }
     }
@@ -547,11 +803,31 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
   }
 }
 
+// Points along z of a thread's tile, fixed per grid size and precision so that
+// every path computes the same bits; workgroup size: the tiles' threads,
+// rounded up to whole wavefronts and to eight of them, so that the nonlocal
+// phases (one wavefront per atom) run the eight atoms of a diamond cell side by
+// side; waves per SIMD the registers have to leave room for. At 20^3 four rows
+// give 500 tiles (512 threads, 64 KB, two workgroups per CU) in complex FP32
+// and two rows 1000 tiles (1024 threads, 128 KB, one per CU) in complex128;
+// 16^3 takes 512 and 12^3 432 tiles, 24^3 (complex FP32 only, 110 KB) 864.
+__host__ __device__ constexpr int fused_rows_of(int n, size_t real) {
+  return n == 12 ? 1 : (n == 16 ? 2 : (n == 20 && real == 8 ? 2 : 4));
+}
+template <typename T, int N>
+struct FusedShape {
+  static constexpr int kRows = fused_rows_of(N, sizeof(T));
+  static constexpr int kTiles = N * N * N / (4 * kRows);
+  static constexpr int kThreads = kTiles <= 512 ? 512 : (kTiles + 63) / 64 * 64;
+  static constexpr int kWaves = 4;
+};
+int fused_rows(int n, size_t elem) { return fused_rows_of(n, elem / 2); }
+
 // one orbital per workgroup
-template <typename T, int N, int ZS, bool PERIODIC, int MAXT>
-__global__ __launch_bounds__(MAXT) void k_fused(FusedArgs<T> a) {
+template <typename T, int N, bool PERIODIC>
+__global__ __launch_bounds__((FusedShape<T, N>::kThreads), (FusedShape<T, N>::kWaves)) void k_fused(FusedArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  fused_body<T, N, ZS, PERIODIC>(a, blockIdx.x, smem_raw);
+  fused_body<T, N, FusedShape<T, N>::kRows, PERIODIC>(a, blockIdx.x, smem_raw);
 }
 
 // Persistent form for batches of cells with the same grid: a fixed grid of
@@ -559,10 +835,9 @@ __global__ __launch_bounds__(MAXT) void k_fused(FusedArgs<T> a) {
 // (largest-cell-first) order until the list is exhausted; every item is
 // computed exactly as in k_fused, so the result does not depend on which
 // workgroup takes it.
-template <typename T, int N, int ZS, bool PERIODIC, int MAXT>
-__global__ __launch_bounds__(MAXT, (MAXT <= 512 && sizeof(T) == 4) ? 4 : 1) void k_fused_persistent(const FusedArgs<T>* __restrict__ cells,
-                                                           const int2* __restrict__ items, int n_items,
-                                                           int* queue) {
+template <typename T, int N, bool PERIODIC>
+__global__ __launch_bounds__((FusedShape<T, N>::kThreads), (FusedShape<T, N>::kWaves)) void k_fused_persistent(
+    const FusedArgs<T>* __restrict__ cells, const int2* __restrict__ items, int n_items, int* queue) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ int next;
   if (threadIdx.x == 0) next = atomicAdd(queue, 1);
@@ -578,7 +853,7 @@ __global__ __launch_bounds__(MAXT, (MAXT <= 512 && sizeof(T) == 4) ? 4 : 1) void
     // cell's arguments are read with scalar loads as kernel arguments are
     const int2 ci = items[it];
     const int cx = __builtin_amdgcn_readfirstlane(ci.x), orb = __builtin_amdgcn_readfirstlane(ci.y);
-    fused_body<T, N, ZS, PERIODIC, true>(cells[cx], orb, smem_raw);
+    fused_body<T, N, FusedShape<T, N>::kRows, PERIODIC, true>(cells[cx], orb, smem_raw);
     __syncthreads();
     if (threadIdx.x == 0) next = claim;
     __syncthreads();
@@ -587,28 +862,27 @@ __global__ __launch_bounds__(MAXT, (MAXT <= 512 && sizeof(T) == 4) ? 4 : 1) void
   }
 }
 
-// per k-point coefficients of the step in the stage precision (from kappa at
-// the step midpoint): kappa_mu d_m / h_mu and the diagonal
-// -1/2 sum_mu c_0 / h_mu^2 + |kappa|^2 / 2
+// per k-point row of coefficients of the step in the stage precision (from
+// kappa at the step midpoint): -1/2 c_m / h_mu^2 and kappa_mu d_m / h_mu per
+// axis, and the diagonal -1/2 sum_mu c_0 / h_mu^2 + |kappa|^2 / 2
 template <typename T>
-__device__ __forceinline__ void fused_coef_k(const double* __restrict__ kappa, const double (&dh)[3][4], double cdiag,
-                                             T* __restrict__ coef, int k) {
-  const double kx = kappa[3 * k], ky = kappa[3 * k + 1], kz = kappa[3 * k + 2];
+__device__ __forceinline__ void fused_coef_k(const double* __restrict__ kappa, const double (&lap)[3][5],
+                                             const double (&dh)[3][4], double cdiag, T* __restrict__ coef, int k) {
+  const double kap[3] = {kappa[3 * k], kappa[3 * k + 1], kappa[3 * k + 2]};
   T* c = coef + (size_t)k * kCoef;
-  for (int m = 0; m < 4; ++m) {
-    c[m] = (T)(kx * dh[0][m]);
-    c[4 + m] = (T)(ky * dh[1][m]);
-    c[8 + m] = (T)(kz * dh[2][m]);
-  }
-  c[12] = (T)(cdiag + 0.5 * (kx * kx + ky * ky + kz * kz));
-  c[13] = c[14] = c[15] = (T)0;
+  for (int mu = 0; mu < 3; ++mu)
+    for (int m = 0; m < 4; ++m) {
+      c[8 * mu + m] = (T)lap[mu][m + 1];
+      c[8 * mu + kCoefB + m] = (T)(kap[mu] * dh[mu][m]);
+    }
+  c[kCoefDiag] = (T)(cdiag + 0.5 * (kap[0] * kap[0] + kap[1] * kap[1] + kap[2] * kap[2]));
 }
 
 template <typename T>
 __global__ void k_fused_coef(const double* __restrict__ kappa, int n_k, FusedCoefIn in, T* __restrict__ coef) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n_k) return;
-  fused_coef_k<T>(kappa, in.dh, in.cdiag, coef, k);
+  fused_coef_k<T>(kappa, in.lap, in.dh, in.cdiag, coef, k);
 }
 
 // exp(i kappa . x_e) = exp(i k . x_e) exp(i A . x_e / c) for every k-point and
@@ -633,7 +907,7 @@ __global__ void k_fused_coef_group(const ParamCell* __restrict__ tab) {
   const ParamCell& c = tab[blockIdx.y];
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= c.n_k) return;
-  fused_coef_k<T>(c.kappa, c.dh, c.cdiag, static_cast<T*>(c.coef), k);
+  fused_coef_k<T>(c.kappa, c.lap, c.dh, c.cdiag, static_cast<T*>(c.coef), k);
 }
 
 __global__ void k_fused_phase_group(const ParamCell* __restrict__ tab) {
@@ -657,8 +931,8 @@ template hipError_t launch_fused_coef_group<float>(const ParamCell*, int, int, l
 template <typename T>
 hipError_t launch_fused_coef(const FusedArgs<T>& a, hipStream_t s) {
   FusedCoefIn in;
-  for (int i = 0; i < 3; ++i)
-    for (int m = 0; m < 4; ++m) in.dh[i][m] = a.dh[i][m];
+  std::memcpy(in.lap, a.lap, sizeof(in.lap));
+  std::memcpy(in.dh, a.dh, sizeof(in.dh));
   in.cdiag = a.cdiag;
   const int nk = a.g.n_k;
   hipLaunchKernelGGL((k_fused_coef<T>), dim3((unsigned)((nk + 63) / 64)), dim3(64), 0, s, a.kappa, nk, in, a.coef);
@@ -674,21 +948,22 @@ template hipError_t launch_fused_coef<float>(const FusedArgs<float>&, hipStream_
 
 // the per-k coefficient table alone (the per-stage kernels read it too)
 template <typename T>
-hipError_t launch_coef_table(const double* kappa, int n_k, const double dh[3][4], double cdiag, T* coef,
+hipError_t launch_coef_table(const double* kappa, int n_k, const double lap[3][5], const double dh[3][4], double cdiag, T* coef,
                              hipStream_t s) {
   FusedCoefIn in;
-  for (int i = 0; i < 3; ++i)
-    for (int m = 0; m < 4; ++m) in.dh[i][m] = dh[i][m];
+  std::memcpy(in.lap, lap, sizeof(in.lap));
+  std::memcpy(in.dh, dh, sizeof(in.dh));
   in.cdiag = cdiag;
   hipLaunchKernelGGL((k_fused_coef<T>), dim3((unsigned)((n_k + 63) / 64)), dim3(64), 0, s, kappa, n_k, in, coef);
   return hipGetLastError();
 }
-template hipError_t launch_coef_table<double>(const double*, int, const double[3][4], double, double*, hipStream_t);
-template hipError_t launch_coef_table<float>(const double*, int, const double[3][4], double, float*, hipStream_t);
+template hipError_t launch_coef_table<double>(const double*, int, const double[3][5], const double[3][4], double, double*, hipStream_t);
+template hipError_t launch_coef_table<float>(const double*, int, const double[3][5], const double[3][4], double, float*, hipStream_t);
 
 size_t fused_lds_bytes(const Geometry& g, int n_atoms, size_t elem) {
   const size_t N = (size_t)g.n1 * g.n2 * g.n3;
-  return ((N * elem + 15) & ~(size_t)15) + (size_t)n_atoms * kMaxProj * sizeof(double2) + 16 * 8 * sizeof(double) +
+  // the orbital with a zero word per 16-byte word array (LdsOrb), eu, red, ja
+  return (N * elem + elem / 4 * 16) + (size_t)n_atoms * kMaxProj * sizeof(double2) + 16 * 4 * sizeof(double) +
          (size_t)n_atoms * 4 * sizeof(double);
 }
 
@@ -699,31 +974,14 @@ bool fused_supported(const Geometry& g, int n_atoms, size_t elem) {
   return fused_lds_bytes(g, n_atoms, elem) <= 160 * 1024;
 }
 
-// Workgroup size: the column threads, rounded up to eight wavefronts so that
-// the nonlocal phases (one wavefront per atom) run the eight atoms of a
-// diamond cell side by side; the extra wavefronts idle through the stencil.
-// Results do not depend on the count (inactive threads add exact zeros).
-template <int N, int ZS>
-constexpr int fused_threads() {
-  return ZS * (((N * N + 63) / 64) * 64) < 512 ? 512 : ZS * (((N * N + 63) / 64) * 64);
-}
-
-// launch bound: 512, or the exact count above it (24^3: 576 threads, one
-// workgroup per CU by LDS, so up to 168 registers per lane)
-template <int N, int ZS>
-constexpr int fused_bound() {
-  return fused_threads<N, ZS>() <= 512 ? 512 : fused_threads<N, ZS>();
-}
-
-template <typename T, int N, int ZS>
+template <typename T, int N>
 static void launch_n(bool periodic, const FusedArgs<T>& a, size_t lds, hipStream_t s) {
-  constexpr int threads = fused_threads<N, ZS>();
-  constexpr int bound = fused_bound<N, ZS>();
+  constexpr int threads = FusedShape<T, N>::kThreads;
   const dim3 grid((unsigned)((size_t)a.g.n_orb * a.g.n_k));
   if (periodic)
-    hipLaunchKernelGGL((k_fused<T, N, ZS, true, bound>), grid, dim3(threads), lds, s, a);
+    hipLaunchKernelGGL((k_fused<T, N, true>), grid, dim3(threads), lds, s, a);
   else
-    hipLaunchKernelGGL((k_fused<T, N, ZS, false, bound>), grid, dim3(threads), lds, s, a);
+    hipLaunchKernelGGL((k_fused<T, N, false>), grid, dim3(threads), lds, s, a);
 }
 
 template <typename T>
@@ -733,62 +991,53 @@ hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s) {
   const size_t lds = fused_lds_bytes(a.g, a.nl.n_atoms, sizeof(T2));
   const bool per = a.g.periodic != 0;
   switch (a.g.n3) {
-    case 12: launch_n<T, 12, 2>(per, a, lds, s); break;
-    case 16: launch_n<T, 16, 2>(per, a, lds, s); break;
-    case 20: launch_n<T, 20, 1>(per, a, lds, s); break;
-    default: launch_n<T, 24, 1>(per, a, lds, s); break;
+    case 12: launch_n<T, 12>(per, a, lds, s); break;
+    case 16: launch_n<T, 16>(per, a, lds, s); break;
+    case 20: launch_n<T, 20>(per, a, lds, s); break;
+    default:
+      if constexpr (sizeof(T) == 4) launch_n<T, 24>(per, a, lds, s);  // complex128 does not fit
+      break;
   }
   return hipGetLastError();
 }
-
-// Column split per grid size, fixed so that every path computes the same
-// bits: measured on MI355X, splitting the 12^3 and 16^3 columns between two
-// wavefronts is faster; at 20^3 the split spills registers and is slower, and
-// at 24^3 (576 column threads) two halves would exceed 1024 threads.
-int fused_column_split(int n) { return n <= 16 ? 2 : 1; }
 
 template hipError_t launch_fused<double>(const FusedArgs<double>&, hipStream_t);
 template hipError_t launch_fused<float>(const FusedArgs<float>&, hipStream_t);
 
-template <typename T, int N, int ZS>
+template <typename T, int N>
 static void launch_pers_n(bool periodic, const FusedArgs<T>* cells, const int2* items, int n_items,
                           int* queue, int wgs, size_t lds, hipStream_t s) {
-  constexpr int threads = fused_threads<N, ZS>();
-  constexpr int bound = fused_bound<N, ZS>();
+  constexpr int threads = FusedShape<T, N>::kThreads;
   if (periodic)
-    hipLaunchKernelGGL((k_fused_persistent<T, N, ZS, true, bound>), dim3(wgs), dim3(threads), lds, s, cells,
-                       items, n_items, queue);
+    hipLaunchKernelGGL((k_fused_persistent<T, N, true>), dim3(wgs), dim3(threads), lds, s, cells, items, n_items,
+                       queue);
   else
-    hipLaunchKernelGGL((k_fused_persistent<T, N, ZS, false, bound>), dim3(wgs), dim3(threads), lds, s, cells,
-                       items, n_items, queue);
+    hipLaunchKernelGGL((k_fused_persistent<T, N, false>), dim3(wgs), dim3(threads), lds, s, cells, items, n_items,
+                       queue);
 }
 
 template <typename T>
-hipError_t launch_fused_persistent(int n, int zs, bool periodic, const FusedArgs<T>* cells, const int2* items,
-                                   int n_items, int* queue, int wgs, size_t lds, hipStream_t s) {
+hipError_t launch_fused_persistent(int n, bool periodic, const FusedArgs<T>* cells, const int2* items, int n_items,
+                                   int* queue, int wgs, size_t lds, hipStream_t s) {
   if (wgs < 1 || n_items < 1) return hipErrorInvalidValue;
-  if (zs == 2) {
-    switch (n) {
-      case 12: launch_pers_n<T, 12, 2>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      case 16: launch_pers_n<T, 16, 2>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      case 20: launch_pers_n<T, 20, 2>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    switch (n) {
-      case 12: launch_pers_n<T, 12, 1>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      case 16: launch_pers_n<T, 16, 1>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      case 20: launch_pers_n<T, 20, 1>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      case 24: launch_pers_n<T, 24, 1>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
-      default: return hipErrorInvalidValue;
-    }
+  switch (n) {
+    case 12: launch_pers_n<T, 12>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
+    case 16: launch_pers_n<T, 16>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
+    case 20: launch_pers_n<T, 20>(periodic, cells, items, n_items, queue, wgs, lds, s); break;
+    case 24:
+      if constexpr (sizeof(T) == 4) {
+        launch_pers_n<T, 24>(periodic, cells, items, n_items, queue, wgs, lds, s);
+        break;
+      }
+      return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template hipError_t launch_fused_persistent<double>(int, int, bool, const FusedArgs<double>*, const int2*, int,
-                                                    int*, int, size_t, hipStream_t);
-template hipError_t launch_fused_persistent<float>(int, int, bool, const FusedArgs<float>*, const int2*, int,
-                                                   int*, int, size_t, hipStream_t);
+template hipError_t launch_fused_persistent<double>(int, bool, const FusedArgs<double>*, const int2*, int, int*, int,
+                                                    size_t, hipStream_t);
+template hipError_t launch_fused_persistent<float>(int, bool, const FusedArgs<float>*, const int2*, int, int*, int,
+                                                   size_t, hipStream_t);
 
 }  // namespace td

@@ -271,15 +271,15 @@ __global__ __launch_bounds__(1024) void k_stage(StageArgs<T> a) {
     cx[m] = a.lapc[0][m];
     cy[m] = a.lapc[1][m];
     cz[m] = a.lapc[2][m];
-    bx[m] = ck[m];
-    by[m] = ck[4 + m];
-    bz[m] = ck[8 + m];
+    bx[m] = ck[kCoefB + m];
+    by[m] = ck[8 + kCoefB + m];
+    bz[m] = ck[16 + kCoefB + m];
   }
   const T tau = (T)a.tau;
   const T tau_re = (T)a.tau_re;
   // diagonal without V: kinetic |kappa|^2 / 2 and, in the length gauge, the
   // field's in-plane part E_x x + E_y y (the z part is added per plane)
-  T dgx = ck[12], ez = 0;
+  T dgx = ck[kCoefDiag], ez = 0;
   if (a.efield) {
     const double xr = (gx - 0.5 * (n1 - 1)) * g.h1;
     const double yr = (gy - 0.5 * (n2 - 1)) * g.h2;
