@@ -275,23 +275,77 @@ MggaArgs mgga_args(const tddft_ctx* c) {
 
 bool is_mgga(const tddft_ctx* c) { return c->cfg.xc == TDDFT_XC_TB09 || c->cfg.xc == TDDFT_XC_BJ; }
 
+// tolerance of the norm watchdog (0: off)
+double norm_tol(const tddft_ctx* c) { return (c->cfg.flags & TDDFT_FLAG_NORM_WATCHDOG) ? 1e-3 : 0.0; }
+
+// the arguments of the end of a step
+TailCell tail_cell(const tddft_ctx* c) {
+  TailCell t{};
+  t.w = c->W;
+  t.kw = c->kw_d;
+  t.n_orb = c->cfg.n_orb;
+  t.n_k = c->cfg.n_k;
+  t.nchunks = c->rho_nchunks;
+  t.chunk = c->rho_chunk;
+  // with a single chunk of orbitals the partial sums are the sums: written in
+  // place, no reduction (0 + x = x, the same bits)
+  t.rho_out = c->rho_nchunks == 1 ? c->rho : c->rho_part;
+  t.rho_part = c->rho_part;
+  t.rho = c->rho;
+  t.fft = c->fft;
+  t.Kfft = c->Kfft;
+  t.vh_scale = c->vh_scale;
+  t.Vloc = c->Vloc;
+  t.Vd = c->Vd;
+  t.Vf = c->Vf;
+  t.vh = c->vh;
+  t.exc = c->exc;
+  t.obs = c->obs;
+  t.tiles = c->fused ? 1 : c->g.tiles_x * c->g.tiles_y * c->g.zslabs;
+  t.jnl = c->jnl;
+  t.use_nl = c->nl.n_atoms > 0 ? 1 : 0;
+  t.kappaJ = c->kappaJ;
+  t.dV = c->dV;
+  t.volume = c->volume;
+  t.counter = c->counter;
+  t.Jtab = c->Jtab;
+  t.scalars = c->scalars;
+  t.nanflag = c->nanflag;
+  t.norm_tol = norm_tol(c);
+  return t;
+}
+
+// rho and the potential of the current orbitals; with_finish: also the
+// current of the step (its observables are formed), on a workgroup of the
+// density pass
 template <typename T>
-tddft_status enqueue_density_potential(tddft_ctx* c) {
+tddft_status enqueue_density_potential(tddft_ctx* c, bool with_finish = false) {
   const int N = (int)c->N;
   const bool mgga = is_mgga(c);
-  // with a single chunk of orbitals the partial sums are the sums: write them
-  // in place and skip the reduction (0 + x = x, the same bits)
   const bool one = c->rho_nchunks == 1;
+  const TailCell tail = tail_cell(c);
+  const bool planes = c->potential_set && poisson_planes(c->g.periodic, c->cfg.hartree, c->g.n1, c->g.n2);
   if (mgga) {
+    if (with_finish) LAUNCH(launch_finish(tail, 1, c->stream), "finish");
     // rho and the kinetic energy density with kappa at the orbitals' time
     LAUNCH(launch_rho_tau_partial<T>(as2<T>(c->W), c->kw_d, c->kappaJ, mgga_args(c), c->rho_chunk,
                                      one ? c->rho : c->rho_part, one ? c->tau : c->tau_part, c->stream),
            "rho_tau_partial");
     if (!one) LAUNCH(launch_rho_reduce(c->tau_part, c->rho_nchunks, N, c->tau, c->stream), "tau_reduce");
   } else {
-    LAUNCH(launch_rho_partial<T>(as2<T>(c->W), c->kw_d, c->cfg.n_orb, c->cfg.n_k, N, c->rho_chunk,
-                                 one ? c->rho : c->rho_part, c->stream),
-           "rho_partial");
+    LAUNCH(launch_density<T>(tail, N, with_finish ? 1 : 0, c->stream), "density");
+  }
+  if (planes) {
+    const int n1 = c->g.n1, n2 = c->g.n2, n3 = c->g.n3;
+    LAUNCH(launch_poisson_forward(tail, n1, n2, n3, c->stream), "Poisson, forward planes");
+    LAUNCH(launch_fft_lines(c->fft, n1, n2, n3, 2, -1, c->stream, nullptr, 0, 0, 0, c->Kfft, n1, n2, n3, n3, 1),
+           "Poisson, z lines");
+    if (mgga)
+      LAUNCH(launch_mgga_potential(c->rho, c->tau, mgga_args(c), c->cfg.xc == TDDFT_XC_TB09, c->dV, c->volume,
+                                   c->gpart, c->cval, c->vx_mgga, c->stream),
+             "mgga exchange");
+    LAUNCH(launch_poisson_inverse(tail, n1, n2, n3, c->cfg.xc, c->vx_mgga, c->stream), "Poisson, inverse planes");
+    return TDDFT_OK;
   }
   if (!one) LAUNCH(launch_rho_reduce(c->rho_part, c->rho_nchunks, N, c->rho, c->stream), "rho_reduce");
   if (!c->potential_set) return TDDFT_OK;
@@ -357,10 +411,8 @@ const float* vpot<float>(tddft_ctx* c) {
   return c->Vf;
 }
 
-// tolerance of the norm watchdog (0: off)
-double norm_tol(const tddft_ctx* c) { return (c->cfg.flags & TDDFT_FLAG_NORM_WATCHDOG) ? 1e-3 : 0.0; }
-
-// observables of W with kappaJ / phAJ already set: obs, jnl, then finish
+// observables of W with kappaJ / phAJ already set: obs, jnl, then (on demand;
+// a step, bump, finishes with its density pass) the sums
 template <typename T>
 tddft_status enqueue_observe(tddft_ctx* c, int bump) {
   ObserveArgs<T> oa{};
@@ -389,42 +441,47 @@ tddft_status enqueue_observe(tddft_ctx* c, int bump) {
     pa.jnl = c->jnl;
     LAUNCH(launch_project<T>(pa, c->stream), "project moments");
   }
-  LAUNCH(launch_finish(c->obs, c->g.tiles_x * c->g.tiles_y * c->g.zslabs, c->jnl, nl ? 1 : 0, c->kw_d, c->kappaJ,
-                       c->cfg.n_orb, c->cfg.n_k, c->dV, c->volume, c->counter, bump, c->Jtab, c->scalars,
-                       c->nanflag, norm_tol(c), c->stream),
-         "finish");
+  if (bump) return TDDFT_OK;  // a step's density pass carries the finish
+  TailCell tail = tail_cell(c);
+  tail.tiles = c->g.tiles_x * c->g.tiles_y * c->g.zslabs;
+  LAUNCH(launch_finish(tail, 0, c->stream), "finish");
   return TDDFT_OK;
 }
 
-template <typename T>
-FusedArgs<T> fused_args(tddft_ctx* c);
+// the arguments of the start of a step over the table A (counter: the step
+// index on the device, nullptr: the table's first interval)
+ParamCell param_cell(const tddft_ctx* c, const double* A, const int* counter, bool with_coef = true) {
+  ParamCell q{};
+  q.A = A;
+  q.counter = counter;
+  q.kpt = c->kpt_d;
+  q.n_k = c->cfg.n_k;
+  q.S = c->nl.n_ent;
+  q.gauge = c->cfg.gauge;
+  q.ent_x = c->ent_x;
+  q.dt = c->cfg.dt;
+  q.kappa = c->kappa;
+  q.kappaJ = c->kappaJ;
+  q.efield = c->efield;
+  q.phA = c->phA;
+  q.phAJ = c->phAJ;
+  q.Alast = c->Alast;
+  std::memcpy(q.lap, c->lap, sizeof(q.lap));
+  std::memcpy(q.dh, c->dh, sizeof(q.dh));
+  q.cdiag = c->cdiag;
+  q.coef = with_coef ? c->coef : nullptr;
+  q.phk = c->nl.phk;
+  q.phkA = with_coef && c->fused ? c->phkA : nullptr;
+  return q;
+}
 
-// stencil coefficients of the step from the kappa just set (and, for the
-// fused step, the combined projector phases)
-tddft_status enqueue_coef(tddft_ctx* c) {
-  if (!c->fused) {
-    if (c->mixed)
-      LAUNCH(launch_coef_table<float>(c->kappa, c->cfg.n_k, c->lap, c->dh, c->cdiag, reinterpret_cast<float*>(c->coef),
-                                      c->stream),
-             "stage coefficients");
-    else
-      LAUNCH(launch_coef_table<double>(c->kappa, c->cfg.n_k, c->lap, c->dh, c->cdiag, c->coef, c->stream),
-             "stage coefficients");
-    return TDDFT_OK;
-  }
-  if (c->mixed)
-    LAUNCH(launch_fused_coef<float>(fused_args<float>(c), c->stream), "fused coefficients");
-  else
-    LAUNCH(launch_fused_coef<double>(fused_args<double>(c), c->stream), "fused coefficients");
-  return TDDFT_OK;
+hipError_t step_begin(const tddft_ctx* c, const ParamCell& q) {
+  return c->mixed ? launch_step_begin<float>(q, c->stream) : launch_step_begin<double>(q, c->stream);
 }
 
 tddft_status enqueue_params(tddft_ctx* c) {
-  LAUNCH(launch_step_params(c->Atab, c->counter, 1, c->kpt_d, c->cfg.n_k, c->ent_x, c->nl.n_ent,
-                            c->cfg.gauge, c->cfg.dt, c->kappa, c->kappaJ, c->efield, c->phA, c->phAJ,
-                            c->Alast, c->stream),
-         "step_params");
-  return enqueue_coef(c);
+  LAUNCH(step_begin(c, param_cell(c, c->Atab, c->counter)), "step begin");
+  return TDDFT_OK;
 }
 
 template <typename T>
@@ -456,16 +513,6 @@ FusedArgs<T> fused_args(tddft_ctx* c) {
   for (int mu = 0; mu < 3; ++mu)
     for (int m = 0; m < 4; ++m) f.dhc[mu][m] = (T)c->dh[mu][m];
   return f;
-}
-
-// after the fused orbital update: current, density and the new potential
-template <typename T>
-tddft_status enqueue_fused_tail(tddft_ctx* c) {
-  LAUNCH(launch_finish(c->obs, 1, c->jnl, c->nl.n_atoms > 0 ? 1 : 0, c->kw_d, c->kappaJ, c->cfg.n_orb,
-                       c->cfg.n_k, c->dV, c->volume, c->counter, 1, c->Jtab, c->scalars, c->nanflag,
-                       norm_tol(c), c->stream),
-         "finish");
-  return enqueue_density_potential<T>(c);
 }
 
 // one kernel per Horner stage, then observables, current, density, potential
@@ -532,7 +579,7 @@ tddft_status enqueue_streaming_update(tddft_ctx* c) {
   if (st != TDDFT_OK) return st;
   st = enqueue_observe<T>(c, 1);
   if (st != TDDFT_OK) return st;
-  return enqueue_density_potential<T>(c);
+  return enqueue_density_potential<T>(c, true);
 }
 
 template <typename T>
@@ -558,7 +605,7 @@ tddft_status enqueue_step(tddft_ctx* c) {
   }
   if (c->fused) {
     LAUNCH(launch_fused<T>(fused_args<T>(c), c->stream), "fused step");
-    return enqueue_fused_tail<T>(c);
+    return enqueue_density_potential<T>(c, true);  // current, density, potential
   }
   return enqueue_streaming_update<T>(c);
 }
@@ -576,10 +623,7 @@ tddft_status observe_now(tddft_ctx* c) {
   double Ab[6];
   for (int i = 0; i < 3; ++i) Ab[i] = Ab[3 + i] = c->A_last[i];
   HIP_TRY(hipMemcpyAsync(c->Aobs, Ab, sizeof(Ab), hipMemcpyHostToDevice, c->stream));
-  LAUNCH(launch_step_params(c->Aobs, c->counter, 0, c->kpt_d, c->cfg.n_k, c->ent_x, c->nl.n_ent,
-                            c->cfg.gauge, c->cfg.dt, c->kappa, c->kappaJ, c->efield, c->phA, c->phAJ,
-                            c->Alast, c->stream),
-         "step_params");
+  LAUNCH(step_begin(c, param_cell(c, c->Aobs, nullptr, false)), "step begin");
   tddft_status st = observe_dispatch(c);
   if (st != TDDFT_OK) return st;
   HIP_TRY(hipStreamSynchronize(c->stream));
@@ -711,9 +755,9 @@ tddft_status launch_one(tddft_ctx* c, int which) {
                                      c->tau_part, c->stream),
            "rho_tau_partial");
   } else {
-    LAUNCH(launch_rho_partial<T>(as2<T>(c->W), c->kw_d, c->cfg.n_orb, c->cfg.n_k, (int)c->N, c->rho_chunk,
-                                 c->rho_part, c->stream),
-           "rho_partial");
+    TailCell tail = tail_cell(c);
+    tail.rho_out = c->rho_part;
+    LAUNCH(launch_density<T>(tail, (int)c->N, 0, c->stream), "density");
   }
   return TDDFT_OK;
 }
@@ -913,17 +957,13 @@ tddft_status tune_stage(tddft_ctx* c) {
       double Ab[6];
       for (int i = 0; i < 3; ++i) Ab[i] = Ab[3 + i] = c->A_last[i];
       HIP_TRY(hipMemcpyAsync(c->Aobs, Ab, sizeof(Ab), hipMemcpyHostToDevice, c->stream));
-      LAUNCH(launch_step_params(c->Aobs, c->counter, 0, c->kpt_d, c->cfg.n_k, c->ent_x, c->nl.n_ent, c->cfg.gauge,
-                                c->cfg.dt, c->kappa, c->kappaJ, c->efield, c->phA, c->phAJ, c->Alast, c->stream),
-             "step_params");
-      tddft_status st = enqueue_coef(c);
-      if (st != TDDFT_OK) return st;
+      LAUNCH(step_begin(c, param_cell(c, c->Aobs, nullptr)), "step begin");
       const std::vector<StagePlan> cand = stage_candidates(c);
       cands = "[";
       best.ms = 1e300;
       for (size_t i = 0; i < cand.size(); ++i) {
         StagePlan p = cand[i];
-        st = c->mixed ? time_stage<float>(c, p, 3, &p.ms) : time_stage<double>(c, p, 3, &p.ms);
+        tddft_status st = c->mixed ? time_stage<float>(c, p, 3, &p.ms) : time_stage<double>(c, p, 3, &p.ms);
         if (st != TDDFT_OK) return st;
         cands += (i ? ", " : "") + plan_json(p);
         if (p.ms < best.ms) best = p;
@@ -1185,7 +1225,7 @@ tddft_status tddft_init(const tddft_config* cfg, const double* psi0, tddft_ctx**
       (st = dalloc_t(c, N, &c->vh)) || (st = dalloc_t(c, N, &c->exc)) || (st = dalloc_t(c, N, &c->rho)) ||
       (st = dalloc_t(c, N, &c->rho0)))
     return cleanup(st);
-  c->rho_chunk = is_mgga(c) ? rho_tau_chunk(c->g, (int)c->n_orb_tot) : 64;
+  c->rho_chunk = is_mgga(c) ? rho_tau_chunk(c->g, (int)c->n_orb_tot) : density_chunk((int)N, (int)c->n_orb_tot);
   c->rho_nchunks = (int)((c->n_orb_tot + c->rho_chunk - 1) / c->rho_chunk);
   if ((st = dalloc_t(c, (size_t)c->rho_nchunks * N, &c->rho_part))) return cleanup(st);
   if (is_mgga(c) && ((st = dalloc_t(c, (size_t)c->rho_nchunks * N, &c->tau_part)) || (st = dalloc_t(c, N, &c->tau)) ||
@@ -1220,8 +1260,7 @@ tddft_status tddft_init(const tddft_config* cfg, const double* psi0, tddft_ctx**
     // kappa, kappaJ and the field at A = 0 until the first step sets them
     const double Az[6] = {0, 0, 0, 0, 0, 0};
     if (hipMemcpyAsync(c->Aobs, Az, sizeof(Az), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        launch_step_params(c->Aobs, c->counter, 0, c->kpt_d, cfg->n_k, c->ent_x, 0, cfg->gauge, cfg->dt, c->kappa,
-                           c->kappaJ, c->efield, c->phA, c->phAJ, c->Alast, c->stream) != hipSuccess)
+        step_begin(c, param_cell(c, c->Aobs, nullptr, false)) != hipSuccess)
       return cleanup(fail(c, TDDFT_EDEVICE, "initial field parameters failed"));
   }
   if ((st = potential_dispatch(c)) != TDDFT_OK) return cleanup(st);
@@ -1627,13 +1666,8 @@ tddft_status tddft_time_kernel(tddft_ctx* c, int32_t which, int32_t reps, double
   double Ab[6];
   for (int i = 0; i < 3; ++i) Ab[i] = Ab[3 + i] = c->A_last[i];
   HIP_TRY(hipMemcpyAsync(c->Aobs, Ab, sizeof(Ab), hipMemcpyHostToDevice, c->stream));
-  LAUNCH(launch_step_params(c->Aobs, c->counter, 0, c->kpt_d, c->cfg.n_k, c->ent_x, c->nl.n_ent,
-                            c->cfg.gauge, c->cfg.dt, c->kappa, c->kappaJ, c->efield, c->phA, c->phAJ,
-                            c->Alast, c->stream),
-         "step_params");
-  tddft_status st = enqueue_coef(c);
-  if (st != TDDFT_OK) return st;
-  st = c->mixed ? launch_one<float>(c, which) : launch_one<double>(c, which);  // warm-up
+  LAUNCH(step_begin(c, param_cell(c, c->Aobs, nullptr)), "step begin");
+  tddft_status st = c->mixed ? launch_one<float>(c, which) : launch_one<double>(c, which);  // warm-up
   if (st != TDDFT_OK) return st;
   HIP_TRY(hipEventRecord(c->ev0, c->stream));
   for (int r = 0; r < reps; ++r) {
@@ -1673,13 +1707,8 @@ tddft_status tddft_ground_state(tddft_ctx* c, int32_t n_iter, double tau, double
   double Ab[6] = {0, 0, 0, 0, 0, 0};
   HIP_TRY(hipMemcpyAsync(c->Aobs, Ab, sizeof(Ab), hipMemcpyHostToDevice, c->stream));
   for (int it = 0; it < n_iter; ++it) {
-    LAUNCH(launch_step_params(c->Aobs, c->counter, 0, c->kpt_d, c->cfg.n_k, c->ent_x, c->nl.n_ent,
-                              c->cfg.gauge, c->cfg.dt, c->kappa, c->kappaJ, c->efield, c->phA, c->phAJ,
-                              c->Alast, c->stream),
-           "step_params");
-    tddft_status st = enqueue_coef(c);
-    if (st != TDDFT_OK) return st;
-    st = c->mixed ? ground_state_iteration<float>(c, tau) : ground_state_iteration<double>(c, tau);
+    LAUNCH(step_begin(c, param_cell(c, c->Aobs, nullptr)), "step begin");
+    tddft_status st = c->mixed ? ground_state_iteration<float>(c, tau) : ground_state_iteration<double>(c, tau);
     if (st != TDDFT_OK) return st;
     if (energies) {
       st = tddft_energy(c, &energies[it]);
@@ -1792,7 +1821,6 @@ struct BatchGroup {
   // the start of the step (field, kappa, phases, coefficients) for all cells
   ParamCell* d_par = nullptr;
   int max_S = 0, max_nk = 0;
-  long max_phases = 0;
 };
 
 }  // namespace
@@ -1905,7 +1933,7 @@ tddft_status batch_plan(tddft_batch* b) {
       const tddft_ctx* c = b->cells[i];
       g.max_chunks = std::max(g.max_chunks, c->rho_nchunks);
       if (is_mgga(c) || c->cfg.hartree != c0->cfg.hartree || c->cfg.xc != c0->cfg.xc ||
-          c->rho_chunk != c0->rho_chunk || c->N != c0->N || c->M[0] != c0->M[0] || c->M[1] != c0->M[1] ||
+          c->N != c0->N || c->M[0] != c0->M[0] || c->M[1] != c0->M[1] ||
           c->M[2] != c0->M[2])
         g.tail_ok = false;
     }
@@ -1918,7 +1946,6 @@ tddft_status batch_plan(tddft_batch* b) {
       const tddft_ctx* c = b->cells[i];
       g.max_S = std::max(g.max_S, c->nl.n_ent);
       g.max_nk = std::max(g.max_nk, c->cfg.n_k);
-      g.max_phases = std::max(g.max_phases, (long)c->cfg.n_k * c->nl.n_ent);
     }
     BHIP(hipMalloc(&p, g.cells.size() * sizeof(ParamCell)));
     b->allocs.push_back(p);
@@ -1956,66 +1983,13 @@ tddft_status batch_plan(tddft_batch* b) {
 // tables move when a longer run needs more room)
 tddft_status batch_tail_upload(tddft_batch* b) {
   for (auto& g : b->groups) {
-    std::vector<ParamCell> par(g.cells.size());
-    for (size_t j = 0; j < g.cells.size(); ++j) {
-      tddft_ctx* c = b->cells[g.cells[j]];
-      ParamCell& q = par[j];
-      q.A = c->Atab;
-      q.counter = c->counter;
-      q.kpt = c->kpt_d;
-      q.n_k = c->cfg.n_k;
-      q.S = c->nl.n_ent;
-      q.gauge = c->cfg.gauge;
-      q.ent_x = c->ent_x;
-      q.dt = c->cfg.dt;
-      q.kappa = c->kappa;
-      q.kappaJ = c->kappaJ;
-      q.efield = c->efield;
-      q.phA = c->phA;
-      q.phAJ = c->phAJ;
-      q.Alast = c->Alast;
-      std::memcpy(q.lap, c->lap, sizeof(q.lap));
-      std::memcpy(q.dh, c->dh, sizeof(q.dh));
-      q.cdiag = c->cdiag;
-      q.coef = c->coef;
-      q.phk = c->nl.phk;
-      q.phkA = c->phkA;
-    }
+    std::vector<ParamCell> par;
+    for (int i : g.cells) par.push_back(param_cell(b->cells[i], b->cells[i]->Atab, b->cells[i]->counter));
     BHIP(hipMemcpyAsync(g.d_par, par.data(), par.size() * sizeof(ParamCell), hipMemcpyHostToDevice, b->stream));
     BHIP(hipStreamSynchronize(b->stream));
     if (!g.tail_ok) continue;
-    std::vector<TailCell> tab(g.cells.size());
-    for (size_t j = 0; j < g.cells.size(); ++j) {
-      tddft_ctx* c = b->cells[g.cells[j]];
-      TailCell& t = tab[j];
-      t.w = c->W;
-      t.kw = c->kw_d;
-      t.n_orb = c->cfg.n_orb;
-      t.n_k = c->cfg.n_k;
-      t.nchunks = c->rho_nchunks;
-      t.rho_out = c->rho_nchunks == 1 ? c->rho : c->rho_part;
-      t.rho_part = c->rho_part;
-      t.rho = c->rho;
-      t.fft = c->fft;
-      t.Kfft = c->Kfft;
-      t.vh_scale = c->vh_scale;
-      t.Vloc = c->Vloc;
-      t.Vd = c->Vd;
-      t.Vf = c->Vf;
-      t.vh = c->vh;
-      t.exc = c->exc;
-      t.obs = c->obs;
-      t.jnl = c->jnl;
-      t.use_nl = c->nl.n_atoms > 0 ? 1 : 0;
-      t.kappaJ = c->kappaJ;
-      t.dV = c->dV;
-      t.volume = c->volume;
-      t.counter = c->counter;
-      t.Jtab = c->Jtab;
-      t.scalars = c->scalars;
-      t.nanflag = c->nanflag;
-      t.norm_tol = norm_tol(c);
-    }
+    std::vector<TailCell> tab;
+    for (int i : g.cells) tab.push_back(tail_cell(b->cells[i]));
     BHIP(hipMemcpyAsync(g.d_tail, tab.data(), tab.size() * sizeof(TailCell), hipMemcpyHostToDevice, b->stream));
     BHIP(hipStreamSynchronize(b->stream));
   }
@@ -2023,17 +1997,22 @@ tddft_status batch_tail_upload(tddft_batch* b) {
 }
 
 // the end of the step for every cell of a group, one launch per kernel: the
-// same kernels and order as enqueue_fused_tail applied to each cell
+// same kernels and order as enqueue_density_potential applied to each cell
 template <typename T>
 tddft_status enqueue_group_tail(tddft_batch* b, const BatchGroup& g, hipStream_t s) {
   const tddft_ctx* c0 = b->cells[g.cells[0]];
   const int nc = (int)g.cells.size();
   const int N = (int)c0->N;
-  BHIP(launch_finish_group(g.d_tail, nc, 1, s));
-  BHIP(launch_rho_partial_group<T>(g.d_tail, nc, N, c0->rho_chunk, g.max_chunks, s));
+  BHIP(launch_density_group<T>(g.d_tail, nc, N, g.max_chunks, s));
+  const int n1 = c0->g.n1, n2 = c0->g.n2, n3 = c0->g.n3;
+  if (poisson_planes(c0->g.periodic, c0->cfg.hartree, n1, n2)) {
+    BHIP(launch_poisson_forward_group(g.d_tail, nc, n1, n2, n3, s));
+    BHIP(launch_fft_lines_group(g.d_tail, nc, n1, n2, n3, 2, -1, 0, n1, n2, n3, 1, n1, n2, n3, n3, 1, s));
+    BHIP(launch_poisson_inverse_group(g.d_tail, nc, n1, n2, n3, c0->cfg.xc, s));
+    return TDDFT_OK;
+  }
   if (g.max_chunks > 1) BHIP(launch_rho_reduce_group(g.d_tail, nc, N, s));
   const int M1 = c0->M[0], M2 = c0->M[1], M3 = c0->M[2];
-  const int n1 = c0->g.n1, n2 = c0->g.n2, n3 = c0->g.n3;
   if (c0->cfg.hartree) {
     BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 0, -1, 1, n1, n2, n3, 0, n2, n3, n1, M1, 0, s));
     BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 1, -1, 0, n1, n2, n3, 0, M1, n3, n2, M2, 0, s));
@@ -2052,8 +2031,7 @@ tddft_status batch_step(tddft_batch* b, bool timing) {
   // cell for the per-stage lanes (the same kernels and arithmetic either way)
   for (auto& g : b->groups) {
     const int nc = (int)g.cells.size();
-    BHIP(launch_step_params_group(g.d_par, nc, g.max_S, b->stream));
-    BHIP(launch_fused_coef_group<T>(g.d_par, nc, g.max_nk, g.max_phases, b->stream));
+    BHIP(launch_step_begin_group<T>(g.d_par, nc, g.max_S, g.max_nk, g.d_queue, b->stream));
   }
   for (auto& lane : b->lanes)
     for (int i : lane) {
@@ -2067,7 +2045,6 @@ tddft_status batch_step(tddft_batch* b, bool timing) {
   for (auto& g : b->groups) {
     hipStream_t s = b->side[si];
     BHIP(hipStreamWaitEvent(s, b->fork, 0));
-    BHIP(launch_set_int(g.d_queue, 0, s));
     if (timing) BHIP(hipEventRecord(g.e0, s));
     BHIP(launch_fused_persistent<T>(g.n, g.periodic, static_cast<const FusedArgs<T>*>(g.d_args), g.d_items,
                                     g.n_items, g.d_queue, g.wgs, g.lds, s));
@@ -2079,7 +2056,7 @@ tddft_status batch_step(tddft_batch* b, bool timing) {
       for (int i : g.cells) {
         tddft_ctx* c = b->cells[i];
         c->stream = s;
-        tddft_status st = enqueue_fused_tail<T>(c);
+        tddft_status st = enqueue_density_potential<T>(c, true);
         c->stream = b->stream;
         if (st != TDDFT_OK) return bcell(b, st, i);
       }

@@ -189,11 +189,6 @@ template <typename T>
 hipError_t launch_project(const ProjArgs<T>& a, hipStream_t s);
 template <typename T>
 hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s);
-template <typename T>
-hipError_t launch_fused_coef(const FusedArgs<T>& a, hipStream_t s);
-template <typename T>
-hipError_t launch_coef_table(const double* kappa, int n_k, const double lap[3][5], const double dh[3][4], double cdiag, T* coef,
-                             hipStream_t s);
 bool fused_supported(const Geometry& g, int n_atoms, size_t elem);
 size_t fused_lds_bytes(const Geometry& g, int n_atoms, size_t elem);
 int fused_rows(int n, size_t elem);  // z points of a thread's tile
@@ -201,14 +196,6 @@ template <typename T>
 hipError_t launch_fused_persistent(int n, bool periodic, const FusedArgs<T>* cells, const int2* items,
                                    int n_items, int* queue, int wgs, size_t lds, hipStream_t s);
 
-hipError_t launch_step_params(const double* A, const int* counter, int use_counter,
-                              const double* kpt, int n_k, const double* ent_x, int S, int gauge,
-                              double dt, double* kappa, double* kappaJ, double* efield, double2* phA,
-                              double2* phAJ, double* Alast, hipStream_t s);
-
-template <typename T>
-hipError_t launch_rho_partial(const typename Vec2<T>::type* w, const double* kw, int n_orb, int n_k,
-                              int N, int chunk, double* part, hipStream_t s);
 hipError_t launch_rho_reduce(const double* part, int nchunks, int N, double* rho, hipStream_t s);
 
 // rho (with n1..n3): the first pass reads the density into the M-box itself;
@@ -223,13 +210,14 @@ hipError_t launch_fft_axis(double2* data, int M1, int M2, int M3, int axis, int 
 hipError_t launch_fft_lines(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s,
                             const double* rho, int n1, int n2, int n3, const double* K, int l1, int l2, int n_in,
                             int n_out, int fused);
-// Per-cell arguments of the end of a step (current, density, Poisson, xc)
-// when a group of same-shape cells runs it with one launch per kernel: the
-// cell is a grid dimension and each cell's pointers come from this table.
+// Per-cell arguments of the end of a step (current, density, Poisson, xc).
+// When a group of same-shape cells runs it with one launch per kernel, the
+// cell is a grid dimension and the arguments come from a table of these.
 struct TailCell {
   const void* w;          // orbitals [n_orb n_k][N], stage precision
   const double* kw;       // [n_k]
-  int n_orb, n_k, nchunks;
+  int n_orb, n_k;
+  int nchunks, chunk;     // chunks of the density pass, orbitals per chunk
   double* rho_out;        // the density pass's output: rho with one chunk, else rho_part
   double* rho_part;       // [nchunks][N]
   double* rho;            // [N]
@@ -242,6 +230,7 @@ struct TailCell {
   double* vh;
   double* exc;
   const double* obs;      // [n_orb n_k][tiles][8]
+  int tiles;
   const double* jnl;      // [n_orb n_k][4] or nullptr
   int use_nl;
   const double* kappaJ;
@@ -253,12 +242,12 @@ struct TailCell {
   double norm_tol;
 };
 
-// Per-cell arguments of the start of a fused step (field, kappa and phases,
-// the stencil coefficients, the per-k sphere phases) for one launch per
-// kernel over a group of cells.
+// Per-cell arguments of the start of a step (field, kappa and phases, the
+// stencil coefficients, the per-k sphere phases): by value for one cell, from a
+// table for a group of cells.
 struct ParamCell {
   const double* A;        // A table [..][3]
-  const int* counter;
+  const int* counter;     // step index (nullptr: 0)
   const double* kpt;      // [n_k][3]
   int n_k, S, gauge;
   const double* ent_x;    // [S][3]
@@ -272,9 +261,9 @@ struct ParamCell {
   double lap[3][5];
   double dh[3][4];
   double cdiag;
-  void* coef;             // [n_k][kCoef] stage precision
+  void* coef;             // [n_k][kCoef] stage precision, or nullptr
   const double2* phk;     // [n_k][S]
-  double2* phkA;          // [n_k][S]
+  double2* phkA;          // [n_k][S], or nullptr (per-stage kernels)
 };
 
 // A batch's per-cell A and J tables moved with one copy each way: the cells'
@@ -291,13 +280,28 @@ hipError_t launch_batch_tables_in(const IOCell* io, int ncells, const double* st
 // the cells' J tables (len doubles) and NaN flags to staged [ncells][len + 1]
 hipError_t launch_batch_tables_out(const IOCell* io, int ncells, double* staged, int len, hipStream_t s);
 
-hipError_t launch_step_params_group(const ParamCell* tab, int ncells, int max_S, hipStream_t s);
+// the start of a step: field, kappa, phases, stencil coefficients
 template <typename T>
-hipError_t launch_fused_coef_group(const ParamCell* tab, int ncells, int max_nk, long max_phases, hipStream_t s);
+hipError_t launch_step_begin(const ParamCell& c, hipStream_t s);
+template <typename T>
+hipError_t launch_step_begin_group(const ParamCell* tab, int ncells, int max_S, int max_nk, int* queue,
+                                   hipStream_t s);  // and *queue = 0
 
+// the density pass, with the current (finish) on a workgroup of its own
+int density_chunk(int N, int n_tot);
 template <typename T>
-hipError_t launch_rho_partial_group(const TailCell* tab, int ncells, int N, int chunk, int max_chunks,
-                                    hipStream_t s);
+hipError_t launch_density(const TailCell& t, int N, int with_finish, hipStream_t s);
+template <typename T>
+hipError_t launch_density_group(const TailCell* tab, int ncells, int N, int max_chunks, hipStream_t s);
+// Poisson solve by planes: periodic boxes of at most kPlaneMax points per plane
+constexpr int kPlaneMax = 2048;
+bool poisson_planes(int periodic, int hartree, int n1, int n2);
+hipError_t launch_poisson_forward(const TailCell& t, int n1, int n2, int n3, hipStream_t s);
+hipError_t launch_poisson_inverse(const TailCell& t, int n1, int n2, int n3, int xc, const double* vx_mgga,
+                                  hipStream_t s);
+hipError_t launch_poisson_forward_group(const TailCell* tab, int ncells, int n1, int n2, int n3, hipStream_t s);
+hipError_t launch_poisson_inverse_group(const TailCell* tab, int ncells, int n1, int n2, int n3, int xc,
+                                        hipStream_t s);
 hipError_t launch_rho_reduce_group(const TailCell* tab, int ncells, int N, hipStream_t s);
 // as launch_fft_lines for every cell of tab (same box and lines); use_rho /
 // use_K: the pass reads the cell's rho / multiplies by its K
@@ -306,7 +310,6 @@ hipError_t launch_fft_lines_group(const TailCell* tab, int ncells, int M1, int M
                                   int n_out, int fused, hipStream_t s);
 hipError_t launch_xc_group(const TailCell* tab, int ncells, int n1, int n2, int n3, int M1, int M2, int hartree,
                            int xc, hipStream_t s);
-hipError_t launch_finish_group(const TailCell* tab, int ncells, int tiles, hipStream_t s);
 
 hipError_t launch_xc_assemble(const double2* data, int n1, int n2, int n3, int M1, int M2, int M3,
                               double vh_scale, const double* rho, const double* Vloc, int hartree,
@@ -320,10 +323,7 @@ int rho_tau_chunk(const Geometry& g, int n_tot);
 hipError_t launch_mgga_potential(const double* rho, const double* tau, const MggaArgs& a, int tb09, double dV,
                                  double volume, double* gpart, double* cval, double* vx, hipStream_t s);
 
-hipError_t launch_finish(const double* obs, int tiles, const double* jnl, int use_nl,
-                         const double* kw, const double* kappaJ, int n_orb, int n_k, double dV,
-                         double volume, int* counter, int bump, double* Jtab, double* scalars,
-                         int* nanflag, double norm_tol, hipStream_t s);
+hipError_t launch_finish(const TailCell& c, int bump, hipStream_t s);
 
 hipError_t launch_grid_sums(const double* rho, const double* rho0, const double* vh,
                             const double* exc, Geometry g, double* out, hipStream_t s);

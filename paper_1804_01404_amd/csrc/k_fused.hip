@@ -18,8 +18,6 @@
 //     w_new that the current needs (norm and momentum, FP64 accumulation) and
 //     the moment projections for the nonlocal current at t_{n+1}.
 // HBM traffic per orbital point and step: read w once, write w_new once.
-#include <cstring>
-
 #include "internal.h"
 
 namespace td {
@@ -153,12 +151,6 @@ __device__ __forceinline__ double wave_sum16(const double (&v)[16], int lane) {
   const double keep = h4 ? c[1] : c[0], send = h4 ? c[0] : c[1];
   return sum_quad(keep + dpp<kXor7>(send));
 }
-
-struct FusedCoefIn {
-  double lap[3][5];
-  double dh[3][4];
-  double cdiag;
-};
 
 // E . r of the length gauge at the tile's first point and its steps along x and z
 template <typename T>
@@ -861,104 +853,6 @@ __global__ __launch_bounds__((FusedShape<T, N>::kThreads), (FusedShape<T, N>::kW
     __syncthreads();
   }
 }
-
-// per k-point row of coefficients of the step in the stage precision (from
-// kappa at the step midpoint): -1/2 c_m / h_mu^2 and kappa_mu d_m / h_mu per
-// axis, and the diagonal -1/2 sum_mu c_0 / h_mu^2 + |kappa|^2 / 2
-template <typename T>
-__device__ __forceinline__ void fused_coef_k(const double* __restrict__ kappa, const double (&lap)[3][5],
-                                             const double (&dh)[3][4], double cdiag, T* __restrict__ coef, int k) {
-  const double kap[3] = {kappa[3 * k], kappa[3 * k + 1], kappa[3 * k + 2]};
-  T* c = coef + (size_t)k * kCoef;
-  for (int mu = 0; mu < 3; ++mu)
-    for (int m = 0; m < 4; ++m) {
-      c[8 * mu + m] = (T)lap[mu][m + 1];
-      c[8 * mu + kCoefB + m] = (T)(kap[mu] * dh[mu][m]);
-    }
-  c[kCoefDiag] = (T)(cdiag + 0.5 * (kap[0] * kap[0] + kap[1] * kap[1] + kap[2] * kap[2]));
-}
-
-template <typename T>
-__global__ void k_fused_coef(const double* __restrict__ kappa, int n_k, FusedCoefIn in, T* __restrict__ coef) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_k) return;
-  fused_coef_k<T>(kappa, in.lap, in.dh, in.cdiag, coef, k);
-}
-
-// exp(i kappa . x_e) = exp(i k . x_e) exp(i A . x_e / c) for every k-point and
-// sphere entry, once per step (each workgroup then reads one factor per entry)
-__device__ __forceinline__ void fused_phase_t(const double2* __restrict__ phk, const double2* __restrict__ phA, int S,
-                                              double2* __restrict__ out, size_t t) {
-  const int e = (int)(t % S);
-  const double2 p1 = phk[t], p2 = phA[e];
-  out[t] = make_double2(p1.x * p2.x - p1.y * p2.y, p1.x * p2.y + p1.y * p2.x);
-}
-
-__global__ void k_fused_phase(const double2* __restrict__ phk, const double2* __restrict__ phA, int S, int n_k,
-                              double2* __restrict__ out) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (size_t)n_k * S) return;
-  fused_phase_t(phk, phA, S, out, t);
-}
-
-// the same two for the cells of a group (cell blockIdx.y)
-template <typename T>
-__global__ void k_fused_coef_group(const ParamCell* __restrict__ tab) {
-  const ParamCell& c = tab[blockIdx.y];
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= c.n_k) return;
-  fused_coef_k<T>(c.kappa, c.lap, c.dh, c.cdiag, static_cast<T*>(c.coef), k);
-}
-
-__global__ void k_fused_phase_group(const ParamCell* __restrict__ tab) {
-  const ParamCell& c = tab[blockIdx.y];
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c.S == 0 || t >= (size_t)c.n_k * c.S) return;
-  fused_phase_t(c.phk, c.phA, c.S, c.phkA, t);
-}
-
-template <typename T>
-hipError_t launch_fused_coef_group(const ParamCell* tab, int ncells, int max_nk, long max_phases, hipStream_t s) {
-  hipLaunchKernelGGL((k_fused_coef_group<T>), dim3((unsigned)((max_nk + 63) / 64), ncells), dim3(64), 0, s, tab);
-  if (max_phases > 0)
-    hipLaunchKernelGGL(k_fused_phase_group, dim3((unsigned)((max_phases + 255) / 256), ncells), dim3(256), 0, s,
-                       tab);
-  return hipGetLastError();
-}
-template hipError_t launch_fused_coef_group<double>(const ParamCell*, int, int, long, hipStream_t);
-template hipError_t launch_fused_coef_group<float>(const ParamCell*, int, int, long, hipStream_t);
-
-template <typename T>
-hipError_t launch_fused_coef(const FusedArgs<T>& a, hipStream_t s) {
-  FusedCoefIn in;
-  std::memcpy(in.lap, a.lap, sizeof(in.lap));
-  std::memcpy(in.dh, a.dh, sizeof(in.dh));
-  in.cdiag = a.cdiag;
-  const int nk = a.g.n_k;
-  hipLaunchKernelGGL((k_fused_coef<T>), dim3((unsigned)((nk + 63) / 64)), dim3(64), 0, s, a.kappa, nk, in, a.coef);
-  const size_t tot = (size_t)nk * a.nl.n_ent;
-  if (tot > 0)
-    hipLaunchKernelGGL(k_fused_phase, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, a.nl.phk, a.phA,
-                       a.nl.n_ent, nk, a.phkA);
-  return hipGetLastError();
-}
-
-template hipError_t launch_fused_coef<double>(const FusedArgs<double>&, hipStream_t);
-template hipError_t launch_fused_coef<float>(const FusedArgs<float>&, hipStream_t);
-
-// the per-k coefficient table alone (the per-stage kernels read it too)
-template <typename T>
-hipError_t launch_coef_table(const double* kappa, int n_k, const double lap[3][5], const double dh[3][4], double cdiag, T* coef,
-                             hipStream_t s) {
-  FusedCoefIn in;
-  std::memcpy(in.lap, lap, sizeof(in.lap));
-  std::memcpy(in.dh, dh, sizeof(in.dh));
-  in.cdiag = cdiag;
-  hipLaunchKernelGGL((k_fused_coef<T>), dim3((unsigned)((n_k + 63) / 64)), dim3(64), 0, s, kappa, n_k, in, coef);
-  return hipGetLastError();
-}
-template hipError_t launch_coef_table<double>(const double*, int, const double[3][5], const double[3][4], double, double*, hipStream_t);
-template hipError_t launch_coef_table<float>(const double*, int, const double[3][5], const double[3][4], double, float*, hipStream_t);
 
 size_t fused_lds_bytes(const Geometry& g, int n_atoms, size_t elem) {
   const size_t N = (size_t)g.n1 * g.n2 * g.n3;

@@ -7,84 +7,118 @@
 
 namespace td {
 
-// ---------------------------------------------------------------- parameters
+// ---------------------------------------------------------------- step begin
 // A: table [..][3]; the step index n is *counter (or 0). Velocity gauge:
 // kappa = k + (A_n + A_{n+1}) / (2c), kappaJ = k + A_{n+1} / c, and the
 // matching sphere phases exp(i A.x / c). Length gauge: kappa = kappaJ = k,
-// unit phases, E_n = -(A_{n+1} - A_n) / (c dt).
-__device__ __forceinline__ void step_params_block(const double* A, const int* counter, int use_counter,
-                                                  const double* kpt, int n_k, const double* ent_x, int S,
-                                                  int gauge, double dt, double* kappa, double* kappaJ,
-                                                  double* efield, double2* phA, double2* phAJ, double* Alast,
-                                                  int bx) {
-  const int n = use_counter ? *counter : 0;
-  const double* A0 = A + 3 * (size_t)n;
+// unit phases, E_n = -(A_{n+1} - A_n) / (c dt). With coef, also the k-point
+// rows of stencil coefficients in the stage precision (-1/2 c_m / h_mu^2 and
+// kappa_mu d_m / h_mu per axis, the diagonal -1/2 sum_mu c_0 / h_mu^2 +
+// |kappa|^2 / 2); with phkA, exp(i kappa . x_e) for every k-point and entry.
+// One launch: as three (field, coefficients, phases) of about 4.5 us each they
+// were a tenth of a small cell's step. A workgroup takes 256 entries and
+// kBeginK k-points, and forms its entries' A phases anew (a sincos or two).
+constexpr int kBeginK = 8;
+
+template <typename T>
+__device__ __forceinline__ void step_begin_block(const ParamCell& c, int bx, int by) {
+  const double* A0 = c.A + 3 * (size_t)(c.counter ? *c.counter : 0);
   const double* A1 = A0 + 3;
+  const bool vel = (c.gauge == 0);
   double ab[3], a1[3];
   for (int i = 0; i < 3; ++i) {
     ab[i] = 0.5 * (A0[i] + A1[i]);
     a1[i] = A1[i];
   }
-  const bool vel = (gauge == 0);
-  const int t = bx * blockDim.x + threadIdx.x;
+  const int t = threadIdx.x;
+  const int k0 = by * kBeginK, k1 = min(c.n_k, k0 + kBeginK);
   if (bx == 0) {
-    for (int k = threadIdx.x; k < n_k; k += blockDim.x) {
-      for (int i = 0; i < 3; ++i) {
-        kappa[3 * k + i] = kpt[3 * k + i] + (vel ? ab[i] / kC : 0.0);
-        kappaJ[3 * k + i] = kpt[3 * k + i] + (vel ? a1[i] / kC : 0.0);
+    if (by == 0 && t < 3) {
+      c.efield[t] = vel ? 0.0 : -(A1[t] - A0[t]) / (kC * c.dt);
+      c.Alast[t] = A1[t];
+    }
+    // 32 threads per k-point: 25 coefficients, kappa, kappaJ
+    const int k = k0 + t / 32, j = t % 32;
+    if (k < k1) {
+      double kap[3];
+      for (int i = 0; i < 3; ++i) kap[i] = c.kpt[3 * k + i] + (vel ? ab[i] / kC : 0.0);
+      if (j >= 25) {
+        const int i = (j - 25) % 3;
+        if (j < 28)
+          c.kappa[3 * k + i] = kap[i];
+        else if (j < 31)
+          c.kappaJ[3 * k + i] = c.kpt[3 * k + i] + (vel ? a1[i] / kC : 0.0);
+      } else if (c.coef) {
+        const int mu = j / 8, m = j % 4;
+        double v;
+        if (j == kCoefDiag)
+          v = c.cdiag + 0.5 * (kap[0] * kap[0] + kap[1] * kap[1] + kap[2] * kap[2]);
+        else
+          v = j % 8 < kCoefB ? c.lap[mu][m + 1] : kap[mu] * c.dh[mu][m];
+        static_cast<T*>(c.coef)[(size_t)k * kCoef + j] = (T)v;
       }
     }
-    if (threadIdx.x < 3) {
-      efield[threadIdx.x] = vel ? 0.0 : -(A1[threadIdx.x] - A0[threadIdx.x]) / (kC * dt);
-      Alast[threadIdx.x] = a1[threadIdx.x];
+  }
+  const int e = bx * blockDim.x + t;
+  if (e >= c.S) return;
+  double2 ph = make_double2(1.0, 0.0), phj = ph;
+  if (vel) {
+    const double* x = c.ent_x + 3 * (size_t)e;
+    double sn, cs;
+    sincos((ab[0] * x[0] + ab[1] * x[1] + ab[2] * x[2]) / kC, &sn, &cs);
+    ph = make_double2(cs, sn);
+    if (by == 0) {
+      sincos((a1[0] * x[0] + a1[1] * x[1] + a1[2] * x[2]) / kC, &sn, &cs);
+      phj = make_double2(cs, sn);
     }
   }
-  if (t < S) {
-    const double* x = ent_x + 3 * (size_t)t;
-    if (vel) {
-      double s, c;
-      sincos((ab[0] * x[0] + ab[1] * x[1] + ab[2] * x[2]) / kC, &s, &c);
-      phA[t] = make_double2(c, s);
-      sincos((a1[0] * x[0] + a1[1] * x[1] + a1[2] * x[2]) / kC, &s, &c);
-      phAJ[t] = make_double2(c, s);
-    } else {
-      phA[t] = make_double2(1.0, 0.0);
-      phAJ[t] = make_double2(1.0, 0.0);
+  if (by == 0) {
+    c.phA[e] = ph;
+    c.phAJ[e] = phj;
+  }
+  if (c.phkA) {
+    for (int k = k0; k < k1; ++k) {
+      const double2 p1 = c.phk[(size_t)k * c.S + e];
+      c.phkA[(size_t)k * c.S + e] = make_double2(p1.x * ph.x - p1.y * ph.y, p1.x * ph.y + p1.y * ph.x);
     }
   }
 }
 
-__global__ void k_step_params(const double* A, const int* counter, int use_counter,
-                              const double* kpt, int n_k, const double* ent_x, int S, int gauge,
-                              double dt, double* kappa, double* kappaJ, double* efield,
-                              double2* phA, double2* phAJ, double* Alast) {
-  step_params_block(A, counter, use_counter, kpt, n_k, ent_x, S, gauge, dt, kappa, kappaJ, efield, phA, phAJ, Alast,
-                    (int)blockIdx.x);
+template <typename T>
+__global__ __launch_bounds__(256) void k_step_begin(ParamCell c) {
+  step_begin_block<T>(c, (int)blockIdx.x, (int)blockIdx.y);
 }
 
-// the same for the cells of a group (cell blockIdx.y), each at its own step
-__global__ void k_step_params_group(const ParamCell* __restrict__ tab) {
-  const ParamCell& c = tab[blockIdx.y];
-  if ((int)blockIdx.x > 0 && (int)blockIdx.x * (int)blockDim.x >= c.S) return;
-  step_params_block(c.A, c.counter, 1, c.kpt, c.n_k, c.ent_x, c.S, c.gauge, c.dt, c.kappa, c.kappaJ, c.efield, c.phA,
-                    c.phAJ, c.Alast, (int)blockIdx.x);
+// the same for the cells of a group (cell blockIdx.z), each at its own step;
+// the group's work queue starts over
+template <typename T>
+__global__ __launch_bounds__(256) void k_step_begin_group(const ParamCell* __restrict__ tab, int* queue) {
+  if (blockIdx.x + blockIdx.y + blockIdx.z == 0 && threadIdx.x == 0) *queue = 0;
+  const ParamCell& c = tab[blockIdx.z];
+  if ((int)blockIdx.x > 0 && (int)blockIdx.x * 256 >= c.S) return;
+  if ((int)blockIdx.y * kBeginK >= c.n_k) return;
+  step_begin_block<T>(c, (int)blockIdx.x, (int)blockIdx.y);
 }
 
-hipError_t launch_step_params_group(const ParamCell* tab, int ncells, int max_S, hipStream_t s) {
-  const int blocks = max_S > 0 ? (max_S + 255) / 256 : 1;
-  hipLaunchKernelGGL(k_step_params_group, dim3(blocks, ncells), dim3(256), 0, s, tab);
+template <typename T>
+hipError_t launch_step_begin(const ParamCell& c, hipStream_t s) {
+  const dim3 grid((unsigned)max(1, (c.S + 255) / 256), (unsigned)((c.n_k + kBeginK - 1) / kBeginK));
+  hipLaunchKernelGGL((k_step_begin<T>), grid, dim3(256), 0, s, c);
   return hipGetLastError();
 }
+template hipError_t launch_step_begin<double>(const ParamCell&, hipStream_t);
+template hipError_t launch_step_begin<float>(const ParamCell&, hipStream_t);
 
-hipError_t launch_step_params(const double* A, const int* counter, int use_counter,
-                              const double* kpt, int n_k, const double* ent_x, int S, int gauge,
-                              double dt, double* kappa, double* kappaJ, double* efield, double2* phA,
-                              double2* phAJ, double* Alast, hipStream_t s) {
-  const int blocks = S > 0 ? (S + 255) / 256 : 1;
-  hipLaunchKernelGGL(k_step_params, dim3(blocks), dim3(256), 0, s, A, counter, use_counter, kpt, n_k,
-                     ent_x, S, gauge, dt, kappa, kappaJ, efield, phA, phAJ, Alast);
+template <typename T>
+hipError_t launch_step_begin_group(const ParamCell* tab, int ncells, int max_S, int max_nk, int* queue,
+                                   hipStream_t s) {
+  const dim3 grid((unsigned)max(1, (max_S + 255) / 256), (unsigned)((max_nk + kBeginK - 1) / kBeginK),
+                  (unsigned)ncells);
+  hipLaunchKernelGGL((k_step_begin_group<T>), grid, dim3(256), 0, s, tab, queue);
   return hipGetLastError();
 }
+template hipError_t launch_step_begin_group<double>(const ParamCell*, int, int, int, int*, hipStream_t);
+template hipError_t launch_step_begin_group<float>(const ParamCell*, int, int, int, int*, hipStream_t);
 
 // ---------------------------------------------------------------- batch tables
 __global__ void k_batch_tables_in(const IOCell* __restrict__ io, const double* __restrict__ staged, int len) {
@@ -113,63 +147,156 @@ hipError_t launch_batch_tables_out(const IOCell* io, int ncells, double* staged,
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- finish
+// One workgroup: I = -(1/Omega) sum_o f_o [p_o + kappaJ_k norm_o + jNL_o],
+// the orbital energy sum_o f_o [kin + kappaJ.p + 1/2 |kappaJ|^2 norm + vloc + E_NL],
+// and the occupied norm; f_o = 2 w_k. Thread t sums orbitals t, t + 256, ...
+// in order, then a fixed pairwise tree combines the threads. nanflag gets
+// bit 0 for a non-finite norm or momentum, bit 1 (only when norm_tol > 0)
+// for a norm further than norm_tol from 1.
+constexpr int kFinishThreads = 256;
+
+__device__ __forceinline__ void finish_block(const TailCell& c, int bump, double (*red)[5]) {
+  const int t = threadIdx.x;
+  const int n_tot = c.n_orb * c.n_k, tiles = c.tiles;
+  double cx = 0, cy = 0, cz = 0, en = 0, nr = 0;
+  int bad = 0;
+  for (int o = t; o < n_tot; o += kFinishThreads) {
+    const int k = o / c.n_orb;
+    double s[6] = {0, 0, 0, 0, 0, 0};
+    for (int tl = 0; tl < tiles; ++tl)
+      for (int i = 0; i < 6; ++i) s[i] += c.obs[((size_t)o * tiles + tl) * 8 + i];
+    for (int i = 0; i < 6; ++i) s[i] *= c.dV;
+    const double f = 2.0 * c.kw[k];
+    const double kx = c.kappaJ[3 * k], ky = c.kappaJ[3 * k + 1], kz = c.kappaJ[3 * k + 2];
+    double jx = 0, jy = 0, jz = 0, enl = 0;
+    if (c.use_nl) {
+      jx = c.jnl[4 * (size_t)o];
+      jy = c.jnl[4 * (size_t)o + 1];
+      jz = c.jnl[4 * (size_t)o + 2];
+      enl = c.jnl[4 * (size_t)o + 3];
+    }
+    cx += f * (s[1] + kx * s[0] + jx);
+    cy += f * (s[2] + ky * s[0] + jy);
+    cz += f * (s[3] + kz * s[0] + jz);
+    en += f * (s[4] + kx * s[1] + ky * s[2] + kz * s[3] + 0.5 * (kx * kx + ky * ky + kz * kz) * s[0] +
+               s[5] + enl);
+    nr += f * s[0];
+    if (!isfinite(s[0]) || !isfinite(s[1]) || !isfinite(s[2]) || !isfinite(s[3])) bad |= 1;
+    else if (c.norm_tol > 0.0 && fabs(s[0] - 1.0) > c.norm_tol) bad |= 2;
+  }
+  red[t][0] = cx;
+  red[t][1] = cy;
+  red[t][2] = cz;
+  red[t][3] = en;
+  red[t][4] = nr;
+  __syncthreads();
+  for (int w = kFinishThreads / 2; w > 0; w >>= 1) {
+    if (t < w)
+      for (int i = 0; i < 5; ++i) red[t][i] += red[t + w][i];
+    __syncthreads();
+  }
+  if (bad) atomicOr(c.nanflag, bad);
+  if (t == 0) {
+    const double J[3] = {-red[0][0] / c.volume, -red[0][1] / c.volume, -red[0][2] / c.volume};
+    for (int i = 0; i < 3; ++i) c.scalars[i] = J[i];
+    c.scalars[3] = red[0][3];
+    c.scalars[4] = red[0][4];
+    if (bump) {
+      const int n = *c.counter;
+      for (int i = 0; i < 3; ++i) c.Jtab[3 * (size_t)n + i] = J[i];
+      *c.counter = n + 1;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kFinishThreads) void k_finish(TailCell c, int bump) {
+  __shared__ double red[kFinishThreads][5];
+  finish_block(c, bump, red);
+}
+
+hipError_t launch_finish(const TailCell& c, int bump, hipStream_t s) {
+  hipLaunchKernelGGL(k_finish, dim3(1), dim3(kFinishThreads), 0, s, c, bump);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- density
 // part[c][p] = sum over orbitals o in chunk c of 2 w_k |w_o(p)|^2, in order.
+// The loads of kRhoPipe orbitals are issued together: one by one a thread
+// waits out the memory latency per orbital (20.8 us for the 16 cells of 64
+// orbitals of a 12^3 slab, 14 MB).
+constexpr int kRhoPipe = 8;
+
 template <typename T>
-__device__ __forceinline__ void rho_partial_point(const typename Vec2<T>::type* w, const double* kw, int n_orb,
-                                                  int n_k, int N, int chunk, int c, int p, double* part) {
-  const int n_tot = n_orb * n_k;
-  const int o0 = c * chunk;
-  const int o1 = min(n_tot, o0 + chunk);
+__device__ __forceinline__ void rho_partial_point(const TailCell& t, int N, int c, int p) {
+  const auto* __restrict__ w = static_cast<const typename Vec2<T>::type*>(t.w) + p;
+  const int n_tot = t.n_orb * t.n_k;
+  const int o0 = c * t.chunk, o1 = min(n_tot, o0 + t.chunk);
   double acc = 0.0;
-  for (int o = o0; o < o1; ++o) {
-    const auto v = w[(size_t)o * N + p];
-    const double re = (double)v.x, im = (double)v.y;
-    acc += 2.0 * kw[o / n_orb] * (re * re + im * im);
+  for (int o = o0; o < o1; o += kRhoPipe) {
+    typename Vec2<T>::type v[kRhoPipe];
+#pragma unroll
+    for (int u = 0; u < kRhoPipe; ++u) v[u] = w[(size_t)min(o + u, o1 - 1) * N];
+#pragma unroll
+    for (int u = 0; u < kRhoPipe; ++u) {
+      const double re = (double)v[u].x, im = (double)v[u].y;
+      if (o + u < o1) acc += 2.0 * t.kw[(o + u) / t.n_orb] * (re * re + im * im);
+    }
   }
-  part[(size_t)c * N + p] = acc;
+  t.rho_out[(size_t)c * N + p] = acc;
+}
+
+// with_finish: the first workgroup forms the current instead (it needs the
+// observables only, and is over long before the density pass)
+template <typename T>
+__device__ __forceinline__ void density_block(const TailCell& t, int N, int with_finish, int bump, int b) {
+  __shared__ double red[kFinishThreads][5];
+  if (with_finish && b == 0) {
+    finish_block(t, bump, red);
+    return;
+  }
+  b -= with_finish;
+  const int bpc = (N + 255) / 256;
+  const int c = b / bpc, p = (b - c * bpc) * 256 + (int)threadIdx.x;
+  if (c < t.nchunks && p < N) rho_partial_point<T>(t, N, c, p);
 }
 
 template <typename T>
-__global__ void k_rho_partial(const typename Vec2<T>::type* w, const double* kw, int n_orb, int n_k,
-                              int N, int chunk, double* part) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  rho_partial_point<T>(w, kw, n_orb, n_k, N, chunk, (int)blockIdx.y, p, part);
+__global__ __launch_bounds__(256) void k_density(TailCell t, int N, int with_finish) {
+  density_block<T>(t, N, with_finish, 1, (int)blockIdx.x);
 }
 
-// the same for the cells of a group: cell blockIdx.z, chunk blockIdx.y
+// the same for the cells of a group (cell blockIdx.y)
 template <typename T>
-__global__ void k_rho_partial_group(const TailCell* __restrict__ tab, int N, int chunk) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  const TailCell& t = tab[blockIdx.z];
-  if (p >= N || (int)blockIdx.y >= t.nchunks) return;
-  rho_partial_point<T>(static_cast<const typename Vec2<T>::type*>(t.w), t.kw, t.n_orb, t.n_k, N, chunk,
-                       (int)blockIdx.y, p, t.rho_out);
+__global__ __launch_bounds__(256) void k_density_group(const TailCell* __restrict__ tab, int N) {
+  density_block<T>(tab[blockIdx.y], N, 1, 1, (int)blockIdx.x);
+}
+
+// Orbitals per chunk: enough (chunk, point block) workgroups to fill the chip
+// (about 2048), but at least 16 orbitals, so that the partial planes stay
+// under a tenth of the orbitals' bytes, and at most 128.
+int density_chunk(int N, int n_tot) {
+  const long want = (long)n_tot * ((N + 255) / 256) / 2048;
+  return (int)std::max(16L, std::min(128L, want));
 }
 
 template <typename T>
-hipError_t launch_rho_partial_group(const TailCell* tab, int ncells, int N, int chunk, int max_chunks,
-                                    hipStream_t s) {
-  hipLaunchKernelGGL((k_rho_partial_group<T>), dim3((N + 255) / 256, max_chunks, ncells), dim3(256), 0, s, tab,
-                     N, chunk);
+hipError_t launch_density(const TailCell& t, int N, int with_finish, hipStream_t s) {
+  const unsigned grid = (unsigned)(with_finish + (N + 255) / 256 * t.nchunks);
+  hipLaunchKernelGGL((k_density<T>), dim3(grid), dim3(256), 0, s, t, N, with_finish);
   return hipGetLastError();
 }
-template hipError_t launch_rho_partial_group<double>(const TailCell*, int, int, int, int, hipStream_t);
-template hipError_t launch_rho_partial_group<float>(const TailCell*, int, int, int, int, hipStream_t);
+template hipError_t launch_density<double>(const TailCell&, int, int, hipStream_t);
+template hipError_t launch_density<float>(const TailCell&, int, int, hipStream_t);
 
 template <typename T>
-hipError_t launch_rho_partial(const typename Vec2<T>::type* w, const double* kw, int n_orb, int n_k,
-                              int N, int chunk, double* part, hipStream_t s) {
-  const int nchunks = (n_orb * n_k + chunk - 1) / chunk;
-  hipLaunchKernelGGL((k_rho_partial<T>), dim3((N + 255) / 256, nchunks), dim3(256), 0, s, w, kw,
-                     n_orb, n_k, N, chunk, part);
+hipError_t launch_density_group(const TailCell* tab, int ncells, int N, int max_chunks, hipStream_t s) {
+  const dim3 grid((unsigned)(1 + (N + 255) / 256 * max_chunks), (unsigned)ncells);
+  hipLaunchKernelGGL((k_density_group<T>), grid, dim3(256), 0, s, tab, N);
   return hipGetLastError();
 }
-template hipError_t launch_rho_partial<double>(const double2*, const double*, int, int, int, int,
-                                               double*, hipStream_t);
-template hipError_t launch_rho_partial<float>(const float2*, const double*, int, int, int, int,
-                                              double*, hipStream_t);
+template hipError_t launch_density_group<double>(const TailCell*, int, int, int, hipStream_t);
+template hipError_t launch_density_group<float>(const TailCell*, int, int, int, hipStream_t);
 
 // rho[p] = sum over chunks of part[c][p]. A workgroup takes 64 points and
 // kRedSlices slices: slice j sums chunks j, j + kRedSlices, ... in order, then
@@ -495,9 +622,11 @@ hipError_t launch_fft_lines_group(const TailCell* tab, int ncells, int M1, int M
   if (fused && (axis != 2 || !use_K)) return hipErrorInvalidValue;
   const long nlines = (long)l1 * l2;
   if (nlines <= 0 || ncells <= 0) return hipSuccess;
-  // every line is transformed the same way whatever B is; with many cells
-  // the grid is full without spreading one cell's lines thinly
-  const int B = max(1, min(256, 2048 / plan.M));
+  // every line is transformed the same way whatever B is; lines per workgroup
+  // as long as all cells together give a workgroup per compute unit (two cells
+  // of 16^3 on four workgroups took 14 us a pass)
+  int B = max(1, min(256, 2048 / plan.M));
+  while (B > 1 && nlines / B * ncells < 256) B /= 2;
   const size_t lds = ((size_t)2 * B * plan.M + 2 * (size_t)plan.M) * sizeof(double2);
   FFTEnds ends{nullptr, n1, n2, n3, nullptr};
   FFTLines ln{l1, l2, n_in, n_out, fused};
@@ -567,15 +696,9 @@ __device__ void pz81(double rho, int exchange_too, double* v, double* e) {
 }
 
 // xc: 0 none, 1 PZ81, 2 and 3 the exchange in vx_mgga plus PZ81 correlation
-__device__ __forceinline__ void xc_point(const double2* data, int n1, int n2, int M1, int M2, double vh_scale,
-                                         const double* rho, const double* Vloc, int hartree, int xc,
-                                         const double* vx_mgga, double* Vd, float* Vf, double* vh_out,
-                                         double* exc, size_t p) {
-  const int x = (int)(p % n1);
-  const int y = (int)((p / n1) % n2);
-  const int z = (int)(p / ((size_t)n1 * n2));
-  double vh = 0.0;
-  if (hartree) vh = data[((size_t)z * M2 + y) * M1 + x].x * vh_scale;
+__device__ __forceinline__ void xc_value(double vh, const double* rho, const double* Vloc, int xc,
+                                         const double* vx_mgga, double* Vd, float* Vf, double* vh_out, double* exc,
+                                         size_t p) {
   double vxc = 0.0, e = 0.0;
   if (xc) {
     pz81(rho[p], xc == 1, &vxc, &e);
@@ -586,6 +709,194 @@ __device__ __forceinline__ void xc_point(const double2* data, int n1, int n2, in
   Vf[p] = (float)v;
   vh_out[p] = vh;
   exc[p] = e;
+}
+
+__device__ __forceinline__ void xc_point(const double2* data, int n1, int n2, int M1, int M2, double vh_scale,
+                                         const double* rho, const double* Vloc, int hartree, int xc,
+                                         const double* vx_mgga, double* Vd, float* Vf, double* vh_out,
+                                         double* exc, size_t p) {
+  const int x = (int)(p % n1);
+  const int y = (int)((p / n1) % n2);
+  const int z = (int)(p / ((size_t)n1 * n2));
+  double vh = 0.0;
+  if (hartree) vh = data[((size_t)z * M2 + y) * M1 + x].x * vh_scale;
+  xc_value(vh, rho, Vloc, xc, vx_mgga, Vd, Vf, vh_out, exc, p);
+}
+
+// ---------------------------------------------------------------- Poisson by planes
+// For a periodic box whose xy plane fits a workgroup the Poisson solve is
+// three launches: (1) per z plane, the density summed over its chunks and the
+// forward transforms along x and y in LDS; (2) the z lines, forward, kernel,
+// inverse (k_fft_axis); (3) per plane the inverse transforms along y and x and
+// the potential. Each line is transformed as in the pass-by-pass form (which
+// isolated boxes and larger planes use), so the bits of the solve are the same;
+// that form's reduction, five passes and assembly are seven launches of 4 to
+// 7 us each, half of a small cell's step.
+struct PlanePlan {
+  int n1, n2, n3;
+  FFTPlan x, y;
+};
+
+bool poisson_planes(int periodic, int hartree, int n1, int n2) {
+  return periodic && hartree && n1 * n2 <= kPlaneMax;
+}
+
+__device__ __forceinline__ void plane_twiddles(const PlanePlan& pl, int sign, double2* twx, double2* twy) {
+  fft_twiddles(pl.x, sign, twx);
+  fft_twiddles(pl.y, sign, twy);
+}
+
+// [rows][cols] -> [cols][rows]
+__device__ __forceinline__ void plane_transpose(const double2* in, double2* out, int rows, int cols) {
+  for (int i = threadIdx.x; i < rows * cols; i += blockDim.x) {
+    const int r = i / cols, c = i - r * cols;
+    out[c * rows + r] = in[i];
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void poisson_forward_plane(const TailCell& t, const PlanePlan& pl, int z,
+                                                      unsigned char* smem_raw) {
+  const int P = pl.n1 * pl.n2;
+  const size_t N = (size_t)P * pl.n3;
+  double2* a = reinterpret_cast<double2*>(smem_raw);
+  double2* b = a + P;
+  double2 *twx = b + P, *twy = twx + pl.n1;
+  plane_twiddles(pl, -1, twx, twy);
+  double* rho = t.rho + (size_t)z * P;
+  if (t.nchunks == 1) {
+    for (int p = threadIdx.x; p < P; p += blockDim.x) a[p] = make_double2(rho[p], 0.0);
+  } else {
+    // slices of the workgroup sum chunks j, j + nsl, ... in order, then the
+    // slices add up in order
+    const int nsl = max(1, (int)blockDim.x / P);
+    double* red = reinterpret_cast<double*>(twy + pl.n2);  // [nsl][P] (nsl > 1: at most blockDim.x)
+    const double* part = t.rho_part + (size_t)z * P;
+    for (int i = threadIdx.x; i < nsl * P; i += blockDim.x) {
+      const int j = i / P, p = i - j * P;
+      double acc = 0.0;
+      for (int c = j; c < t.nchunks; c += kRhoPipe * nsl) {
+        double v[kRhoPipe];
+#pragma unroll
+        for (int u = 0; u < kRhoPipe; ++u) v[u] = part[(size_t)min(c + u * nsl, t.nchunks - 1) * N + p];
+#pragma unroll
+        for (int u = 0; u < kRhoPipe; ++u) acc += c + u * nsl < t.nchunks ? v[u] : 0.0;
+      }
+      if (nsl == 1) {
+        rho[p] = acc;
+        a[p] = make_double2(acc, 0.0);
+      } else {
+        red[i] = acc;
+      }
+    }
+    if (nsl > 1) {
+      __syncthreads();
+      for (int p = threadIdx.x; p < P; p += blockDim.x) {
+        double acc = red[p];
+        for (int j = 1; j < nsl; ++j) acc += red[j * P + p];
+        rho[p] = acc;
+        a[p] = make_double2(acc, 0.0);
+      }
+    }
+  }
+  __syncthreads();
+  double2* r = fft_lines_lds(pl.x, a, b, pl.n2, -1, twx);   // [y][x]
+  double2* o = r == a ? b : a;
+  plane_transpose(r, o, pl.n2, pl.n1);                       // [x][y]
+  r = fft_lines_lds(pl.y, o, r, pl.n1, -1, twy);
+  double2* out = t.fft + (size_t)z * P;
+  for (int i = threadIdx.x; i < P; i += blockDim.x) {
+    const int y = i / pl.n1, x = i - y * pl.n1;
+    out[i] = r[x * pl.n2 + y];
+  }
+}
+
+__device__ __forceinline__ void poisson_inverse_plane(const TailCell& t, const PlanePlan& pl, int xc,
+                                                      const double* vx_mgga, int z, unsigned char* smem_raw) {
+  const int P = pl.n1 * pl.n2;
+  double2* a = reinterpret_cast<double2*>(smem_raw);
+  double2* b = a + P;
+  double2 *twx = b + P, *twy = twx + pl.n1;
+  plane_twiddles(pl, +1, twx, twy);
+  const double2* in = t.fft + (size_t)z * P;
+  for (int i = threadIdx.x; i < P; i += blockDim.x) {
+    const int y = i / pl.n1, x = i - y * pl.n1;
+    a[x * pl.n2 + y] = in[i];
+  }
+  __syncthreads();
+  double2* r = fft_lines_lds(pl.y, a, b, pl.n1, +1, twy);   // [x][y]
+  double2* o = r == a ? b : a;
+  plane_transpose(r, o, pl.n1, pl.n2);                       // [y][x]
+  r = fft_lines_lds(pl.x, o, r, pl.n2, +1, twx);
+  for (int i = threadIdx.x; i < P; i += blockDim.x)
+    xc_value(r[i].x * t.vh_scale, t.rho, t.Vloc, xc, vx_mgga, t.Vd, t.Vf, t.vh, t.exc, (size_t)z * P + i);
+}
+
+constexpr int kPlaneThreads = 1024;
+
+__global__ __launch_bounds__(kPlaneThreads) void k_poisson_forward(TailCell t, PlanePlan pl) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  poisson_forward_plane(t, pl, (int)blockIdx.x, smem_raw);
+}
+__global__ __launch_bounds__(kPlaneThreads) void k_poisson_inverse(TailCell t, PlanePlan pl, int xc,
+                                                                   const double* vx_mgga) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  poisson_inverse_plane(t, pl, xc, vx_mgga, (int)blockIdx.x, smem_raw);
+}
+// the same for the cells of a group (cell blockIdx.y; LDA or no xc)
+__global__ __launch_bounds__(kPlaneThreads) void k_poisson_forward_group(const TailCell* __restrict__ tab,
+                                                                         PlanePlan pl) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  poisson_forward_plane(tab[blockIdx.y], pl, (int)blockIdx.x, smem_raw);
+}
+__global__ __launch_bounds__(kPlaneThreads) void k_poisson_inverse_group(const TailCell* __restrict__ tab,
+                                                                         PlanePlan pl, int xc) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  poisson_inverse_plane(tab[blockIdx.y], pl, xc, nullptr, (int)blockIdx.x, smem_raw);
+}
+
+static bool plane_plan(int n1, int n2, int n3, PlanePlan* pl, size_t* lds, int* threads) {
+  pl->n1 = n1;
+  pl->n2 = n2;
+  pl->n3 = n3;
+  *lds = ((size_t)2 * n1 * n2 + n1 + n2) * sizeof(double2) + kPlaneThreads * sizeof(double);
+  *threads = kPlaneThreads;
+  return n1 * n2 <= kPlaneMax && fft_plan(n1, &pl->x) && fft_plan(n2, &pl->y);
+}
+
+hipError_t launch_poisson_forward(const TailCell& t, int n1, int n2, int n3, hipStream_t s) {
+  PlanePlan pl;
+  size_t lds;
+  int th;
+  if (!plane_plan(n1, n2, n3, &pl, &lds, &th)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_poisson_forward, dim3(n3), dim3(th), lds, s, t, pl);
+  return hipGetLastError();
+}
+hipError_t launch_poisson_inverse(const TailCell& t, int n1, int n2, int n3, int xc, const double* vx_mgga,
+                                  hipStream_t s) {
+  PlanePlan pl;
+  size_t lds;
+  int th;
+  if (!plane_plan(n1, n2, n3, &pl, &lds, &th)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_poisson_inverse, dim3(n3), dim3(th), lds, s, t, pl, xc, vx_mgga);
+  return hipGetLastError();
+}
+hipError_t launch_poisson_forward_group(const TailCell* tab, int ncells, int n1, int n2, int n3, hipStream_t s) {
+  PlanePlan pl;
+  size_t lds;
+  int th;
+  if (!plane_plan(n1, n2, n3, &pl, &lds, &th)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_poisson_forward_group, dim3(n3, ncells), dim3(th), lds, s, tab, pl);
+  return hipGetLastError();
+}
+hipError_t launch_poisson_inverse_group(const TailCell* tab, int ncells, int n1, int n2, int n3, int xc,
+                                        hipStream_t s) {
+  PlanePlan pl;
+  size_t lds;
+  int th;
+  if (xc >= 2 || !plane_plan(n1, n2, n3, &pl, &lds, &th)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_poisson_inverse_group, dim3(n3, ncells), dim3(th), lds, s, tab, pl, xc);
+  return hipGetLastError();
 }
 
 __global__ void k_xc_assemble(const double2* data, int n1, int n2, int n3, int M1, int M2,
@@ -625,102 +936,6 @@ hipError_t launch_xc_assemble(const double2* data, int n1, int n2, int n3, int M
   const size_t N = (size_t)n1 * n2 * n3;
   hipLaunchKernelGGL(k_xc_assemble, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, data, n1, n2,
                      n3, M1, M2, vh_scale, rho, Vloc, hartree, xc, vx_mgga, Vd, Vf, vh, exc);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------- finish
-// One workgroup: I = -(1/Omega) sum_o f_o [p_o + kappaJ_k norm_o + jNL_o],
-// the orbital energy sum_o f_o [kin + kappaJ.p + 1/2 |kappaJ|^2 norm + vloc + E_NL],
-// and the occupied norm; f_o = 2 w_k. Thread t sums orbitals t, t+1024, ...
-// in order, then a fixed pairwise tree combines the threads. nanflag gets
-// bit 0 for a non-finite norm or momentum, bit 1 (only when norm_tol > 0)
-// for a norm further than norm_tol from 1.
-__device__ __forceinline__ void finish_block(const double* obs, int tiles, const double* jnl, int use_nl,
-                                             const double* kw, const double* kappaJ, int n_orb, int n_k,
-                                             double dV, double volume, int* counter, int bump, double* Jtab,
-                                             double* scalars, int* nanflag, double norm_tol, double (*red)[5]) {
-  const int t = threadIdx.x;
-  const int n_tot = n_orb * n_k;
-  double cx = 0, cy = 0, cz = 0, en = 0, nr = 0;
-  int bad = 0;
-  for (int o = t; o < n_tot; o += blockDim.x) {
-    const int k = o / n_orb;
-    double s[6] = {0, 0, 0, 0, 0, 0};
-    for (int tl = 0; tl < tiles; ++tl)
-      for (int i = 0; i < 6; ++i) s[i] += obs[((size_t)o * tiles + tl) * 8 + i];
-    for (int i = 0; i < 6; ++i) s[i] *= dV;
-    const double f = 2.0 * kw[k];
-    const double kx = kappaJ[3 * k], ky = kappaJ[3 * k + 1], kz = kappaJ[3 * k + 2];
-    double jx = 0, jy = 0, jz = 0, enl = 0;
-    if (use_nl) {
-      jx = jnl[4 * (size_t)o];
-      jy = jnl[4 * (size_t)o + 1];
-      jz = jnl[4 * (size_t)o + 2];
-      enl = jnl[4 * (size_t)o + 3];
-    }
-    cx += f * (s[1] + kx * s[0] + jx);
-    cy += f * (s[2] + ky * s[0] + jy);
-    cz += f * (s[3] + kz * s[0] + jz);
-    en += f * (s[4] + kx * s[1] + ky * s[2] + kz * s[3] + 0.5 * (kx * kx + ky * ky + kz * kz) * s[0] +
-               s[5] + enl);
-    nr += f * s[0];
-    if (!isfinite(s[0]) || !isfinite(s[1]) || !isfinite(s[2]) || !isfinite(s[3])) bad |= 1;
-    else if (norm_tol > 0.0 && fabs(s[0] - 1.0) > norm_tol) bad |= 2;
-  }
-  red[t][0] = cx;
-  red[t][1] = cy;
-  red[t][2] = cz;
-  red[t][3] = en;
-  red[t][4] = nr;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if (t < w)
-      for (int i = 0; i < 5; ++i) red[t][i] += red[t + w][i];
-    __syncthreads();
-  }
-  if (bad) atomicOr(nanflag, bad);
-  if (t == 0) {
-    const double J[3] = {-red[0][0] / volume, -red[0][1] / volume, -red[0][2] / volume};
-    for (int i = 0; i < 3; ++i) scalars[i] = J[i];
-    scalars[3] = red[0][3];
-    scalars[4] = red[0][4];
-    if (bump) {
-      const int n = *counter;
-      for (int i = 0; i < 3; ++i) Jtab[3 * (size_t)n + i] = J[i];
-      *counter = n + 1;
-    }
-  }
-}
-
-__global__ __launch_bounds__(1024) void k_finish(const double* obs, int tiles, const double* jnl,
-                                                 int use_nl, const double* kw, const double* kappaJ,
-                                                 int n_orb, int n_k, double dV, double volume,
-                                                 int* counter, int bump, double* Jtab,
-                                                 double* scalars, int* nanflag, double norm_tol) {
-  __shared__ double red[1024][5];
-  finish_block(obs, tiles, jnl, use_nl, kw, kappaJ, n_orb, n_k, dV, volume, counter, bump, Jtab, scalars, nanflag,
-               norm_tol, red);
-}
-
-// one step's current of every cell of a group (one workgroup per cell)
-__global__ __launch_bounds__(1024) void k_finish_group(const TailCell* __restrict__ tab, int tiles) {
-  __shared__ double red[1024][5];
-  const TailCell& c = tab[blockIdx.x];
-  finish_block(c.obs, tiles, c.jnl, c.use_nl, c.kw, c.kappaJ, c.n_orb, c.n_k, c.dV, c.volume, c.counter, 1, c.Jtab,
-               c.scalars, c.nanflag, c.norm_tol, red);
-}
-
-hipError_t launch_finish_group(const TailCell* tab, int ncells, int tiles, hipStream_t s) {
-  hipLaunchKernelGGL(k_finish_group, dim3(ncells), dim3(1024), 0, s, tab, tiles);
-  return hipGetLastError();
-}
-
-hipError_t launch_finish(const double* obs, int tiles, const double* jnl, int use_nl,
-                         const double* kw, const double* kappaJ, int n_orb, int n_k, double dV,
-                         double volume, int* counter, int bump, double* Jtab, double* scalars,
-                         int* nanflag, double norm_tol, hipStream_t s) {
-  hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, obs, tiles, jnl, use_nl, kw, kappaJ, n_orb,
-                     n_k, dV, volume, counter, bump, Jtab, scalars, nanflag, norm_tol);
   return hipGetLastError();
 }
 
