@@ -52,7 +52,8 @@ hipError_t nalloc(P** p, size_t count) {
 }
 
 void nn_release_work(tddft_nn* n) {
-  for (float* p : {n->X, n->target, n->wk.h1, n->wk.h2, n->wk.y, n->wk.dy, n->wk.dz2, n->wk.dz1, n->wk.loss})
+  for (float* p : {n->X, n->target, n->wk.h1, n->wk.h2, n->wk.y, n->wk.dy, n->wk.dz2, n->wk.dz1, n->wk.loss,
+                   n->wk.part})
     if (p) (void)hipFree(p);
   if (n->idx) (void)hipFree(n->idx);
   n->X = n->target = nullptr;
@@ -68,7 +69,7 @@ tddft_status nn_reserve(tddft_nn* n, int B) {
   if (nalloc(&n->X, (size_t)B * W) || nalloc(&n->target, B) || nalloc(&n->idx, B) ||
       nalloc(&n->wk.h1, (size_t)B * H) || nalloc(&n->wk.h2, (size_t)B * H) || nalloc(&n->wk.y, B) ||
       nalloc(&n->wk.dy, B) || nalloc(&n->wk.dz2, (size_t)B * H) || nalloc(&n->wk.dz1, (size_t)B * H) ||
-      nalloc(&n->wk.loss, 1)) {
+      nalloc(&n->wk.loss, 1) || nalloc(&n->wk.part, nn_part_floats(n->sh, B))) {
     nn_release_work(n);
     return nn_fail(n, TDDFT_ENOMEM, "device allocation failed (network workspace)");
   }
@@ -76,12 +77,16 @@ tddft_status nn_reserve(tddft_nn* n, int B) {
   return TDDFT_OK;
 }
 
-tddft_status nn_adam_now(tddft_nn* n, float lr = -1.0f) {
+// the next Adam step's numbers (lr < 0: the configuration's)
+NNAdam nn_adam_next(tddft_nn* n, float lr = -1.0f) {
   n->t_adam += 1;
   const double c1 = 1.0 - std::pow((double)n->cfg.beta1, n->t_adam);
   const double c2 = 1.0 - std::pow((double)n->cfg.beta2, n->t_adam);
-  NHIP(nn_adam(n->theta, n->m, n->v, n->grad, n->np, lr > 0.0f ? lr : n->cfg.lr, n->cfg.beta1, n->cfg.beta2,
-               n->cfg.eps, (float)c1, (float)c2, n->stream));
+  return NNAdam{lr > 0.0f ? lr : n->cfg.lr, n->cfg.beta1, n->cfg.beta2, n->cfg.eps, (float)c1, (float)c2};
+}
+
+tddft_status nn_adam_now(tddft_nn* n, float lr = -1.0f) {
+  NHIP(nn_adam(n->theta, n->m, n->v, n->grad, n->np, nn_adam_next(n, lr), n->stream));
   return TDDFT_OK;
 }
 
@@ -204,17 +209,15 @@ tddft_status tddft_nn_fit_linear(tddft_nn* n, int32_t n_traj, int32_t T, const d
     ++used;
   }
   if ((long)used * T < W + 1) return nn_fail(n, TDDFT_EINVAL, "too few samples within a_fit for the linear fit");
-  const int nn1 = W + 1;
-  double *dA = nullptr, *dY = nullptr, *dG = nullptr, *db = nullptr;
+  double *dA = nullptr, *dY = nullptr, *dG = nullptr;
   int* dok = nullptr;
   auto cleanup = [&](tddft_status st) {
-    for (double* p : {dA, dY, dG, db})
+    for (double* p : {dA, dY, dG})
       if (p) (void)hipFree(p);
     if (dok) (void)hipFree(dok);
     return st;
   };
-  if (nalloc(&dA, hA.size()) || nalloc(&dY, hY.size()) || nalloc(&dG, (size_t)nn1 * nn1) || nalloc(&db, nn1) ||
-      nalloc(&dok, 1))
+  if (nalloc(&dA, hA.size()) || nalloc(&dY, hY.size()) || nalloc(&dG, nn_fit_doubles(W)) || nalloc(&dok, 1))
     return cleanup(nn_fail(n, TDDFT_ENOMEM, "device allocation failed (linear fit)"));
 #define FHIP(expr)                                                                                       do {                                                                                                     hipError_t e_ = (expr);                                                                                if (e_ != hipSuccess) return cleanup(nn_fail(n, TDDFT_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)));   } while (0)
   FHIP(hipMemcpyAsync(dA, hA.data(), hA.size() * sizeof(double), hipMemcpyHostToDevice, n->stream));
@@ -224,7 +227,7 @@ tddft_status tddft_nn_fit_linear(tddft_nn* n, int32_t n_traj, int32_t T, const d
   float* w3 = n->theta + off_w3;
   float* b3 = w3 + H;
   float* ws = b3 + 1;
-  FHIP(nn_fit_linear(dA, dY, used, T, W, lambda_rel, dG, db, ws, b3, dok, n->stream));
+  FHIP(nn_fit_linear(dA, dY, used, T, W, lambda_rel, dG, ws, b3, dok, n->stream));
   // the hidden layers start from zero output weight: the network is the fit
   FHIP(nn_zero(w3, H, n->stream));
   FHIP(nn_zero(n->m, n->np, n->stream));
@@ -286,18 +289,23 @@ tddft_status tddft_nn_train_ex(tddft_nn* n, int32_t n_traj, int32_t T, const dou
     THIP(hipMemcpyAsync(dperm, perm.data(), S * sizeof(int), hipMemcpyHostToDevice, n->stream));
     for (long off = 0; off < S; off += B) {
       const int b = (int)std::min<long>(B, S - off);
+      const float lr = (flags & TDDFT_NN_COSINE_LR)
+                           ? (float)(0.5 * n->cfg.lr * (1.0 + std::cos(M_PI * (double)ep / (double)epochs)))
+                           : n->cfg.lr;
+      ++n_batches[ep];
+      if (nn_fused(n->sh, B)) {
+        THIP(nn_train_step(n->sh, n->theta, n->m, n->v, n->grad, dA, dJ, T, dperm + off, b, n->wk,
+                           nn_adam_next(n, lr), (flags & TDDFT_NN_FREEZE_LINEAR) ? 1 : 0, dloss + ep, n->stream));
+        continue;
+      }
       THIP(nn_gather(dA, dJ, T, n->sh.W, dperm + off, b, n->X, n->target, n->stream));
       THIP(nn_forward(n->sh, n->theta, n->X, b, n->wk, n->stream));
       THIP(nn_backward(n->sh, n->theta, n->X, n->target, b, n->wk, n->grad, n->stream));
       THIP(nn_accumulate(n->wk.loss, dloss + ep, n->stream));
       if (flags & TDDFT_NN_FREEZE_LINEAR)  // b3 and ws are the last W + 1 parameters
         THIP(nn_zero(n->grad + n->np - (n->sh.W + 1), n->sh.W + 1, n->stream));
-      const float lr = (flags & TDDFT_NN_COSINE_LR)
-                           ? (float)(0.5 * n->cfg.lr * (1.0 + std::cos(M_PI * (double)ep / (double)epochs)))
-                           : n->cfg.lr;
       st = nn_adam_now(n, lr);
       if (st != TDDFT_OK) return cleanup(st);
-      ++n_batches[ep];
     }
   }
   std::vector<float> el(std::max(epochs, 1));

@@ -389,19 +389,30 @@ struct NNShape {
 };
 struct NNWork {  // per-batch activations and gradients, FP32
   float *h1, *h2, *y, *dy, *dz2, *dz1, *loss;
+  float* part;  // the training step's sums per tile of samples
+};
+struct NNAdam {  // Adam's step: lr, the moments' decay, eps, and 1 - beta^t
+  float lr, b1, b2, eps, c1, c2;
 };
 hipError_t nn_forward(const NNShape& sh, const float* theta, const float* X, int B, NNWork& wk, hipStream_t s);
 hipError_t nn_backward(const NNShape& sh, const float* theta, const float* X, const float* target, int B,
                        NNWork& wk, float* grad, hipStream_t s);
-hipError_t nn_adam(float* theta, float* m, float* v, const float* g, long n, float lr, float b1, float b2,
-                   float eps, float c1, float c2, hipStream_t s);
+hipError_t nn_adam(float* theta, float* m, float* v, const float* g, long n, const NNAdam& o, hipStream_t s);
+// one Adam step on a batch of the trajectories in two launches, where
+// nn_fused says so; wk.part holds nn_part_floats
+bool nn_fused(const NNShape& sh, int B);
+size_t nn_part_floats(const NNShape& sh, int B);
+hipError_t nn_train_step(const NNShape& sh, float* theta, float* m, float* v, float* grad, const float* seqA,
+                         const float* seqJ, int T, const int* idx, int B, NNWork& wk, const NNAdam& o, int freeze,
+                         float* loss, hipStream_t s);
 hipError_t nn_gather(const float* seqA, const float* seqJ, int T, int W, const int* idx, int B, float* X,
                      float* target, hipStream_t s);
 hipError_t nn_accumulate(const float* src, float* dst, hipStream_t s);
 // least squares of the skip weights ws [W] and output bias b3 over trajectories
-// A, Y [n_traj][T] (scaled, FP64); G [(W+1)^2] and b [W+1] are work arrays
+// A, Y [n_traj][T] (scaled, FP64); G is a work array of nn_fit_doubles(W)
+size_t nn_fit_doubles(int W);
 hipError_t nn_fit_linear(const double* A, const double* Y, int n_traj, int T, int W, double lambda_rel, double* G,
-                         double* b, float* ws, float* b3, int* ok, hipStream_t s);
+                         float* ws, float* b3, int* ok, hipStream_t s);
 hipError_t nn_zero(float* p, long n, hipStream_t s);
 
 }  // namespace td

@@ -122,14 +122,26 @@ __global__ __launch_bounds__(256) void k_nn_dy_loss(const float* __restrict__ y,
   if (threadIdx.x == 0) loss[0] = red[0] / (float)B;
 }
 
-// out[j] = sum_b M[b][j] * (wgt ? wgt[b] : 1), j < N (column sums in b order)
-__global__ void k_colsum(const float* __restrict__ M, const float* __restrict__ wgt, int B, int N,
-                         float* __restrict__ out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
+// out[j] = sum_b M[b][j] * (wgt ? wgt[b] : 1), j < N. Sixteen slices of the
+// workgroup sum rows b = slice, slice + 16, ... in order, then the slices add
+// up in order: one thread per column walked B dependent loads (27.7 us for 256
+// rows).
+constexpr int kSumSlices = 16, kSumCols = 16;
+__global__ __launch_bounds__(kSumSlices * kSumCols) void k_colsum(const float* __restrict__ M,
+                                                                  const float* __restrict__ wgt, int B, int N,
+                                                                  float* __restrict__ out) {
+  __shared__ float red[kSumSlices][kSumCols];
+  const int c = threadIdx.x % kSumCols, r = threadIdx.x / kSumCols;
+  const int j = blockIdx.x * kSumCols + c;
   float s = 0.0f;
-  for (int b = 0; b < B; ++b) s = fmaf(M[(long)b * N + j], wgt ? wgt[b] : 1.0f, s);
-  out[j] = s;
+  if (j < N)
+    for (int b = r; b < B; b += kSumSlices) s = fmaf(M[(long)b * N + j], wgt ? wgt[b] : 1.0f, s);
+  red[r][c] = s;
+  __syncthreads();
+  if (r == 0 && j < N) {
+    for (int i = 1; i < kSumSlices; ++i) s += red[i][c];
+    out[j] = s;
+  }
 }
 
 // dz2[b][h] = dy[b] w3[h] (1 - h2[b][h]^2)
@@ -144,17 +156,19 @@ __global__ void k_nn_dz2(const float* __restrict__ dy, const float* __restrict__
 
 // Adam: m = b1 m + (1 - b1) g; v = b2 v + (1 - b2) g^2;
 // theta -= lr (m / c1) / (sqrt(v / c2) + eps), c1 = 1 - b1^t, c2 = 1 - b2^t
-__global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, long n, float lr, float b1, float b2, float eps, float c1,
-                       float c2) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+__device__ __forceinline__ void adam_one(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
+                                         long i, float gi, const NNAdam& o) {
+  const float mi = o.b1 * m[i] + (1.0f - o.b1) * gi;
+  const float vi = o.b2 * v[i] + (1.0f - o.b2) * gi * gi;
   m[i] = mi;
   v[i] = vi;
-  theta[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  theta[i] -= o.lr * (mi / o.c1) / (sqrtf(vi / o.c2) + o.eps);
+}
+
+__global__ void k_adam(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
+                       const float* __restrict__ g, long n, NNAdam o) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) adam_one(theta, m, v, i, g[i], o);
 }
 
 // training batch from trajectories: for sample s = idx[b] = traj * T + t,
@@ -176,6 +190,286 @@ __global__ void k_accum(const float* __restrict__ src, float* __restrict__ dst) 
   if (threadIdx.x == 0) dst[0] += src[0];
 }
 
+// ---------------------------------------------------------------- training step
+// One Adam step on a batch in two launches, for hidden widths up to 64,
+// windows up to 1024 and batches up to 4096. As seventeen launches (window
+// gather, three products, sums, Adam) a batch of 256 with W = 512, H = 16 took
+// 0.19 ms, all of it launch latency and serial column sums; as two it is 21 us
+// (14.5 and 6.3 us: dependent loads and eight barriers on 16 workgroups).
+//
+// k_nn_tile: sixteen samples per workgroup, forward and backward down to dz1,
+// with their windows read from the trajectories into LDS; writes dz1, dy and
+// the tile's sums for the small parameters (b1, W2, b2, w3, b3) and the loss.
+// k_nn_update: a 16 x 16 tile of W1 per workgroup, gW1 = dz1^T X on the matrix
+// cores with the windows again read from the trajectories, then Adam on the
+// tile; the last workgroups add up the small parameters' sums in tile order.
+constexpr int kFusedH = 64, kFusedW = 1024, kFusedB = 4096;
+
+struct NNTrain {
+  const float* seqA;   // [n_traj][T]
+  const float* seqJ;
+  const int* idx;      // [B] sample = traj * T + t
+  int T, B, W, H;
+  float *theta, *m, *v, *grad;
+  float *dz1, *dy, *part;
+  float* loss;         // the batch's mean loss is added to it
+  int freeze;          // b3 and ws get a zero gradient
+};
+
+__host__ __device__ inline long nn_small(int H) { return (long)H * H + 3L * H + 1; }
+
+bool nn_fused(const NNShape& sh, int B) { return sh.H <= kFusedH && sh.W <= kFusedW && B <= kFusedB; }
+// room for any fused batch of at most B samples
+size_t nn_part_floats(const NNShape& sh, int B) {
+  if (!nn_fused(sh, 1)) return 1;
+  return (size_t)((std::min(B, kFusedB) + 15) / 16) * (nn_small(sh.H) + 1);
+}
+
+constexpr int kTileWaves = 8, kTileThreads = 64 * kTileWaves;
+
+template <int HT>  // 16-wide tiles of the hidden layer
+__global__ __launch_bounds__(kTileThreads) void k_nn_tile(NNTrain a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int HP = 16 * HT, HS = HP + 1;
+  const int W = a.W, H = a.H, W16 = (W + 15) / 16 * 16, XS = W16 + 4;
+  float* X = reinterpret_cast<float*>(smem_raw);   // [16][XS], zero beyond W
+  float* zp = X + 16 * XS;                          // [kTileWaves][16][HS] partial products of the wavefronts
+  float* h1 = zp + kTileWaves * 16 * HS;                     // [16][HS] each
+  float* h2 = h1 + 16 * HS;
+  float* d2 = h2 + 16 * HS;
+  float* d1 = d2 + 16 * HS;
+  float* sk = d1 + 16 * HS;                         // [16] skip, then dy
+  float* rr = sk + 16;                              // [16] squared residuals
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b0 = blockIdx.x * 16;
+  const float* W1 = a.theta;
+  const float* b1 = W1 + (long)H * W;
+  const float* W2 = b1 + H;
+  const float* b2 = W2 + (long)H * H;
+  const float* w3 = b2 + H;
+  const float* b3 = w3 + H;
+  const float* ws = b3 + 1;
+  // windows: 32 threads per sample
+  {
+    const int s = tid >> 5;
+    const int smp = b0 + s < a.B ? a.idx[b0 + s] : -1;
+    const int tr = smp / a.T, t = smp - tr * a.T, lo = t - W + 1;
+    const float* q = a.seqA + (long)tr * a.T + lo;
+    for (int w = tid & 31; w < W16; w += 32) {
+      float x = 0.0f;
+      if (smp >= 0 && w < W && lo + w >= 0) x = q[w];
+      X[s * XS + w] = x;
+    }
+  }
+  __syncthreads();
+  // z1 = X W1^T: each wavefront a contiguous share of the groups of 16 window
+  // points; within a group lane (r, q) holds points 4 q .. 4 q + 3. The
+  // weights of kAhead groups are loaded before their products.
+  const int r = lane & 15, q = lane >> 4;
+  const int groups = W16 / 16, per = (groups + kTileWaves - 1) / kTileWaves;
+  const int g0 = wave * per, g1 = min(groups, g0 + per);
+  constexpr int kAhead = HT <= 2 ? 4 : 2;
+  f32x4 acc[HT];
+#pragma unroll
+  for (int h = 0; h < HT; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int gc = g0; gc < g1; gc += kAhead) {
+    f32x4 wv[kAhead][HT];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int w0 = 16 * (gc + u) + 4 * q;
+#pragma unroll
+      for (int h = 0; h < HT; ++h) {
+        const float* src = W1 + (long)min(16 * h + r, H - 1) * W;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wv[u][h][e] = src[min(w0 + e, W - 1)];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (gc + u >= g1) break;  // uniform over the wavefront
+      const int w0 = 16 * (gc + u) + 4 * q;
+      const f32x4 xv = *reinterpret_cast<const f32x4*>(X + r * XS + w0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+          const float w = 16 * h + r < H && w0 + e < W ? wv[u][h][e] : 0.0f;
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[e], w, acc[h], 0, 0, 0);
+        }
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < HT; ++h)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) zp[(wave * 16 + 4 * q + e) * HS + 16 * h + r] = acc[h][e];
+  // the linear skip, two samples per wavefront
+  {
+    float t0 = 0.0f, t1 = 0.0f;
+    const float* x0 = X + 2 * wave * XS;
+    for (int w = lane; w < W; w += 64) {
+      const float v = ws[w];
+      t0 = fmaf(x0[w], v, t0);
+      t1 = fmaf(x0[XS + w], v, t1);
+    }
+    t0 = wave_sum_f(t0);
+    t1 = wave_sum_f(t1);
+    if (lane == 0) {
+      sk[2 * wave] = t0;
+      sk[2 * wave + 1] = t1;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < 16 * H; i += kTileThreads) {
+    const int s = i / H, h = i - s * H;
+    float z = zp[s * HS + h];
+    for (int wv = 1; wv < kTileWaves; ++wv) z += zp[(wv * 16 + s) * HS + h];
+    h1[s * HS + h] = tanhf(z + b1[h]);
+  }
+  __syncthreads();
+  for (int i = tid; i < 16 * H; i += kTileThreads) {
+    const int s = i / H, h = i - s * H;
+    float z = 0.0f;
+    for (int k = 0; k < H; ++k) z = fmaf(h1[s * HS + k], W2[(long)h * H + k], z);
+    h2[s * HS + h] = tanhf(z + b2[h]);
+  }
+  __syncthreads();
+  if (tid < 256) {
+    // y, dy and the residual: sixteen lanes per sample
+    const int s = tid >> 4, l = tid & 15;
+    float y = 0.0f;
+    for (int h = l; h < H; h += 16) y = fmaf(h2[s * HS + h], w3[h], y);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) y += __shfl_xor(y, o, 16);
+    if (l == 0) {
+      float res = 0.0f;
+      if (b0 + s < a.B) res = y + b3[0] + sk[s] - a.seqJ[a.idx[b0 + s]];
+      const float dy = 2.0f * res / (float)a.B;
+      rr[s] = res * res;
+      sk[s] = dy;
+      if (b0 + s < a.B) a.dy[b0 + s] = dy;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < 16 * H; i += kTileThreads) {
+    const int s = i / H, h = i - s * H;
+    const float v = h2[s * HS + h];
+    d2[s * HS + h] = sk[s] * w3[h] * (1.0f - v * v);
+  }
+  __syncthreads();
+  for (int i = tid; i < 16 * H; i += kTileThreads) {
+    const int s = i / H, k = i - s * H;
+    float z = 0.0f;
+    for (int h = 0; h < H; ++h) z = fmaf(d2[s * HS + h], W2[(long)h * H + k], z);
+    const float v = h1[s * HS + k];
+    z *= 1.0f - v * v;
+    d1[s * HS + k] = z;
+    if (b0 + s < a.B) a.dz1[(long)(b0 + s) * H + k] = z;
+  }
+  __syncthreads();
+  // the tile's sums for b1, W2, b2, w3, b3 and the loss (samples in order)
+  const int ns = (int)nn_small(H);
+  float* out = a.part + (long)blockIdx.x * (ns + 1);
+  for (int i = tid; i <= ns; i += kTileThreads) {
+    float z = 0.0f;
+    if (i < H) {
+      for (int s = 0; s < 16; ++s) z += d1[s * HS + i];
+    } else if (i < H + H * H) {
+      const int h = (i - H) / H, k = (i - H) - h * H;
+      for (int s = 0; s < 16; ++s) z = fmaf(d2[s * HS + h], h1[s * HS + k], z);
+    } else if (i < 2 * H + H * H) {
+      for (int s = 0; s < 16; ++s) z += d2[s * HS + i - H - H * H];
+    } else if (i < 3 * H + H * H) {
+      for (int s = 0; s < 16; ++s) z = fmaf(sk[s], h2[s * HS + i - 2 * H - H * H], z);
+    } else if (i == ns - 1) {
+      for (int s = 0; s < 16; ++s) z += sk[s];
+    } else {
+      for (int s = 0; s < 16; ++s) z += rr[s];
+    }
+    out[i] = z;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_nn_update(NNTrain a, NNAdam o, int w_tiles, int h_tiles) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ float zp[4][16][17];
+  const int W = a.W, H = a.H, B = a.B, tid = threadIdx.x;
+  const long oW1 = 0, oSmall = (long)H * W, ns = nn_small(H), oWs = oSmall + ns;
+  const int blk = blockIdx.x;
+  if (blk >= w_tiles * h_tiles) {
+    // small parameters, one per thread: the tiles' sums in order
+    const long i = (long)(blk - w_tiles * h_tiles) * 256 + tid;
+    if (i > ns) return;
+    const int tiles = (B + 15) / 16;
+    float g = 0.0f;
+    for (int t = 0; t < tiles; ++t) g += a.part[(long)t * (ns + 1) + i];
+    if (i == ns) {
+      a.loss[0] += g / (float)B;
+      return;
+    }
+    if (i == ns - 1 && a.freeze) g = 0.0f;
+    a.grad[oSmall + i] = g;
+    adam_one(a.theta, a.m, a.v, oSmall + i, g, o);
+    return;
+  }
+  int* start = reinterpret_cast<int*>(smem_raw);   // [B] first window point in seqA
+  int* skip = start + B;                            // [B] window points before the trajectory's start
+  for (int b = tid; b < B; b += 256) {
+    const int smp = a.idx[b], tr = smp / a.T, t = smp - tr * a.T;
+    start[b] = smp - W + 1;
+    skip[b] = W - 1 - t;
+  }
+  __syncthreads();
+  const int lane = tid & 63, wave = tid >> 6, r = lane & 15, q = lane >> 4;
+  const int w0 = (blk % w_tiles) * 16, h0 = (blk / w_tiles) * 16;
+  const int w = w0 + r, h = h0 + r;
+  const int steps = (B + 3) / 4, per = (steps + 3) / 4;
+  const int s0 = wave * per, s1 = min(steps, s0 + per);
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int kChunk = 8;
+  for (int c0 = s0; c0 < s1; c0 += kChunk) {
+    float av[kChunk], bv[kChunk];
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const int b = 4 * (c0 + u) + q, bc = min(b, B - 1);
+      const bool in = c0 + u < s1 && b < B;
+      const bool xin = in && w < W && w >= skip[bc];
+      const float dv = a.dz1[(long)bc * H + min(h, H - 1)];
+      const float xv = a.seqA[xin ? start[bc] + w : 0];
+      av[u] = in && h < H ? dv : 0.0f;
+      bv[u] = xin ? xv : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) zp[wave][4 * q + e][r] = acc[e];
+  __syncthreads();
+  {
+    const int i = tid >> 4, j = tid & 15;
+    if (h0 + i < H && w0 + j < W) {
+      const float g = zp[0][i][j] + zp[1][i][j] + zp[2][i][j] + zp[3][i][j];
+      const long at = oW1 + (long)(h0 + i) * W + w0 + j;
+      a.grad[at] = g;
+      adam_one(a.theta, a.m, a.v, at, g, o);
+    }
+  }
+  if (h0 > 0) return;
+  // the skip weights of these window points: sixteen slices of the batch
+  __syncthreads();
+  float g = 0.0f;
+  const int j = tid & 15, sl = tid >> 4, wj = w0 + j;
+  if (!a.freeze && wj < W)
+    for (int b = sl; b < B; b += 16)
+      if (wj >= skip[b]) g = fmaf(a.dy[b], a.seqA[start[b] + wj], g);
+  zp[0][sl][j] = g;
+  __syncthreads();
+  if (sl == 0 && wj < W) {
+    for (int i = 1; i < 16; ++i) g += zp[0][i][j];
+    a.grad[oWs + wj] = g;
+    adam_one(a.theta, a.m, a.v, oWs + wj, g, o);
+  }
+}
+
 // ---------------------------------------------------------------- launchers
 static hipError_t gemm(const float* A, long sai, long sak, const float* B, long sbk, long sbj, float* C, int M,
                        int N, int K, const float* bias, int act, const float* aux, hipStream_t s) {
@@ -191,9 +485,11 @@ __global__ void k_zero_f(float* __restrict__ p, long n) {
 }
 
 // G[i][i] += lambda_rel * trace(G) / n (one workgroup, fixed-order sum)
-__global__ __launch_bounds__(1024) void k_lin_trace_scale(double* __restrict__ G, int n, double lambda_rel) {
+__global__ __launch_bounds__(1024) void k_lin_trace_scale(double* __restrict__ G, int n, double lambda_rel,
+                                                          int* __restrict__ ok) {
   __shared__ double red[1024];
   const int t = threadIdx.x;
+  if (t == 0) *ok = 1;
   double s = 0.0;
   for (int i = t; i < n; i += 1024) s += G[(size_t)i * n + i];
   red[t] = s;
@@ -211,127 +507,236 @@ __global__ __launch_bounds__(1024) void k_lin_trace_scale(double* __restrict__ G
 // Least-squares fit of the linear part (skip weights and output bias) over a
 // set of trajectories, FP64. With the regressors x = (window of A, 1), n = W + 1:
 //   G[i][j] = sum over samples of x_i x_j,  b[i] = sum x_i y,
-// then (G + lambda I) w = b by a Cholesky factorisation in one workgroup.
+// then (G + lambda I) w = b by a Cholesky factorisation.
 // Window entry i of the sample at time t of a trajectory is A(t - W + 1 + i),
-// zero before t = 0; the sums run over trajectories and times in order.
+// zero before t = 0.
 
-__device__ __forceinline__ double lin_x(const double* __restrict__ a, int T, int W, int t, int i) {
-  if (i == W) return 1.0;
-  const int tt = t - W + 1 + i;
-  return tt >= 0 ? a[tt] : 0.0;
-}
-
-// one thread per (i, j >= i) pair of G, and one per entry of b (j = n)
-__global__ void k_lin_gram(const double* __restrict__ A, const double* __restrict__ Y, int n_traj, int T, int W,
-                           double* __restrict__ G, double* __restrict__ b) {
-  const int n = W + 1;
-  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long pairs = (long)n * (n + 1) / 2;
-  if (id >= pairs + n) return;
-  int i, j;
-  bool rhs = id >= pairs;
-  if (rhs) {
-    i = (int)(id - pairs);
-    j = -1;
-  } else {
-    // id -> (i, j) with 0 <= i <= j < n, row by row
-    long r = id;
-    i = 0;
-    while (r >= n - i) {
-      r -= n - i;
-      ++i;
-    }
-    j = i + (int)r;
-  }
-  double acc = 0.0;
-  for (int k = 0; k < n_traj; ++k) {
-    const double* a = A + (size_t)k * T;
-    const double* y = Y + (size_t)k * T;
-    for (int t = 0; t < T; ++t) {
-      const double xi = lin_x(a, T, W, t, i);
-      acc += xi * (rhs ? y[t] : lin_x(a, T, W, t, j));
-    }
-  }
-  if (rhs) {
-    b[i] = acc;
-  } else {
-    G[(size_t)i * n + j] = acc;
-    G[(size_t)j * n + i] = acc;
-  }
-}
-
-// Solve (G + lambda I) w = b in place (G n x n, row-major): right-looking
-// Cholesky G = L L^T (L in the lower triangle), then L z = b, L^T w = z.
-// One workgroup; *ok = 0 if a pivot is not positive.
-__global__ __launch_bounds__(1024) void k_lin_solve(double* __restrict__ G, double* __restrict__ b, int n,
-                                                    double lambda, float* __restrict__ ws, float* __restrict__ b3,
-                                                    int* __restrict__ ok) {
-  __shared__ double piv;
-  __shared__ int good;
-  const int t = threadIdx.x, nt = blockDim.x;
-  if (t == 0) good = 1;
-  for (int i = t; i < n; i += nt) G[(size_t)i * n + i] += lambda;
-  __syncthreads();
-  for (int j = 0; j < n; ++j) {
-    if (t == 0) {
-      const double d = G[(size_t)j * n + j];
-      if (!(d > 0.0)) good = 0;
-      piv = d > 0.0 ? sqrt(d) : 1.0;
-      G[(size_t)j * n + j] = piv;
-    }
-    __syncthreads();
-    for (int i = j + 1 + t; i < n; i += nt) G[(size_t)i * n + j] /= piv;
-    __syncthreads();
-    // trailing update of the lower triangle: G[i][k] -= L[i][j] L[k][j], j < k <= i
-    const int m = n - j - 1;
-    const long cnt = (long)m * (m + 1) / 2;
-    for (long q = t; q < cnt; q += nt) {
-      // q -> (ii, kk) with 0 <= kk <= ii < m
-      const int ii = (int)((sqrt(8.0 * (double)q + 1.0) - 1.0) * 0.5);
-      int i2 = ii;
-      long base = (long)i2 * (i2 + 1) / 2;
-      if (base > q) {
-        --i2;
-        base = (long)i2 * (i2 + 1) / 2;
-      } else if (base + i2 + 1 <= q) {
-        ++i2;
-        base = (long)i2 * (i2 + 1) / 2;
+// The windows of a trajectory are shifts of one series, so the matrix is summed
+// along its diagonals: with d = j - i and a(s) the series,
+//   G[i][i + d] = sum over trajectories of sum_{s = 0}^{T - W + i} a(s) a(s + d),
+// a running sum over s per lag d (W T products per trajectory; pair by pair it
+// is W^2 T / 2 of them, 2.4 ms for W = 512 and 13200 samples). One workgroup
+// per lag; d = W: the column of the constant, with a(s) alone. Only the lower
+// triangle G[i + d][i] is written; row n of G is the right-hand side.
+__global__ __launch_bounds__(256) void k_lin_lags(const double* __restrict__ A, int n_traj, int T, int W,
+                                                  double* __restrict__ G) {
+  __shared__ double sc[256];
+  const int n = W + 1, d = blockIdx.x, tid = threadIdx.x;
+  const bool one = d == W;
+  const int cnt = one ? W : W - d;      // entries i = 0 .. cnt - 1
+  const int shift = T - W;              // entry i is the running sum at s = shift + i
+  auto put = [&](int i, double v) { G[one ? (size_t)W * n + i : (size_t)(i + d) * n + i] = v; };
+  for (int i = tid; i < min(cnt, -shift); i += 256) put(i, 0.0);  // windows that never reach the series
+  double carry = 0.0;
+  const int smax = shift + cnt - 1;     // <= T - 1 - d
+  for (int s0 = 0; s0 <= smax; s0 += 256) {
+    const int s = s0 + tid;
+    double c = 0.0;
+    if (s <= smax)
+      for (int k = 0; k < n_traj; ++k) {
+        const double* a = A + (size_t)k * T;
+        c += one ? a[s] : a[s] * a[s + d];
       }
-      const int kk = (int)(q - base);
-      const int row = j + 1 + i2, col = j + 1 + kk;
-      G[(size_t)row * n + col] -= G[(size_t)row * n + j] * G[(size_t)col * n + j];
+    sc[tid] = c;
+    __syncthreads();
+    for (int h = 1; h < 256; h <<= 1) {
+      const double v = tid >= h ? sc[tid - h] : 0.0;
+      __syncthreads();
+      sc[tid] += v;
+      __syncthreads();
+    }
+    if (s <= smax && s >= shift) put(s - shift, carry + sc[tid]);
+    carry += sc[255];
+    __syncthreads();
+  }
+  if (one && tid == 0) G[(size_t)W * n + W] = (double)n_traj * T;
+}
+
+// the right-hand side b[i] = sum x_i y (row n of G): one workgroup per entry,
+// thread t sums samples t, t + 256, ... in order, then a fixed pairwise tree
+__global__ __launch_bounds__(256) void k_lin_rhs(const double* __restrict__ A, const double* __restrict__ Y,
+                                                 int n_traj, int T, int W, double* __restrict__ G) {
+  __shared__ double red[256];
+  const int n = W + 1, i = blockIdx.x, tid = threadIdx.x;
+  const int t0 = i == W ? 0 : max(0, W - 1 - i);  // first sample whose window entry i is inside
+  double acc = 0.0;
+  for (int k = 0; k < n_traj; ++k)
+    for (int t = t0 + tid; t < T; t += 256) {
+      const double y = Y[(size_t)k * T + t];
+      acc += i == W ? y : y * A[(size_t)k * T + t - W + 1 + i];
+    }
+  red[tid] = acc;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (tid < h) red[tid] += red[tid + h];
+    __syncthreads();
+  }
+  if (tid == 0) G[(size_t)n * n + i] = red[0];
+}
+
+// Cholesky G = L L^T by panels of kPanel columns, rows 0 .. n (the last is the
+// right-hand side, whose row of L is the forward substitution's result), then
+// the back substitution. In one workgroup, column by column, the 513 columns
+// of a 512-point window took 15.9 ms; by panels 0.55 ms (17 panels of 19 us,
+// 16 updates of 6 us and the back substitution 0.13 ms, all latency).
+constexpr int kPanel = 32;
+
+__device__ __forceinline__ double lane_read(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// The panel at column j: every workgroup factors the diagonal block (kept in
+// Ld, so that G's is not overwritten while others read it) and solves 64 rows
+// below it. *ok = 0 if a pivot is not positive.
+__global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ G, double* __restrict__ Ld, int n, int j,
+                                                   int* __restrict__ ok) {
+  __shared__ double D[kPanel][kPanel + 1];
+  const int lane = threadIdx.x, nb = min(kPanel, n - j);
+  for (int i = lane; i < kPanel * kPanel; i += 64) {
+    const int r = i / kPanel, c = i % kPanel;
+    D[r][c] = r < nb && c <= r ? G[(size_t)(j + r) * n + j + c] : (r == c ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  // the block's row lane & 31 in registers; the values of other rows come by
+  // lane reads
+  const int r = lane & 31;
+  double a[kPanel];
+#pragma unroll
+  for (int c = 0; c < kPanel; ++c) a[c] = D[r][c];
+  bool good = true;
+#pragma unroll
+  for (int c = 0; c < kPanel; ++c) {
+    double d = lane_read(a[c], c);
+    if (!(d > 0.0)) {
+      good = false;
+      d = 1.0;
+    }
+    const double piv = sqrt(d);
+    a[c] = r == c ? piv : a[c] / piv;
+#pragma unroll
+    for (int k = c + 1; k < kPanel; ++k) a[k] -= a[c] * lane_read(a[c], k);  // of use where k <= r
+  }
+  if (!good && blockIdx.x == 0 && lane == 0) *ok = 0;
+  __syncthreads();
+  if (lane < kPanel) {
+#pragma unroll
+    for (int c = 0; c < kPanel; ++c) D[r][c] = c <= r ? a[c] : 0.0;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0)
+    for (int i = lane; i < kPanel * kPanel; i += 64)
+      Ld[(size_t)(j / kPanel) * kPanel * kPanel + i] = D[i / kPanel][i % kPanel];
+  const int row = j + kPanel + blockIdx.x * 64 + lane;
+  if (nb < kPanel) {
+    // the last panel: only the right-hand side (row n) is left below it
+    if (blockIdx.x > 0 || lane > 0) return;
+    for (int c = 0; c < nb; ++c) {
+      double x = G[(size_t)n * n + j + c];
+      for (int k = 0; k < c; ++k) x -= G[(size_t)n * n + j + k] * D[c][k];
+      G[(size_t)n * n + j + c] = x / D[c][c];
+    }
+    return;
+  }
+  if (row > n) return;
+  double x[kPanel];
+#pragma unroll
+  for (int c = 0; c < kPanel; ++c) x[c] = G[(size_t)row * n + j + c];
+#pragma unroll
+  for (int c = 0; c < kPanel; ++c) {
+#pragma unroll
+    for (int k = 0; k < c; ++k) x[c] -= x[k] * D[c][k];
+    x[c] /= D[c][c];
+  }
+#pragma unroll
+  for (int c = 0; c < kPanel; ++c) G[(size_t)row * n + j + c] = x[c];
+}
+
+// G[r][c] -= sum_k L[r][j + k] L[c][j + k] for the 32 x 32 tile (blockIdx.y,
+// blockIdx.x) below and right of the panel at j (lower tiles only)
+__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ G, int n, int j) {
+  if (blockIdx.x > blockIdx.y) return;
+  __shared__ double R[32][kPanel + 1], C[32][kPanel + 1];
+  const int r0 = j + kPanel + blockIdx.y * 32, c0 = j + kPanel + blockIdx.x * 32, tid = threadIdx.x;
+  for (int i = tid; i < 32 * kPanel; i += 256) {
+    const int a = i / kPanel, k = i % kPanel;
+    R[a][k] = r0 + a <= n ? G[(size_t)(r0 + a) * n + j + k] : 0.0;
+    C[a][k] = c0 + a < n ? G[(size_t)(c0 + a) * n + j + k] : 0.0;
+  }
+  __syncthreads();
+  const int c = tid & 31;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int a = (tid >> 5) + 8 * u;
+    double acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPanel; ++k) acc += R[a][k] * C[c][k];
+    if (r0 + a <= n && c0 + c < n && c0 + c <= r0 + a) G[(size_t)(r0 + a) * n + c0 + c] -= acc;
+  }
+}
+
+// L^T w = z with z in row n of G (overwritten): blocks from the last, the
+// triangle by one wavefront, the rest by the workgroup
+__global__ __launch_bounds__(1024) void k_chol_back(double* __restrict__ G, const double* __restrict__ Ld, int n,
+                                                    float* __restrict__ ws, float* __restrict__ b3) {
+  __shared__ double w[kPanel];
+  double* z = G + (size_t)n * n;
+  const int tid = threadIdx.x;
+  for (int j = (n - 1) / kPanel * kPanel; j >= 0; j -= kPanel) {
+    const int nb = min(kPanel, n - j);
+    if (tid < 64) {
+      // lane k holds column k of the block (padded with the identity)
+      const double* D = Ld + (size_t)(j / kPanel) * kPanel * kPanel;
+      const int k = tid & 31;
+      double d[kPanel];
+#pragma unroll
+      for (int c = 0; c < kPanel; ++c) d[c] = D[c * kPanel + k];
+      double x = k < nb ? z[j + k] : 0.0;
+#pragma unroll
+      for (int c = kPanel - 1; c >= 0; --c) {
+        const double wc = lane_read(x, c) / lane_read(d[c], c);
+        if (k == c) x = wc;
+        if (k < c) x -= d[c] * wc;
+      }
+      if (tid < kPanel) w[tid] = x;
+      if (tid < nb) z[j + tid] = x;
+    }
+    __syncthreads();
+    for (int i = tid; i < j; i += 1024) {
+      double acc = z[i];
+#pragma unroll 16
+      for (int c = 0; c < kPanel; ++c)
+        if (c < nb) acc -= G[(size_t)(j + c) * n + i] * w[c];
+      z[i] = acc;
     }
     __syncthreads();
   }
-  // forward substitution L z = b (z in b), then back substitution L^T w = z
-  for (int j = 0; j < n; ++j) {
-    if (t == 0) b[j] /= G[(size_t)j * n + j];
-    __syncthreads();
-    for (int i = j + 1 + t; i < n; i += nt) b[i] -= G[(size_t)i * n + j] * b[j];
-    __syncthreads();
-  }
-  for (int j = n - 1; j >= 0; --j) {
-    if (t == 0) b[j] /= G[(size_t)j * n + j];
-    __syncthreads();
-    for (int i = t; i < j; i += nt) b[i] -= G[(size_t)j * n + i] * b[j];
-    __syncthreads();
-  }
-  for (int i = t; i < n - 1; i += nt) ws[i] = (float)b[i];
-  if (t == 0) {
-    *b3 = (float)b[n - 1];
-    *ok = good;
-  }
+  for (int i = tid; i < n - 1; i += 1024) ws[i] = (float)z[i];
+  if (tid == 0) *b3 = (float)z[n - 1];
+}
+
+size_t nn_fit_doubles(int W) {
+  const size_t n = (size_t)W + 1;
+  return (n + 1) * n + (n + kPanel - 1) / kPanel * kPanel * kPanel;
 }
 
 hipError_t nn_fit_linear(const double* A, const double* Y, int n_traj, int T, int W, double lambda_rel, double* G,
-                         double* b, float* ws, float* b3, int* ok, hipStream_t s) {
+                         float* ws, float* b3, int* ok, hipStream_t s) {
   const int n = W + 1;
-  const long work = (long)n * (n + 1) / 2 + n;
-  hipLaunchKernelGGL(k_lin_gram, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, A, Y, n_traj, T, W, G, b);
-  // lambda relative to the mean diagonal of G, added by the solve kernel
-  // (which reads the diagonal first)
-  hipLaunchKernelGGL(k_lin_trace_scale, dim3(1), dim3(1024), 0, s, G, n, lambda_rel);
-  hipLaunchKernelGGL(k_lin_solve, dim3(1), dim3(1024), 0, s, G, b, n, 0.0, ws, b3, ok);
+  double* Ld = G + (size_t)(n + 1) * n;
+  hipLaunchKernelGGL(k_lin_lags, dim3((unsigned)n), dim3(256), 0, s, A, n_traj, T, W, G);
+  hipLaunchKernelGGL(k_lin_rhs, dim3((unsigned)n), dim3(256), 0, s, A, Y, n_traj, T, W, G);
+  // lambda relative to the mean diagonal of G
+  hipLaunchKernelGGL(k_lin_trace_scale, dim3(1), dim3(1024), 0, s, G, n, lambda_rel, ok);
+  for (int j = 0; j < n; j += kPanel) {
+    const int below = n + 1 - j - kPanel;  // rows under the panel, the right-hand side among them
+    hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)max(1, (below + 63) / 64)), dim3(64), 0, s, G, Ld, n, j, ok);
+    if (below > 0) {
+      const unsigned tr = (unsigned)((below + 31) / 32), tc = (unsigned)((n - j - kPanel + 31) / 32);
+      if (tc > 0) hipLaunchKernelGGL(k_chol_update, dim3(tc, tr), dim3(256), 0, s, G, n, j);
+    }
+  }
+  hipLaunchKernelGGL(k_chol_back, dim3(1), dim3(1024), 0, s, G, Ld, n, ws, b3);
   return hipGetLastError();
 }
 
@@ -357,6 +762,11 @@ hipError_t nn_forward(const NNShape& sh, const float* theta, const float* X, int
   return hipGetLastError();
 }
 
+static void colsum(const float* M, const float* wgt, int B, int N, float* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((N + kSumCols - 1) / kSumCols)), dim3(kSumSlices * kSumCols), 0, s, M,
+                     wgt, B, N, out);
+}
+
 hipError_t nn_backward(const NNShape& sh, const float* theta, const float* X, const float* target, int B,
                        NNWork& wk, float* grad, hipStream_t s) {
   const int W = sh.W, H = sh.H;
@@ -372,27 +782,25 @@ hipError_t nn_backward(const NNShape& sh, const float* theta, const float* X, co
   hipError_t e;
   hipLaunchKernelGGL(k_nn_dy_loss, dim3(1), dim3(256), 0, s, wk.y, target, B, wk.dy, wk.loss);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((H + 63) / 64)), dim3(64), 0, s, wk.h2, wk.dy, B, H, gw3);
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(64), 0, s, wk.dy, nullptr, B, 1, gb3);
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((W + 63) / 64)), dim3(64), 0, s, X, wk.dy, B, W, gws);
+  colsum(wk.h2, wk.dy, B, H, gw3, s);
+  colsum(wk.dy, nullptr, B, 1, gb3, s);
+  colsum(X, wk.dy, B, W, gws, s);
   hipLaunchKernelGGL(k_nn_dz2, dim3((unsigned)(((long)B * H + 255) / 256)), dim3(256), 0, s, wk.dy, w3, wk.h2, B,
                      H, wk.dz2);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // gW2[h][k] = sum_b dz2[b][h] h1[b][k]: A(i=h, k=b) = dz2[b][h], B(k=b, j) = h1[b][j]
   if ((e = gemm(wk.dz2, 1, H, wk.h1, H, 1, gW2, H, H, B, nullptr, 0, nullptr, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((H + 63) / 64)), dim3(64), 0, s, wk.dz2, nullptr, B, H, gb2);
+  colsum(wk.dz2, nullptr, B, H, gb2, s);
   // dz1[b][k] = (sum_h dz2[b][h] W2[h][k]) (1 - h1[b][k]^2)
   if ((e = gemm(wk.dz2, H, 1, W2, H, 1, wk.dz1, B, H, H, nullptr, 0, wk.h1, s)) != hipSuccess) return e;
   // gW1[h][w] = sum_b dz1[b][h] X[b][w]
   if ((e = gemm(wk.dz1, 1, H, X, W, 1, gW1, H, W, B, nullptr, 0, nullptr, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((H + 63) / 64)), dim3(64), 0, s, wk.dz1, nullptr, B, H, gb1);
+  colsum(wk.dz1, nullptr, B, H, gb1, s);
   return hipGetLastError();
 }
 
-hipError_t nn_adam(float* theta, float* m, float* v, const float* g, long n, float lr, float b1, float b2,
-                   float eps, float c1, float c2, hipStream_t s) {
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, m, v, g, n, lr, b1, b2, eps,
-                     c1, c2);
+hipError_t nn_adam(float* theta, float* m, float* v, const float* g, long n, const NNAdam& o, hipStream_t s) {
+  hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, m, v, g, n, o);
   return hipGetLastError();
 }
 
@@ -406,6 +814,28 @@ hipError_t nn_gather(const float* seqA, const float* seqJ, int T, int W, const i
 
 hipError_t nn_accumulate(const float* src, float* dst, hipStream_t s) {
   hipLaunchKernelGGL(k_accum, dim3(1), dim3(64), 0, s, src, dst);
+  return hipGetLastError();
+}
+
+hipError_t nn_train_step(const NNShape& sh, float* theta, float* m, float* v, float* grad, const float* seqA,
+                         const float* seqJ, int T, const int* idx, int B, NNWork& wk, const NNAdam& o, int freeze,
+                         float* loss, hipStream_t s) {
+  if (!nn_fused(sh, B) || B < 1) return hipErrorInvalidValue;
+  const NNTrain a{seqA, seqJ, idx, T, B, sh.W, sh.H, theta, m, v, grad, wk.dz1, wk.dy, wk.part, loss, freeze};
+  const int HT = (sh.H + 15) / 16, HS = 16 * HT + 1, XS = (sh.W + 15) / 16 * 16 + 4;
+  const size_t lds = ((size_t)16 * XS + (kTileWaves + 4) * 16 * HS + 32) * sizeof(float);
+  const dim3 grid((unsigned)((B + 15) / 16));
+  switch (HT) {
+    case 1: hipLaunchKernelGGL(k_nn_tile<1>, grid, dim3(kTileThreads), lds, s, a); break;
+    case 2: hipLaunchKernelGGL(k_nn_tile<2>, grid, dim3(kTileThreads), lds, s, a); break;
+    case 3: hipLaunchKernelGGL(k_nn_tile<3>, grid, dim3(kTileThreads), lds, s, a); break;
+    default: hipLaunchKernelGGL(k_nn_tile<4>, grid, dim3(kTileThreads), lds, s, a); break;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int wt = (sh.W + 15) / 16, sm = (int)((nn_small(sh.H) + 1 + 255) / 256);
+  hipLaunchKernelGGL(k_nn_update, dim3((unsigned)(wt * HT + sm)), dim3(256), (size_t)2 * B * sizeof(int), s, a, o, wt,
+                     HT);
   return hipGetLastError();
 }
 
