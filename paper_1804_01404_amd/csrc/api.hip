@@ -96,6 +96,7 @@ struct tddft_ctx {
   double* coef = nullptr;  // [n_k][kCoef] in the stage precision (fused step)
   double2* phkA = nullptr;  // [n_k][S] combined projector phases of the step (fused step)
   double2* gram = nullptr;  // [2][n_k][n_orb][n_orb] overlap and its inverse factor (ground state)
+  double* gram_part = nullptr;  // the overlaps' partial sums
   int* chol_bad = nullptr;  // set by the device Cholesky when a pivot is not positive
   void* Wsave = nullptr;    // predictor-corrector: the orbitals at t_n
   void* Wref = nullptr;     // reference (ground-state) orbitals for the excited-pair count
@@ -1050,19 +1051,22 @@ tddft_status orthonormalise(tddft_ctx* c) {
   const int n = c->cfg.n_orb, nk = c->cfg.n_k, N = (int)c->N;
   double2* dS = c->gram;
   double2* dM = dS + (size_t)nk * n * n;
-  for (int pass = 0; pass < 2; ++pass) {
-    LAUNCH(launch_gram<T>(as2<T>(c->W), n, nk, N, c->dV, dS, c->stream), "gram");
-    LAUNCH(launch_chol_inverse(dS, dM, n, nk, c->chol_bad, c->stream), "cholesky inverse");
-    LAUNCH(launch_apply_lower<T>(as2<T>(c->W), dM, n, nk, N, as2<T>(c->U0), c->stream), "apply L^-1");
-    HIP_TRY(hipMemcpyAsync(c->W, c->U0, c->n_orb_tot * c->N * sizeof(typename Vec2<T>::type),
-                           hipMemcpyDeviceToDevice, c->stream));
-  }
+  for (int pass = 0; pass < 2; ++pass)
+    LAUNCH(launch_orthonormalise<T>(as2<T>(c->W), n, nk, N, c->dV, c->gram_part, dS, dM, c->chol_bad, c->stream),
+           "orthonormalise");
   return TDDFT_OK;
 }
 
 template <typename T>
 tddft_status ground_state_iteration(tddft_ctx* c, double tau) {
-  tddft_status st = enqueue_taylor_stages<T>(c, 0.0, tau);
+  tddft_status st = TDDFT_OK;
+  if (c->fused) {
+    FusedArgs<T> f = fused_args<T>(c);
+    f.dt = tau;
+    LAUNCH(launch_fused<T>(f, c->stream, true), "imaginary-time step");
+  } else {
+    st = enqueue_taylor_stages<T>(c, 0.0, tau);
+  }
   if (st != TDDFT_OK) return st;
   st = orthonormalise<T>(c);
   if (st != TDDFT_OK) return st;
@@ -1699,6 +1703,7 @@ tddft_status tddft_ground_state(tddft_ctx* c, int32_t n_iter, double tau, double
   if (!c->gram) {
     tddft_status st = dalloc_t(c, (size_t)2 * c->cfg.n_k * n * n, &c->gram);
     if (st != TDDFT_OK) return st;
+    if ((st = dalloc_t(c, gram_part_doubles(n, c->cfg.n_k, (int)c->N), &c->gram_part)) != TDDFT_OK) return st;
     if ((st = dalloc_t(c, 1, &c->chol_bad)) != TDDFT_OK) return st;
   }
   LAUNCH(launch_set_int(c->chol_bad, 0, c->stream), "flag reset");

@@ -187,8 +187,10 @@ template <typename T>
 hipError_t launch_observe(int bc, const ObserveArgs<T>& a, hipStream_t s);
 template <typename T>
 hipError_t launch_project(const ProjArgs<T>& a, hipStream_t s);
+// the four-stage update of every orbital; imaginary: w <- sum_m (-dt h)^m / m! w
+// without observables
 template <typename T>
-hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s);
+hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s, bool imaginary = false);
 bool fused_supported(const Geometry& g, int n_atoms, size_t elem);
 size_t fused_lds_bytes(const Geometry& g, int n_atoms, size_t elem);
 int fused_rows(int n, size_t elem);  // z points of a thread's tile
@@ -336,16 +338,14 @@ template <typename T>
 hipError_t launch_kick(typename Vec2<T>::type* w, Geometry g, double F0, int axis, size_t n_orb_tot,
                        hipStream_t s);
 hipError_t launch_set_int(int* p, int v, hipStream_t s);
+// Cholesky-QR of every k-point's orbitals, in place; part: gram_part_doubles
+size_t gram_part_doubles(int n_orb, int n_k, int N);
 template <typename T>
-hipError_t launch_gram(const typename Vec2<T>::type* w, int n_orb, int n_k, int N, double dV, double2* S,
-                       hipStream_t s);
+hipError_t launch_orthonormalise(typename Vec2<T>::type* w, int n_orb, int n_k, int N, double dV, double* part,
+                                 double2* S, double2* Mt, int* bad, hipStream_t s);
 template <typename T>
 hipError_t launch_overlap_weight(const typename Vec2<T>::type* ref, const typename Vec2<T>::type* w, int n_orb,
                                  int n_k, int N, double dV, double* Sk, hipStream_t s);
-template <typename T>
-hipError_t launch_apply_lower(const typename Vec2<T>::type* w, const double2* M, int n_orb, int n_k, int N,
-                              typename Vec2<T>::type* out, hipStream_t s);
-hipError_t launch_chol_inverse(double2* S, double2* M, int n, int n_k, int* bad, hipStream_t s);
 hipError_t launch_real_part(const double2* src, double* dst, size_t n, hipStream_t s);
 hipError_t launch_fill(double* p, double v, size_t n, hipStream_t s);
 hipError_t launch_copy8(const void* src, void* dst, size_t bytes, hipStream_t s);

@@ -364,7 +364,7 @@ __device__ __forceinline__ void add_x_pair(Quad<T>& t, T c, T b, const Quad<T>& 
 // (complex128, 64 k) when a thread owned a whole column of points read one by
 // one with the last wavefronts idle; now 1.21 and 0.32 ms; 16^3 x 64 k 0.136 ->
 // 0.122 and 0.290 -> 0.183 ms, 24^3 x 27 k (FP32) 0.229 -> 0.144 ms.
-template <typename T, int N, int ZR, bool PERIODIC>
+template <typename T, int N, int ZR, bool PERIODIC, bool IMAG>
 __device__ __forceinline__ void stencil_tile(const LdsOrb<T, N> u, gp<const T> V, cp<T> row, const FieldE<T>& fe,
                                              const TileAt<ZR>& at, gp<const typename Vec2<T>::type> wg,
                                              Quad<T> (&un)[ZR], T tau) {
@@ -446,8 +446,13 @@ __device__ __forceinline__ void stencil_tile(const LdsOrb<T, N> u, gp<const T> V
     if (!PERIODIC) dg += (V4)(fe.ext + fe.ez * (T)r) + V4{T(0), fe.ex, 2 * fe.ex, 3 * fe.ex};
     const V4 hr = __builtin_elementwise_fma(dg, c.re, un[r].re + t.re);
     const V4 hi = __builtin_elementwise_fma(dg, c.im, un[r].im + t.im);
-    un[r].re = fma4(tau, hi, w.re);
-    un[r].im = fma4(-tau, hr, w.im);
+    if (IMAG) {  // u_{s-1} = w - tau h u_s
+      un[r].re = fma4(-tau, hr, w.re);
+      un[r].im = fma4(-tau, hi, w.im);
+    } else {
+      un[r].re = fma4(tau, hi, w.re);
+      un[r].im = fma4(-tau, hr, w.im);
+    }
     // one row at a time: bounds the loads in flight and so the registers
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -517,8 +522,9 @@ __device__ __forceinline__ void observe_tile(const LdsOrb<T, N> u, const T (&dw)
   }
 }
 
-// ITEMS: the body runs once per item of a loop (the persistent form)
-template <typename T, int N, int ZR, bool PERIODIC, bool ITEMS = false>
+// ITEMS: the body runs once per item of a loop (the persistent form); IMAG:
+// imaginary time (dt is the real step of exp(-dt h)), no observables
+template <typename T, int N, int ZR, bool PERIODIC, bool ITEMS = false, bool IMAG = false>
 __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, unsigned char* smem_raw) {
   using T2 = typename Vec2<T>::type;
   using V16 = typename Wide<T>::type;
@@ -617,7 +623,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
     const T tau = (T)(a.dt / s);
     Quad<T> un[ZR];
     const int own = tile_at<N, ZR>(tile).own;
-    if (active) stencil_tile<T, N, ZR, PERIODIC>(u, G(a.V), row, fe, tile_at<N, ZR>(opaque_i(tile)), wg, un, tau);
+    if (active) stencil_tile<T, N, ZR, PERIODIC, IMAG>(u, G(a.V), row, fe, tile_at<N, ZR>(opaque_i(tile)), wg, un, tau);
     __syncthreads();
     if (active) {
 #pragma unroll
@@ -654,7 +660,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
             }
             const double cr = pr * sr + pim * si, ci = pr * si - pim * sr;
             T* const pt = u.point(idx);
-            const T vx = pt[0] + (T)(taud * ci), vy = pt[LdsOrb<T, N>::kImag] - (T)(taud * cr);
+            const T vx = pt[0] + (T)(taud * (IMAG ? -cr : ci)), vy = pt[LdsOrb<T, N>::kImag] - (T)(taud * (IMAG ? ci : cr));
             pt[0] = vx;
             pt[LdsOrb<T, N>::kImag] = vy;
             const double gr = pr * (double)vx - pim * (double)vy;
@@ -697,7 +703,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
               }
               const double cr = pr * sr + pim * si, ci = pr * si - pim * sr;
               T* const pt = u.point(idx);
-              const T vx = pt[0] + (T)(taud * ci), vy = pt[LdsOrb<T, N>::kImag] - (T)(taud * cr);
+              const T vx = pt[0] + (T)(taud * (IMAG ? -cr : ci)), vy = pt[LdsOrb<T, N>::kImag] - (T)(taud * (IMAG ? ci : cr));
               pt[0] = vx;
               pt[LdsOrb<T, N>::kImag] = vy;
             }
@@ -717,9 +723,10 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, const int o, u
 #pragma unroll
       for (int r = 0; r < ZR; ++r)
         store_quad((gp<V16>)(wg + 4 * (at.own + r * plane)), u.get(at.own + r * plane, T(0)));
-      observe_tile<T, N, ZR, PERIODIC>(u, a.dhc, at, sv);
+      if (!IMAG) observe_tile<T, N, ZR, PERIODIC>(u, a.dhc, at, sv);
     }
   }
+  if (IMAG) return;
 #pragma unroll
   for (int i = 0; i < 4; ++i) sv[i] = wave_sum(i == 0 ? sv[0] : 2.0 * sv[i]);
   if (lane == 0) {
@@ -822,6 +829,16 @@ __global__ __launch_bounds__((FusedShape<T, N>::kThreads), (FusedShape<T, N>::kW
   fused_body<T, N, FusedShape<T, N>::kRows, PERIODIC>(a, blockIdx.x, smem_raw);
 }
 
+// the imaginary-time step of the ground-state preparation: as the per-stage
+// kernels (four stages of 23 us, projections of 17, the add-back) it was
+// 0.19 ms for 16^3 x 64 k in complex FP32, this is 0.10 ms
+template <typename T, int N, bool PERIODIC>
+__global__ __launch_bounds__((FusedShape<T, N>::kThreads), (FusedShape<T, N>::kWaves)) void k_fused_imaginary(
+    FusedArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  fused_body<T, N, FusedShape<T, N>::kRows, PERIODIC, false, true>(a, blockIdx.x, smem_raw);
+}
+
 // Persistent form for batches of cells with the same grid: a fixed grid of
 // workgroups pulls (cell, orbital) items from a device queue in the given
 // (largest-cell-first) order until the list is exhausted; every item is
@@ -869,34 +886,38 @@ bool fused_supported(const Geometry& g, int n_atoms, size_t elem) {
 }
 
 template <typename T, int N>
-static void launch_n(bool periodic, const FusedArgs<T>& a, size_t lds, hipStream_t s) {
+static void launch_n(bool periodic, bool imaginary, const FusedArgs<T>& a, size_t lds, hipStream_t s) {
   constexpr int threads = FusedShape<T, N>::kThreads;
   const dim3 grid((unsigned)((size_t)a.g.n_orb * a.g.n_k));
-  if (periodic)
+  if (periodic && !imaginary)
     hipLaunchKernelGGL((k_fused<T, N, true>), grid, dim3(threads), lds, s, a);
-  else
+  else if (!imaginary)
     hipLaunchKernelGGL((k_fused<T, N, false>), grid, dim3(threads), lds, s, a);
+  else if (periodic)
+    hipLaunchKernelGGL((k_fused_imaginary<T, N, true>), grid, dim3(threads), lds, s, a);
+  else
+    hipLaunchKernelGGL((k_fused_imaginary<T, N, false>), grid, dim3(threads), lds, s, a);
 }
 
 template <typename T>
-hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s) {
+hipError_t launch_fused(const FusedArgs<T>& a, hipStream_t s, bool imaginary) {
   using T2 = typename Vec2<T>::type;
   if (!fused_supported(a.g, a.nl.n_atoms, sizeof(T2))) return hipErrorInvalidValue;
   const size_t lds = fused_lds_bytes(a.g, a.nl.n_atoms, sizeof(T2));
   const bool per = a.g.periodic != 0;
   switch (a.g.n3) {
-    case 12: launch_n<T, 12>(per, a, lds, s); break;
-    case 16: launch_n<T, 16>(per, a, lds, s); break;
-    case 20: launch_n<T, 20>(per, a, lds, s); break;
+    case 12: launch_n<T, 12>(per, imaginary, a, lds, s); break;
+    case 16: launch_n<T, 16>(per, imaginary, a, lds, s); break;
+    case 20: launch_n<T, 20>(per, imaginary, a, lds, s); break;
     default:
-      if constexpr (sizeof(T) == 4) launch_n<T, 24>(per, a, lds, s);  // complex128 does not fit
+      if constexpr (sizeof(T) == 4) launch_n<T, 24>(per, imaginary, a, lds, s);  // complex128 does not fit
       break;
   }
   return hipGetLastError();
 }
 
-template hipError_t launch_fused<double>(const FusedArgs<double>&, hipStream_t);
-template hipError_t launch_fused<float>(const FusedArgs<float>&, hipStream_t);
+template hipError_t launch_fused<double>(const FusedArgs<double>&, hipStream_t, bool);
+template hipError_t launch_fused<float>(const FusedArgs<float>&, hipStream_t, bool);
 
 template <typename T, int N>
 static void launch_pers_n(bool periodic, const FusedArgs<T>* cells, const int2* items, int n_items,

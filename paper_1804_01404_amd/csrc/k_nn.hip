@@ -615,7 +615,12 @@ __global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ G, doubl
     const double piv = sqrt(d);
     a[c] = r == c ? piv : a[c] / piv;
 #pragma unroll
-    for (int k = c + 1; k < kPanel; ++k) a[k] -= a[c] * lane_read(a[c], k);  // of use where k <= r
+    for (int k = c + 1; k < kPanel; ++k) {
+      a[k] -= a[c] * lane_read(a[c], k);  // of use where k <= r
+      // keeps the lane reads (scalar registers) next to their use
+      if (k % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
   if (!good && blockIdx.x == 0 && lane == 0) *ok = 0;
   __syncthreads();
