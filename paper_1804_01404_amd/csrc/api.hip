@@ -339,7 +339,8 @@ tddft_status enqueue_density_potential(tddft_ctx* c, bool with_finish = false) {
   if (planes) {
     const int n1 = c->g.n1, n2 = c->g.n2, n3 = c->g.n3;
     LAUNCH(launch_poisson_forward(tail, n1, n2, n3, c->stream), "Poisson, forward planes");
-    LAUNCH(launch_fft_lines(c->fft, n1, n2, n3, 2, -1, c->stream, nullptr, 0, 0, 0, c->Kfft, n1, n2, n3, n3, 1),
+    LAUNCH(launch_fft_lines(c->fft, n1, n2, n3, 2, -1, c->stream, kKernel, nullptr, 0, 0, c->Kfft, n1 / 2 + 1, n2,
+                            n3, n3),
            "Poisson, z lines");
     if (mgga)
       LAUNCH(launch_mgga_potential(c->rho, c->tau, mgga_args(c), c->cfg.xc == TDDFT_XC_TB09, c->dV, c->volume,
@@ -354,21 +355,22 @@ tddft_status enqueue_density_potential(tddft_ctx* c, bool with_finish = false) {
     // rho fills the corner n1 x n2 x n3 of the M-box (all of it for a
     // periodic cell) and only that corner of the potential is read back, so
     // each pass transforms only the lines that hold data or are needed:
-    // forward x over y < n2, z < n3 (packing rho into the box), forward y
-    // over z < n3 (zero beyond y = n2), then along z the forward transform,
-    // the kernel K and the inverse in one pass, storing z < n3, inverse y over
-    // z < n3 storing y < n2, inverse x over y < n2, z < n3 storing x < n1
-    const int M1 = c->M[0], M2 = c->M[1], M3 = c->M[2];
+    // forward x over y < n2, z < n3 (packing rho into the box, storing
+    // kx <= M1 / 2: both ends are real), forward y over those kx and z < n3
+    // (zero beyond y = n2), then along z the forward transform, the kernel K
+    // and the inverse in one pass, storing z < n3, inverse y over z < n3
+    // storing y < n2, inverse x over y < n2, z < n3 storing x < n1
+    const int M1 = c->M[0], M2 = c->M[1], M3 = c->M[2], H1 = M1 / 2 + 1;
     const int n1 = c->g.n1, n2 = c->g.n2, n3 = c->g.n3;
-    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 0, -1, c->stream, c->rho, n1, n2, n3, nullptr, n2, n3, n1, M1, 0),
+    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 0, -1, c->stream, kRho, c->rho, n1, n2, nullptr, n2, n3, n1, H1),
            "fft x");
-    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 1, -1, c->stream, nullptr, 0, 0, 0, nullptr, M1, n3, n2, M2, 0),
+    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 1, -1, c->stream, kPlain, nullptr, 0, 0, nullptr, H1, n3, n2, M2),
            "fft y");
-    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 2, -1, c->stream, nullptr, 0, 0, 0, c->Kfft, M1, M2, n3, n3, 1),
+    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 2, -1, c->stream, kKernel, nullptr, 0, 0, c->Kfft, H1, M2, n3, n3),
            "fft z, kernel, inverse z");
-    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 1, +1, c->stream, nullptr, 0, 0, 0, nullptr, M1, n3, M2, n2, 0),
+    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 1, +1, c->stream, kPlain, nullptr, 0, 0, nullptr, H1, n3, M2, n2),
            "inverse fft y");
-    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 0, +1, c->stream, nullptr, 0, 0, 0, nullptr, n2, n3, M1, n1, 0),
+    LAUNCH(launch_fft_lines(c->fft, M1, M2, M3, 0, +1, c->stream, kConj, nullptr, 0, 0, nullptr, n2, n3, M1, n1),
            "inverse fft x");
   }
   if (mgga)
@@ -2012,18 +2014,19 @@ tddft_status enqueue_group_tail(tddft_batch* b, const BatchGroup& g, hipStream_t
   const int n1 = c0->g.n1, n2 = c0->g.n2, n3 = c0->g.n3;
   if (poisson_planes(c0->g.periodic, c0->cfg.hartree, n1, n2)) {
     BHIP(launch_poisson_forward_group(g.d_tail, nc, n1, n2, n3, s));
-    BHIP(launch_fft_lines_group(g.d_tail, nc, n1, n2, n3, 2, -1, 0, n1, n2, n3, 1, n1, n2, n3, n3, 1, s));
+    BHIP(launch_fft_lines_group(g.d_tail, nc, n1, n2, n3, 2, -1, kKernel, n1, n2, n1 / 2 + 1, n2, n3, n3, s));
     BHIP(launch_poisson_inverse_group(g.d_tail, nc, n1, n2, n3, c0->cfg.xc, s));
     return TDDFT_OK;
   }
   if (g.max_chunks > 1) BHIP(launch_rho_reduce_group(g.d_tail, nc, N, s));
   const int M1 = c0->M[0], M2 = c0->M[1], M3 = c0->M[2];
   if (c0->cfg.hartree) {
-    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 0, -1, 1, n1, n2, n3, 0, n2, n3, n1, M1, 0, s));
-    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 1, -1, 0, n1, n2, n3, 0, M1, n3, n2, M2, 0, s));
-    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 2, -1, 0, n1, n2, n3, 1, M1, M2, n3, n3, 1, s));
-    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 1, +1, 0, n1, n2, n3, 0, M1, n3, M2, n2, 0, s));
-    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 0, +1, 0, n1, n2, n3, 0, n2, n3, M1, n1, 0, s));
+    const int H1 = M1 / 2 + 1;
+    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 0, -1, kRho, n1, n2, n2, n3, n1, H1, s));
+    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 1, -1, kPlain, n1, n2, H1, n3, n2, M2, s));
+    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 2, -1, kKernel, n1, n2, H1, M2, n3, n3, s));
+    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 1, +1, kPlain, n1, n2, H1, n3, M2, n2, s));
+    BHIP(launch_fft_lines_group(g.d_tail, nc, M1, M2, M3, 0, +1, kConj, n1, n2, n2, n3, M1, n1, s));
   }
   BHIP(launch_xc_group(g.d_tail, nc, n1, n2, n3, M1, M2, c0->cfg.hartree, c0->cfg.xc, s));
   return TDDFT_OK;

@@ -200,18 +200,19 @@ hipError_t launch_fused_persistent(int n, bool periodic, const FusedArgs<T>* cel
 
 hipError_t launch_rho_reduce(const double* part, int nchunks, int N, double* rho, hipStream_t s);
 
-// rho (with n1..n3): the first pass reads the density into the M-box itself;
-// K: the pass multiplies what it stores by K (the Poisson kernel)
-hipError_t launch_fft_axis(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s,
-                           const double* rho = nullptr, int n1 = 0, int n2 = 0, int n3 = 0,
-                           const double* K = nullptr);
+hipError_t launch_fft_axis(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s);
 // a pass over part of the box: lines (i1 < l1, i2 < l2) — (y, z) for the x
 // axis, (x, z) for y, (x, y) for z — reading elements below n_in (the rest is
-// 0) and storing those below n_out; fused (z axis, with K): forward, times K,
-// inverse in one pass
-hipError_t launch_fft_lines(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s,
-                            const double* rho, int n1, int n2, int n3, const double* K, int l1, int l2, int n_in,
-                            int n_out, int fused);
+// 0) and storing those below n_out. What the pass does besides:
+enum FFTEnds {
+  kPlain = 0,
+  kRho = 1,     // x axis: reads the real density rho (n1 x n2 x n3) in place of data
+  kConj = 2,    // x axis: reads element e > M1 / 2 as the conjugate of M1 - e
+  kKernel = 3,  // z axis: forward transform, times K, inverse transform
+};
+hipError_t launch_fft_lines(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s, int ends,
+                            const double* rho, int n1, int n2, const double* K, int l1, int l2, int n_in,
+                            int n_out);
 // Per-cell arguments of the end of a step (current, density, Poisson, xc).
 // When a group of same-shape cells runs it with one launch per kernel, the
 // cell is a grid dimension and the arguments come from a table of these.
@@ -305,11 +306,9 @@ hipError_t launch_poisson_forward_group(const TailCell* tab, int ncells, int n1,
 hipError_t launch_poisson_inverse_group(const TailCell* tab, int ncells, int n1, int n2, int n3, int xc,
                                         hipStream_t s);
 hipError_t launch_rho_reduce_group(const TailCell* tab, int ncells, int N, hipStream_t s);
-// as launch_fft_lines for every cell of tab (same box and lines); use_rho /
-// use_K: the pass reads the cell's rho / multiplies by its K
+// as launch_fft_lines for every cell of tab (same box and lines)
 hipError_t launch_fft_lines_group(const TailCell* tab, int ncells, int M1, int M2, int M3, int axis, int sign,
-                                  int use_rho, int n1, int n2, int n3, int use_K, int l1, int l2, int n_in,
-                                  int n_out, int fused, hipStream_t s);
+                                  int ends, int n1, int n2, int l1, int l2, int n_in, int n_out, hipStream_t s);
 hipError_t launch_xc_group(const TailCell* tab, int ncells, int n1, int n2, int n3, int M1, int M2, int hartree,
                            int xc, hipStream_t s);
 

@@ -348,12 +348,29 @@ hipError_t launch_rho_reduce(const double* part, int nchunks, int N, double* rho
 }
 
 // ---------------------------------------------------------------- FFT
-// In-place FP64 complex FFT of every line along one axis of an M1 x M2 x M3
-// array (M1 fastest), unnormalised, sign -1 forward / +1 inverse. A workgroup
-// stages B lines in LDS and runs a Stockham mixed-radix (4, 2, 3, 5)
+// In-place FP64 complex FFT of lines along one axis of an M1 x M2 x M3 array
+// (M1 fastest), unnormalised, sign -1 forward / +1 inverse. A workgroup
+// stages B lines in LDS and runs a Stockham mixed-radix (8, 4, 2, 3, 5)
 // transform: for radix R and Ns = product of the radices already applied,
 // butterfly j reads in[j + r M/R], multiplies by exp(sign 2 pi i r (j mod Ns) / (Ns R)),
 // does a length-R DFT and writes out[(j / Ns) Ns R + (j mod Ns) + r Ns].
+//
+// The density is real and so is the kernel K, which is even in each frequency:
+// the potential's transform along x is conjugate-symmetric, so the passes keep
+// kx <= M1 / 2 only and the last inverse x pass fills in the rest. That halves
+// the lines of the y and z passes and their traffic.
+//
+// What bounds it: on the small boxes of a periodic cell the chain of stages
+// (a barrier each; radix 8 makes 192 three stages and 32 two), on the doubled
+// box of an isolated cell the index arithmetic and LDS passes ahead of HBM. So
+// every quotient is a product with a float reciprocal, one table of the M
+// roots serves all stages and both signs, and the lines of the y and z passes
+// lie next to each other in LDS (eight lines are one 128-byte row: no bank
+// conflict in any stage, and full lines of memory). The five passes of the
+// 192^3 box of a 96^3 grid, before (complex, radix 4, divisions) and now:
+// x 39 -> 23 us, y 60 -> 20, z with K 205 -> 58 (120 MB: 2.1 TB/s), inverse y
+// 63 -> 20, inverse x 34 -> 27; a 36 x 40 x 27 cell's three launches by planes
+// 36 -> 29 us.
 struct FFTPlan {
   int M, nf;
   int f[12];
@@ -363,19 +380,23 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// o_s = sum_q v_q exp(sign 2 pi i q s / R) for R = 2, 3, 4, 5
+// t / d for 0 <= t < 2^20 and inv = 1.0f / d: (t + 1/2) / d is at least
+// 1 / (2 d) from an integer, the product's error below t / d 2^-22
+__device__ __forceinline__ int quot(int t, float inv) { return (int)(((float)t + 0.5f) * inv); }
+
+// o_s = sum_q v_q exp(sign 2 pi i q s / R) for R = 2, 3, 4, 5, 8
 template <int R>
-__device__ __forceinline__ void dft_small(double2* v, int sign);
+__device__ __forceinline__ void dft_small(double2* v, double sign);
 
 template <>
-__device__ __forceinline__ void dft_small<2>(double2* v, int) {
+__device__ __forceinline__ void dft_small<2>(double2* v, double) {
   const double2 a = v[0], b = v[1];
   v[0] = make_double2(a.x + b.x, a.y + b.y);
   v[1] = make_double2(a.x - b.x, a.y - b.y);
 }
 
 template <>
-__device__ __forceinline__ void dft_small<4>(double2* v, int sign) {
+__device__ __forceinline__ void dft_small<4>(double2* v, double sign) {
   // omega = exp(sign i pi / 2) = sign * i
   const double2 a = v[0], b = v[1], c = v[2], d = v[3];
   const double2 s02 = make_double2(a.x + c.x, a.y + c.y), d02 = make_double2(a.x - c.x, a.y - c.y);
@@ -388,8 +409,26 @@ __device__ __forceinline__ void dft_small<4>(double2* v, int sign) {
   v[3] = make_double2(d02.x - r13.x, d02.y - r13.y);
 }
 
+// two length-4 transforms (even and odd inputs) and a length-2 step with
+// omega^s, omega = (1 + sign i) / sqrt(2)
 template <>
-__device__ __forceinline__ void dft_small<3>(double2* v, int sign) {
+__device__ __forceinline__ void dft_small<8>(double2* v, double sign) {
+  double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+  dft_small<4>(e, sign);
+  dft_small<4>(o, sign);
+  const double h = 0.70710678118654752440;
+  o[1] = make_double2(h * (o[1].x - sign * o[1].y), h * (sign * o[1].x + o[1].y));
+  o[2] = make_double2(-sign * o[2].y, sign * o[2].x);
+  o[3] = make_double2(-h * (o[3].x + sign * o[3].y), h * (sign * o[3].x - o[3].y));
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    v[s] = make_double2(e[s].x + o[s].x, e[s].y + o[s].y);
+    v[s + 4] = make_double2(e[s].x - o[s].x, e[s].y - o[s].y);
+  }
+}
+
+template <>
+__device__ __forceinline__ void dft_small<3>(double2* v, double sign) {
   const double c1 = -0.5, s1 = sign * 0.86602540378443864676;  // exp(sign 2 pi i / 3)
   const double2 a = v[0], b = v[1], c = v[2];
   const double2 sbc = make_double2(b.x + c.x, b.y + c.y), dbc = make_double2(b.x - c.x, b.y - c.y);
@@ -401,7 +440,7 @@ __device__ __forceinline__ void dft_small<3>(double2* v, int sign) {
 }
 
 template <>
-__device__ __forceinline__ void dft_small<5>(double2* v, int sign) {
+__device__ __forceinline__ void dft_small<5>(double2* v, double sign) {
   const double cs[5] = {1.0, 0.30901699437494742410, -0.80901699437494742410, -0.80901699437494742410,
                         0.30901699437494742410};
   const double sn[5] = {0.0, 0.95105651629515357212, 0.58778525229247312917, -0.58778525229247312917,
@@ -423,60 +462,66 @@ __device__ __forceinline__ void dft_small<5>(double2* v, int sign) {
   for (int s = 0; s < 5; ++s) v[s] = o[s];
 }
 
-// twiddles of a stage: tw[jm (R - 1) + r - 1] = exp(sign 2 pi i r jm / (Ns R)), jm < Ns
+// nl lines in LDS: element e of line l at e * se + l * sl (one of se, sl is 1;
+// consecutive threads take the neighbours along it)
+struct LineSet {
+  int nl, se, sl;
+};
+
+// one stage; w: the M roots exp(2 pi i k / M), step = M / (Ns R)
 template <int R>
-__device__ void stockham_stage(const double2* in, double2* out, int B, int M, int Ns, int sign,
-                               const double2* tw) {
+__device__ __forceinline__ void stockham_stage(const double2* in, double2* out, const LineSet& ls, int M, int Ns,
+                                               int step, double sign, const double2* w) {
   const int nb = M / R;
-  for (int t = threadIdx.x; t < B * nb; t += blockDim.x) {
-    const int line = t / nb;
-    const int jj = t - line * nb;
-    const double2* li = in + (size_t)line * M;
-    double2* lo = out + (size_t)line * M;
+  const bool across = ls.sl == 1;
+  const int d = across ? ls.nl : nb;
+  const float inv_d = 1.0f / (float)d, inv_Ns = 1.0f / (float)Ns;
+  for (int t = threadIdx.x; t < ls.nl * nb; t += blockDim.x) {
+    const int q = quot(t, inv_d), rest = t - q * d;
+    const int line = across ? rest : q, jj = across ? q : rest;
+    const double2* li = in + line * ls.sl + jj * ls.se;
+    const int jq = quot(jj, inv_Ns), jm = jj - jq * Ns;
     double2 v[R];
-    const int jm = jj % Ns;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      v[r] = li[jj + r * nb];
-      if (r > 0 && jm != 0) v[r] = cmul(v[r], tw[jm * (R - 1) + r - 1]);
+    for (int r = 0; r < R; ++r) v[r] = li[r * nb * ls.se];
+    if (Ns > 1) {
+      const int k = jm * step;
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        const double2 c = w[r * k];
+        v[r] = cmul(v[r], make_double2(c.x, sign * c.y));
+      }
     }
     dft_small<R>(v, sign);
-    const int d = (jj / Ns) * Ns * R + jm;
+    double2* lo = out + line * ls.sl + (jq * Ns * R + jm) * ls.se;
 #pragma unroll
-    for (int r = 0; r < R; ++r) lo[d + r * Ns] = v[r];
+    for (int r = 0; r < R; ++r) lo[r * Ns * ls.se] = v[r];
   }
 }
 
-// the twiddles of every stage of the plan, stage after stage (M - 1 values)
-__device__ void fft_twiddles(const FFTPlan& plan, int sign, double2* tw) {
-  int off = 0, Ns = 1;
-  for (int f = 0; f < plan.nf; ++f) {
-    const int R = plan.f[f];
-    for (int t = threadIdx.x; t < Ns * (R - 1); t += blockDim.x) {
-      const int jm = t / (R - 1), r = t - jm * (R - 1) + 1;
-      double sn, cs;
-      sincospi(2.0 * sign * (double)(r * jm) / (double)(Ns * R), &sn, &cs);
-      tw[off + t] = make_double2(cs, sn);
-    }
-    off += Ns * (R - 1);
-    Ns *= R;
+// the M roots exp(2 pi i k / M)
+__device__ __forceinline__ void fft_roots(int M, double2* w) {
+  for (int k = threadIdx.x; k < M; k += blockDim.x) {
+    double sn, cs;
+    sincospi(2.0 * (double)k / (double)M, &sn, &cs);
+    w[k] = make_double2(cs, sn);
   }
 }
 
-// the plan's stages on B lines of length M in LDS (in -> out alternating);
-// returns the buffer that holds the result
-__device__ double2* fft_lines_lds(const FFTPlan& plan, double2* in, double2* out, int nl, int sign,
-                                  const double2* tw) {
+// the plan's stages on the lines in LDS (in -> out alternating, a barrier
+// after each); returns the buffer that holds the result
+__device__ __forceinline__ double2* fft_lines_lds(const FFTPlan& plan, double2* in, double2* out,
+                                                  const LineSet& ls, double sign, const double2* w) {
   const int M = plan.M;
-  int Ns = 1, off = 0;
+  int Ns = 1, step = M;
   for (int f = 0; f < plan.nf; ++f) {
     const int R = plan.f[f];
-    if (R == 4) stockham_stage<4>(in, out, nl, M, Ns, sign, tw + off);
-    else if (R == 2) stockham_stage<2>(in, out, nl, M, Ns, sign, tw + off);
-    else if (R == 3) stockham_stage<3>(in, out, nl, M, Ns, sign, tw + off);
-    else stockham_stage<5>(in, out, nl, M, Ns, sign, tw + off);
+    if (R == 8) stockham_stage<8>(in, out, ls, M, Ns, step /= 8, sign, w);
+    else if (R == 4) stockham_stage<4>(in, out, ls, M, Ns, step /= 4, sign, w);
+    else if (R == 2) stockham_stage<2>(in, out, ls, M, Ns, step /= 2, sign, w);
+    else if (R == 3) stockham_stage<3>(in, out, ls, M, Ns, step /= 3, sign, w);
+    else stockham_stage<5>(in, out, ls, M, Ns, step /= 5, sign, w);
     __syncthreads();
-    off += Ns * (R - 1);
     Ns *= R;
     double2* t = in;
     in = out;
@@ -485,181 +530,162 @@ __device__ double2* fft_lines_lds(const FFTPlan& plan, double2* in, double2* out
   return in;
 }
 
-// Optional ends of the Poisson solve, so that they cost no launch of their
-// own: rho (n1 x n2 x n3, zero beyond it in the M-box) is read in place of
-// data by the first (x) pass, and the result is multiplied by K (the Poisson
-// kernel) by the z pass.
-struct FFTEnds {
-  const double* rho;
-  int n1, n2, n3;
-  const double* K;
-};
-
 // The lines a pass transforms and the part of each it reads and writes: lines
 // (i1, i2) with i1 < l1, i2 < l2 — (y, z) for the x axis, (x, z) for y, (x, y)
 // for z — elements at or beyond n_in read as 0, elements at or beyond n_out
-// not stored. fused (z axis): forward transform, times K, inverse transform
-// with the opposite sign, in one pass.
+// not stored. ends (FFTEnds) says what else a pass does, so that it costs no
+// launch of its own.
 struct FFTLines {
-  int l1, l2, n_in, n_out, fused;
+  int l1, l2, n_in, n_out, ends;
+  int B, nb1;  // lines per workgroup (of one i2) and workgroups per i2
 };
 
-// B lines of one pass from line blk B on (smem_raw: the dynamic LDS)
-__device__ __forceinline__ void fft_axis_block(double2* data, int M1, int M2, int M3, int axis, int sign, int B,
-                                               const FFTPlan& plan, const FFTEnds& ends, const FFTLines& ln,
-                                               long blk, unsigned char* smem_raw) {
-  (void)M3;
-  const int M = plan.M;
+// B lines of one pass (smem_raw: the dynamic LDS)
+__device__ __forceinline__ void fft_axis_block(double2* data, int M1, int M2, int axis, int sign, const FFTPlan& plan,
+                                               const double* rho, int n1, int n2, const double* K,
+                                               const FFTLines& ln, int blk, unsigned char* smem_raw) {
+  const int M = plan.M, B = ln.B;
   double2* buf0 = reinterpret_cast<double2*>(smem_raw);
-  double2* buf1 = buf0 + (size_t)B * M;
-  double2* tw = buf1 + (size_t)B * M;   // M entries
-  double2* twi = tw + M;                // M entries (fused: the inverse's)
-  const long nlines = (long)ln.l1 * ln.l2;
-  const long L0 = blk * B;
-  const int nl = (int)min((long)B, nlines - L0);
-  const long stride = (axis == 0) ? 1 : (axis == 1 ? M1 : (long)M1 * M2);
-  auto line_base = [&](long L) -> long {
-    const long i2 = L / ln.l1, i1 = L - i2 * ln.l1;
-    if (axis == 0) return (i2 * M2 + i1) * M1;
-    if (axis == 1) return i2 * (long)M1 * M2 + i1;
-    return i2 * M1 + i1;
-  };
-  fft_twiddles(plan, sign, tw);
-  if (ln.fused) fft_twiddles(plan, -sign, twi);
-  // load
-  for (int i = threadIdx.x; i < nl * M; i += blockDim.x) {
-    int line, e;
-    if (axis == 0) {
-      line = i / M;
-      e = i - line * M;
-    } else {
-      e = i / nl;
-      line = i - e * nl;
-    }
+  double2* buf1 = buf0 + B * M;
+  double2* w = buf1 + B * M;
+  const int i2 = blk / ln.nb1, i1 = (blk - i2 * ln.nb1) * B;
+  const int nl = min(B, ln.l1 - i1);
+  // element e of line l at base + l * gl + e * ge
+  const size_t ge = axis == 0 ? 1 : (axis == 1 ? (size_t)M1 : (size_t)M1 * M2);
+  const size_t gl = axis == 0 ? (size_t)M1 : 1;
+  const size_t base = axis == 0 ? ((size_t)i2 * M2 + i1) * M1
+                                : (axis == 1 ? (size_t)i2 * M1 * M2 + i1 : (size_t)i2 * M1 + i1);
+  const LineSet ls{nl, axis == 0 ? 1 : B, axis == 0 ? M : 1};
+  const int d = axis == 0 ? M : nl;
+  const float inv_d = 1.0f / (float)d;
+  const int total = nl * M;
+  fft_roots(M, w);
+  for (int i = threadIdx.x; i < total; i += blockDim.x) {
+    const int q = quot(i, inv_d), rest = i - q * d;
+    const int line = axis == 0 ? q : rest, e = axis == 0 ? rest : q;
     double2 v = make_double2(0.0, 0.0);
-    if (e < ln.n_in) {
-      const long gi = line_base(L0 + line) + (long)e * stride;
-      if (ends.rho) {
-        const int x = (int)(gi % M1), y = (int)((gi / M1) % M2), z = (int)(gi / ((long)M1 * M2));
-        if (x < ends.n1 && y < ends.n2 && z < ends.n3)
-          v = make_double2(ends.rho[((size_t)z * ends.n2 + y) * ends.n1 + x], 0.0);
-      } else {
-        v = data[gi];
-      }
+    if (ln.ends == kRho) {
+      if (e < ln.n_in) v.x = rho[((size_t)i2 * n2 + i1 + line) * n1 + e];
+    } else if (ln.ends == kConj && 2 * e > M) {
+      v = data[base + line * gl + (M - e)];
+      v.y = -v.y;
+    } else if (e < ln.n_in) {
+      v = data[base + line * gl + e * ge];
     }
-    buf0[line * M + e] = v;
+    buf0[line * ls.sl + e * ls.se] = v;
   }
   __syncthreads();
-  double2* res = fft_lines_lds(plan, buf0, buf1, nl, sign, tw);
-  if (ln.fused) {
-    for (int i = threadIdx.x; i < nl * M; i += blockDim.x) {
-      const int e = i / nl, line = i - e * nl;
-      const double k = ends.K[line_base(L0 + line) + (long)e * stride];
-      const double2 v = res[line * M + e];
-      res[line * M + e] = make_double2(v.x * k, v.y * k);
+  double2* res = fft_lines_lds(plan, buf0, buf1, ls, (double)sign, w);
+  if (ln.ends == kKernel) {
+    for (int i = threadIdx.x; i < total; i += blockDim.x) {
+      const int e = quot(i, inv_d), line = i - e * d;
+      const double k = K[base + line + e * ge];
+      double2* r = res + line + e * B;
+      *r = make_double2(r->x * k, r->y * k);
     }
     __syncthreads();
-    res = fft_lines_lds(plan, res, res == buf0 ? buf1 : buf0, nl, -sign, twi);
+    res = fft_lines_lds(plan, res, res == buf0 ? buf1 : buf0, ls, -(double)sign, w);
   }
-  for (int i = threadIdx.x; i < nl * M; i += blockDim.x) {
-    int line, e;
-    if (axis == 0) {
-      line = i / M;
-      e = i - line * M;
-    } else {
-      e = i / nl;
-      line = i - e * nl;
-    }
-    if (e >= ln.n_out) continue;
-    const long gi = line_base(L0 + line) + (long)e * stride;
-    double2 v = res[line * M + e];
-    if (ends.K && !ln.fused) {
-      const double k = ends.K[gi];
-      v = make_double2(v.x * k, v.y * k);
-    }
-    data[gi] = v;
+  for (int i = threadIdx.x; i < total; i += blockDim.x) {
+    const int q = quot(i, inv_d), rest = i - q * d;
+    const int line = axis == 0 ? q : rest, e = axis == 0 ? rest : q;
+    if (e < ln.n_out) data[base + line * gl + e * ge] = res[line * ls.sl + e * ls.se];
   }
 }
 
-__global__ __launch_bounds__(256) void k_fft_axis(double2* data, int M1, int M2, int M3, int axis,
-                                                  int sign, int B, FFTPlan plan, FFTEnds ends, FFTLines ln) {
+constexpr int kFFTThreads = 512;
+
+__global__ __launch_bounds__(kFFTThreads) void k_fft_axis(double2* data, int M1, int M2, int axis, int sign,
+                                                          FFTPlan plan, const double* rho, int n1, int n2,
+                                                          const double* K, FFTLines ln) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  fft_axis_block(data, M1, M2, M3, axis, sign, B, plan, ends, ln, (long)blockIdx.x, smem_raw);
+  fft_axis_block(data, M1, M2, axis, sign, plan, rho, n1, n2, K, ln, (int)blockIdx.x, smem_raw);
 }
 
 // the same pass for the cells of a group (cell blockIdx.y)
-__global__ __launch_bounds__(256) void k_fft_axis_group(const TailCell* __restrict__ tab, int M1, int M2, int M3,
-                                                        int axis, int sign, int B, FFTPlan plan, FFTEnds ends,
-                                                        FFTLines ln, int use_rho, int use_K) {
+__global__ __launch_bounds__(kFFTThreads) void k_fft_axis_group(const TailCell* __restrict__ tab, int M1, int M2,
+                                                                int axis, int sign, FFTPlan plan, int n1, int n2,
+                                                                FFTLines ln) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const TailCell& t = tab[blockIdx.y];
-  FFTEnds e = ends;
-  e.rho = use_rho ? t.rho : nullptr;
-  e.K = use_K ? t.Kfft : nullptr;
-  fft_axis_block(t.fft, M1, M2, M3, axis, sign, B, plan, e, ln, (long)blockIdx.x, smem_raw);
+  fft_axis_block(t.fft, M1, M2, axis, sign, plan, t.rho, n1, n2, t.Kfft, ln, (int)blockIdx.x, smem_raw);
 }
 
-// the radix plan of a transform of length M (false: M has other prime factors)
+// the radix plan of a transform of length M (false: M has other prime
+// factors): eights, with 2 x 8 as 4 x 4, then 4 or 2, threes and fives
 static bool fft_plan(int M, FFTPlan* plan) {
   plan->M = M;
   plan->nf = 0;
-  int rem = M;
-  const int radices[4] = {4, 2, 3, 5};
-  for (int r : radices) {
+  int rem = M, twos = 0;
+  if (M < 1) return false;
+  while (rem % 2 == 0) rem /= 2, ++twos;
+  int n8 = twos / 3, left = twos - 3 * n8;
+  if (left == 1 && n8 > 0) --n8, left = 4;
+  for (int i = 0; i < n8 && plan->nf < 12; ++i) plan->f[plan->nf++] = 8;
+  for (; left >= 2 && plan->nf < 12; left -= 2) plan->f[plan->nf++] = 4;
+  if (left == 1 && plan->nf < 12) plan->f[plan->nf++] = 2;
+  for (int r : {3, 5})
     while (rem % r == 0 && plan->nf < 12) {
       plan->f[plan->nf++] = r;
       rem /= r;
     }
-  }
   return rem == 1;
 }
 
+// lines, workgroups, threads and LDS of a pass over ncells boxes: up to 2048
+// points a workgroup (eight lines of 192), fewer until min_wg workgroups share
+// the pass; threads for a radix-4 butterfly each
+struct FFTShape {
+  FFTLines ln;
+  unsigned grid;
+  int threads;
+  size_t lds;
+};
+static FFTShape fft_shape(int M, int l1, int l2, int n_in, int n_out, int ends, int ncells, int min_wg) {
+  int B = 1;
+  while (2 * B * M <= 2048 && B < l1) B *= 2;
+  auto groups = [&](int b) { return (long)((l1 + b - 1) / b) * l2; };
+  while (B > 1 && groups(B) * ncells < min_wg) B /= 2;
+  FFTShape f;
+  f.ln = FFTLines{l1, l2, n_in, n_out, ends, B, (l1 + B - 1) / B};
+  f.grid = (unsigned)groups(B);
+  f.threads = min(kFFTThreads, max(64, (B * M / 4 + 63) / 64 * 64));
+  f.lds = ((size_t)2 * B * M + (size_t)M) * sizeof(double2);
+  return f;
+}
+
 hipError_t launch_fft_lines_group(const TailCell* tab, int ncells, int M1, int M2, int M3, int axis, int sign,
-                                  int use_rho, int n1, int n2, int n3, int use_K, int l1, int l2, int n_in,
-                                  int n_out, int fused, hipStream_t s) {
+                                  int ends, int n1, int n2, int l1, int l2, int n_in, int n_out, hipStream_t s) {
   FFTPlan plan;
   if (!fft_plan(axis == 0 ? M1 : (axis == 1 ? M2 : M3), &plan)) return hipErrorInvalidValue;
-  if (fused && (axis != 2 || !use_K)) return hipErrorInvalidValue;
-  const long nlines = (long)l1 * l2;
-  if (nlines <= 0 || ncells <= 0) return hipSuccess;
-  // every line is transformed the same way whatever B is; lines per workgroup
-  // as long as all cells together give a workgroup per compute unit (two cells
-  // of 16^3 on four workgroups took 14 us a pass)
-  int B = max(1, min(256, 2048 / plan.M));
-  while (B > 1 && nlines / B * ncells < 256) B /= 2;
-  const size_t lds = ((size_t)2 * B * plan.M + 2 * (size_t)plan.M) * sizeof(double2);
-  FFTEnds ends{nullptr, n1, n2, n3, nullptr};
-  FFTLines ln{l1, l2, n_in, n_out, fused};
-  hipLaunchKernelGGL(k_fft_axis_group, dim3((unsigned)((nlines + B - 1) / B), ncells), dim3(256), lds, s, tab, M1,
-                     M2, M3, axis, sign, B, plan, ends, ln, use_rho, use_K);
+  if ((ends == kKernel && axis != 2) || ((ends == kRho || ends == kConj) && axis != 0)) return hipErrorInvalidValue;
+  if (l1 <= 0 || l2 <= 0 || ncells <= 0) return hipSuccess;
+  // a workgroup per compute unit over all cells (two cells of 16^3 on four
+  // workgroups took 14 us a pass)
+  const FFTShape f = fft_shape(plan.M, l1, l2, n_in, n_out, ends, ncells, 256);
+  hipLaunchKernelGGL(k_fft_axis_group, dim3(f.grid, ncells), dim3(f.threads), f.lds, s, tab, M1, M2, axis, sign,
+                     plan, n1, n2, f.ln);
   return hipGetLastError();
 }
 
-hipError_t launch_fft_lines(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s,
-                            const double* rho, int n1, int n2, int n3, const double* K, int l1, int l2, int n_in,
-                            int n_out, int fused) {
+hipError_t launch_fft_lines(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s, int ends,
+                            const double* rho, int n1, int n2, const double* K, int l1, int l2, int n_in,
+                            int n_out) {
   FFTPlan plan;
   if (!fft_plan(axis == 0 ? M1 : (axis == 1 ? M2 : M3), &plan)) return hipErrorInvalidValue;
-  if (fused && (axis != 2 || !K)) return hipErrorInvalidValue;
-  const long nlines = (long)l1 * l2;
-  if (nlines <= 0) return hipSuccess;
-  // lines per workgroup: up to 2048 points, but small boxes are spread over at
-  // least 64 workgroups (each line is transformed the same way wherever it runs)
-  int B = max(1, min(256, 2048 / plan.M));
-  while (B > 1 && nlines / B < 64) B /= 2;
-  const size_t lds = ((size_t)2 * B * plan.M + 2 * (size_t)plan.M) * sizeof(double2);
-  FFTEnds ends{rho, n1, n2, n3, K};
-  FFTLines ln{l1, l2, n_in, n_out, fused};
-  hipLaunchKernelGGL(k_fft_axis, dim3((unsigned)((nlines + B - 1) / B)), dim3(256), lds, s, data, M1, M2, M3,
-                     axis, sign, B, plan, ends, ln);
+  if ((ends == kKernel && (axis != 2 || !K)) || (ends == kRho && (axis != 0 || !rho)) || (ends == kConj && axis != 0))
+    return hipErrorInvalidValue;
+  if (l1 <= 0 || l2 <= 0) return hipSuccess;
+  const FFTShape f = fft_shape(plan.M, l1, l2, n_in, n_out, ends, 1, 64);
+  hipLaunchKernelGGL(k_fft_axis, dim3(f.grid), dim3(f.threads), f.lds, s, data, M1, M2, axis, sign, plan, rho, n1,
+                     n2, K, f.ln);
   return hipGetLastError();
 }
 
-hipError_t launch_fft_axis(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s,
-                           const double* rho, int n1, int n2, int n3, const double* K) {
+hipError_t launch_fft_axis(double2* data, int M1, int M2, int M3, int axis, int sign, hipStream_t s) {
   const int l1 = axis == 0 ? M2 : M1, l2 = axis == 2 ? M2 : M3;
   const int M = axis == 0 ? M1 : (axis == 1 ? M2 : M3);
-  return launch_fft_lines(data, M1, M2, M3, axis, sign, s, rho, n1, n2, n3, K, l1, l2, M, M, 0);
+  return launch_fft_lines(data, M1, M2, M3, axis, sign, s, kPlain, nullptr, 0, 0, nullptr, l1, l2, M, M);
 }
 
 // ---------------------------------------------------------------- LDA + V
@@ -731,7 +757,9 @@ __device__ __forceinline__ void xc_point(const double2* data, int n1, int n2, in
 // the potential. Each line is transformed as in the pass-by-pass form (which
 // isolated boxes and larger planes use), so the bits of the solve are the same;
 // that form's reduction, five passes and assembly are seven launches of 4 to
-// 7 us each, half of a small cell's step.
+// 7 us each, half of a small cell's step. The plane stays [y][x] in LDS for
+// both directions (the stages take the stride), and only kx <= n1 / 2 goes
+// through the y transforms and memory.
 struct PlanePlan {
   int n1, n2, n3;
   FFTPlan x, y;
@@ -741,18 +769,12 @@ bool poisson_planes(int periodic, int hartree, int n1, int n2) {
   return periodic && hartree && n1 * n2 <= kPlaneMax;
 }
 
-__device__ __forceinline__ void plane_twiddles(const PlanePlan& pl, int sign, double2* twx, double2* twy) {
-  fft_twiddles(pl.x, sign, twx);
-  fft_twiddles(pl.y, sign, twy);
-}
-
-// [rows][cols] -> [cols][rows]
-__device__ __forceinline__ void plane_transpose(const double2* in, double2* out, int rows, int cols) {
-  for (int i = threadIdx.x; i < rows * cols; i += blockDim.x) {
-    const int r = i / cols, c = i - r * cols;
-    out[c * rows + r] = in[i];
-  }
-  __syncthreads();
+// the roots of both lengths (one table where they are equal)
+__device__ __forceinline__ const double2* plane_roots(const PlanePlan& pl, double2* wx) {
+  fft_roots(pl.n1, wx);
+  if (pl.n1 == pl.n2) return wx;
+  fft_roots(pl.n2, wx + pl.n1);
+  return wx + pl.n1;
 }
 
 __device__ __forceinline__ void poisson_forward_plane(const TailCell& t, const PlanePlan& pl, int z,
@@ -761,8 +783,8 @@ __device__ __forceinline__ void poisson_forward_plane(const TailCell& t, const P
   const size_t N = (size_t)P * pl.n3;
   double2* a = reinterpret_cast<double2*>(smem_raw);
   double2* b = a + P;
-  double2 *twx = b + P, *twy = twx + pl.n1;
-  plane_twiddles(pl, -1, twx, twy);
+  double2* wx = b + P;
+  const double2* wy = plane_roots(pl, wx);
   double* rho = t.rho + (size_t)z * P;
   if (t.nchunks == 1) {
     for (int p = threadIdx.x; p < P; p += blockDim.x) a[p] = make_double2(rho[p], 0.0);
@@ -770,7 +792,7 @@ __device__ __forceinline__ void poisson_forward_plane(const TailCell& t, const P
     // slices of the workgroup sum chunks j, j + nsl, ... in order, then the
     // slices add up in order
     const int nsl = max(1, (int)blockDim.x / P);
-    double* red = reinterpret_cast<double*>(twy + pl.n2);  // [nsl][P] (nsl > 1: at most blockDim.x)
+    double* red = reinterpret_cast<double*>(wx + pl.n1 + pl.n2);  // [nsl][P] (nsl > 1: at most blockDim.x)
     const double* part = t.rho_part + (size_t)z * P;
     for (int i = threadIdx.x; i < nsl * P; i += blockDim.x) {
       const int j = i / P, p = i - j * P;
@@ -800,14 +822,14 @@ __device__ __forceinline__ void poisson_forward_plane(const TailCell& t, const P
     }
   }
   __syncthreads();
-  double2* r = fft_lines_lds(pl.x, a, b, pl.n2, -1, twx);   // [y][x]
-  double2* o = r == a ? b : a;
-  plane_transpose(r, o, pl.n2, pl.n1);                       // [x][y]
-  r = fft_lines_lds(pl.y, o, r, pl.n1, -1, twy);
+  const int H = pl.n1 / 2 + 1;
+  double2* r = fft_lines_lds(pl.x, a, b, LineSet{pl.n2, 1, pl.n1}, -1.0, wx);
+  r = fft_lines_lds(pl.y, r, r == a ? b : a, LineSet{H, pl.n1, 1}, -1.0, wy);
   double2* out = t.fft + (size_t)z * P;
-  for (int i = threadIdx.x; i < P; i += blockDim.x) {
-    const int y = i / pl.n1, x = i - y * pl.n1;
-    out[i] = r[x * pl.n2 + y];
+  const float inv = 1.0f / (float)H;
+  for (int i = threadIdx.x; i < H * pl.n2; i += blockDim.x) {
+    const int y = quot(i, inv), p = y * pl.n1 + i - y * H;
+    out[p] = r[p];
   }
 }
 
@@ -816,18 +838,27 @@ __device__ __forceinline__ void poisson_inverse_plane(const TailCell& t, const P
   const int P = pl.n1 * pl.n2;
   double2* a = reinterpret_cast<double2*>(smem_raw);
   double2* b = a + P;
-  double2 *twx = b + P, *twy = twx + pl.n1;
-  plane_twiddles(pl, +1, twx, twy);
+  double2* wx = b + P;
+  const double2* wy = plane_roots(pl, wx);
   const double2* in = t.fft + (size_t)z * P;
-  for (int i = threadIdx.x; i < P; i += blockDim.x) {
-    const int y = i / pl.n1, x = i - y * pl.n1;
-    a[x * pl.n2 + y] = in[i];
+  const int H = pl.n1 / 2 + 1;
+  const float inv = 1.0f / (float)H;
+  for (int i = threadIdx.x; i < H * pl.n2; i += blockDim.x) {
+    const int y = quot(i, inv), p = y * pl.n1 + i - y * H;
+    a[p] = in[p];
   }
   __syncthreads();
-  double2* r = fft_lines_lds(pl.y, a, b, pl.n1, +1, twy);   // [x][y]
-  double2* o = r == a ? b : a;
-  plane_transpose(r, o, pl.n1, pl.n2);                       // [y][x]
-  r = fft_lines_lds(pl.x, o, r, pl.n2, +1, twx);
+  double2* r = fft_lines_lds(pl.y, a, b, LineSet{H, pl.n1, 1}, +1.0, wy);
+  // kx > n1 / 2 from its conjugate
+  const int C = pl.n1 - H;
+  const float invC = 1.0f / (float)C;
+  for (int i = threadIdx.x; i < C * pl.n2; i += blockDim.x) {
+    const int y = quot(i, invC), x = H + i - y * C;
+    const double2 v = r[y * pl.n1 + pl.n1 - x];
+    r[y * pl.n1 + x] = make_double2(v.x, -v.y);
+  }
+  __syncthreads();
+  r = fft_lines_lds(pl.x, r, r == a ? b : a, LineSet{pl.n2, 1, pl.n1}, +1.0, wx);
   for (int i = threadIdx.x; i < P; i += blockDim.x)
     xc_value(r[i].x * t.vh_scale, t.rho, t.Vloc, xc, vx_mgga, t.Vd, t.Vf, t.vh, t.exc, (size_t)z * P + i);
 }
