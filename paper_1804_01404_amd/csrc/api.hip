@@ -81,8 +81,8 @@ struct tddft_ctx {
   double* ent_beta = nullptr;  // [S][4]
   int n_colors = 0;
   int *color_start = nullptr, *color_atoms = nullptr;
-  std::vector<int> color_ent_start;  // host: entries of colour c are color_ents[start[c] .. start[c+1])
-  int* color_ents = nullptr;         // [S] entry ids grouped by colour
+  std::vector<int> color_chunk_start;  // host: chunks of colour c are color_chunks[start[c] .. start[c+1])
+  int4* color_chunks = nullptr;        // up to 64 entries of one atom each: first entry, past the last, atom
   bool fused = false;          // whole step per orbital in LDS
   double2* Eu = nullptr;
   double2* Eu2 = nullptr;      // second E_p u_p buffer: stages alternate when the add-back rides in the projection
@@ -392,6 +392,7 @@ StageArgs<T> stage_args(tddft_ctx* c) {
   a.efield = (c->cfg.gauge == TDDFT_LENGTH) ? c->efield : nullptr;
   a.Eu = c->nl.n_atoms > 0 ? c->Eu : nullptr;
   a.phA = c->phA;
+  a.ent_beta = c->ent_beta;
   a.nl = c->nl;
   a.g = c->gs;
   std::memcpy(a.lap, c->lap, sizeof(a.lap));
@@ -434,6 +435,8 @@ tddft_status enqueue_observe(tddft_ctx* c, int bump) {
     ProjArgs<T> pa{};
     pa.u = as2<T>(c->W);
     pa.phA = c->phAJ;
+    pa.ent_beta = c->ent_beta;
+    pa.ent_x = c->ent_x;
     pa.nl = c->nl;
     pa.N = (int)c->N;
     pa.n_orb = c->cfg.n_orb;
@@ -541,6 +544,7 @@ tddft_status enqueue_taylor_stages(tddft_ctx* c, double dt, double tau_imag) {
       ProjArgs<T> pa{};
       pa.u = as2<T>(bufs_in[i]);
       pa.phA = c->phA;
+      pa.ent_beta = c->ent_beta;
       pa.nl = c->nl;
       pa.N = (int)c->N;
       pa.n_orb = c->cfg.n_orb;
@@ -552,7 +556,6 @@ tddft_status enqueue_taylor_stages(tddft_ctx* c, double dt, double tau_imag) {
       if (ride && i > 0) {
         // u_s came from stage s + 1, whose projections are in the other buffer
         pa.Eu_prev = eu_buf[(i - 1) & 1];
-        pa.ent_beta = c->ent_beta;
         pa.tau = dt / (s + 1);
         pa.tau_re = -tau_imag / (s + 1);
       }
@@ -566,11 +569,11 @@ tddft_status enqueue_taylor_stages(tddft_ctx* c, double dt, double tau_imag) {
     a.Eu = nl ? eu_buf[i & 1] : nullptr;
     const int mode = (s == 4) ? kFirst : (s == 1 ? kLast : kMid);
     LAUNCH(launch_stage<T>(mode, c->sbc, a, c->stream), "stage");
-    // the nonlocal term of the stage, added over each colour's sphere entries
+    // the nonlocal term of the stage, added over each colour's spheres
     if (ride && s > 1) continue;
     for (int cl = 0; cl < c->n_colors && nl; ++cl) {
-      const int e0 = c->color_ent_start[cl], ne = c->color_ent_start[cl + 1] - e0;
-      LAUNCH(launch_nl_addback<T>(a, c->color_ents + e0, ne, (int)c->n_orb_tot, c->stream), "nonlocal add-back");
+      const int c0 = c->color_chunk_start[cl], nc = c->color_chunk_start[cl + 1] - c0;
+      LAUNCH(launch_nl_addback<T>(a, c->color_chunks + c0, nc, (int)c->n_orb_tot, c->stream), "nonlocal add-back");
     }
   }
   return TDDFT_OK;
@@ -722,14 +725,15 @@ tddft_status launch_one(tddft_ctx* c, int which) {
     a.tau = c->cfg.dt / 2;
     LAUNCH(launch_stage<T>(kMid, c->sbc, a, c->stream), "stage");
     for (int cl = 0; cl < c->n_colors && c->nl.n_atoms > 0; ++cl) {
-      const int e0 = c->color_ent_start[cl], ne = c->color_ent_start[cl + 1] - e0;
-      LAUNCH(launch_nl_addback<T>(a, c->color_ents + e0, ne, (int)c->n_orb_tot, c->stream), "nonlocal add-back");
+      const int c0 = c->color_chunk_start[cl], nc = c->color_chunk_start[cl + 1] - c0;
+      LAUNCH(launch_nl_addback<T>(a, c->color_chunks + c0, nc, (int)c->n_orb_tot, c->stream), "nonlocal add-back");
     }
   } else if (which == TDDFT_KERNEL_PROJECT) {
     if (c->nl.n_atoms == 0) return TDDFT_OK;
     ProjArgs<T> pa{};
     pa.u = as2<T>(c->U0);
     pa.phA = c->phA;
+    pa.ent_beta = c->ent_beta;
     pa.nl = c->nl;
     pa.N = (int)c->N;
     pa.n_orb = c->cfg.n_orb;
@@ -1290,7 +1294,7 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   }
   // ---- nonlocal tables on the host
   std::vector<int> atom_start(1, 0), ent_idx, ent_atom;
-  std::vector<double> ent_B, atom_E, ent_x;
+  std::vector<double> ent_beta, atom_E, ent_x;
   std::vector<int> cover(N, 0);
   double nl_bound = 0;
   for (int a = 0; a < n_atoms; ++a) {
@@ -1322,10 +1326,7 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
       for (int p = 0; p < kMaxProj; ++p) {
         const double b = p < A.n_proj ? A.beta[(size_t)p * A.npts + i] : 0.0;
         if (!std::isfinite(b)) return fail(c, TDDFT_EINVAL, "projector value not finite");
-        ent_B.push_back(b);
-        ent_B.push_back(b * x[0]);
-        ent_B.push_back(b * x[1]);
-        ent_B.push_back(b * x[2]);
+        ent_beta.push_back(b);
       }
     }
     atom_start.push_back((int)ent_idx.size());
@@ -1365,11 +1366,13 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
       if (color[a] == cl) color_atoms.push_back(a);
     color_start[cl + 1] = (int)color_atoms.size();
   }
-  std::vector<int> color_ent_start(n_colors + 1, 0), color_ents;
+  std::vector<int> color_chunk_start(n_colors + 1, 0);
+  std::vector<int4> color_chunks;
   for (int cl = 0; cl < n_colors; ++cl) {
     for (int i = color_start[cl]; i < color_start[cl + 1]; ++i)
-      for (int e = atom_start[color_atoms[i]]; e < atom_start[color_atoms[i] + 1]; ++e) color_ents.push_back(e);
-    color_ent_start[cl + 1] = (int)color_ents.size();
+      for (int at = color_atoms[i], e = atom_start[at], e1 = atom_start[at + 1]; e < e1; e += 64)
+        color_chunks.push_back(make_int4(e, std::min(e + 64, e1), at, 0));
+    color_chunk_start[cl + 1] = (int)color_chunks.size();
   }
   c->max_overlap = max_overlap;
   // exp(i k . x_e)
@@ -1395,18 +1398,18 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   HIP_TRY(hipStreamSynchronize(c->stream));
   tddft_status st;
   int *d_atom_start, *d_ent_idx, *d_ent_atom, *d_pt_ptr, *d_pt_ent;
-  double *d_ent_B, *d_atom_E, *d_ent_x, *d_ent_beta;
+  double *d_atom_E, *d_ent_x, *d_ent_beta;
   double2 *d_phk, *d_phA, *d_phAJ, *d_Eu, *d_Eu2;
   double* d_jnl;
   const int nA = std::max(n_atoms, 1);
   const int Sx = std::max(S, 1);
   if ((st = dalloc_t(c, atom_start.size(), &d_atom_start)) || (st = dalloc_t(c, Sx, &d_ent_idx)) ||
       (st = dalloc_t(c, Sx, &d_ent_atom)) || (st = dalloc_t(c, N + 1, &d_pt_ptr)) ||
-      (st = dalloc_t(c, pt_ent.size(), &d_pt_ent)) || (st = dalloc_t(c, (size_t)Sx * kCols, &d_ent_B)) ||
+      (st = dalloc_t(c, pt_ent.size(), &d_pt_ent)) ||
       (st = dalloc_t(c, (size_t)nA * kMaxProj, &d_atom_E)) || (st = dalloc_t(c, (size_t)Sx * 3, &d_ent_x)) ||
       (st = dalloc_t(c, (size_t)Sx * kMaxProj, &d_ent_beta)) ||
       (st = dalloc_t(c, (size_t)n_colors + 1, &c->color_start)) || (st = dalloc_t(c, (size_t)nA, &c->color_atoms)) ||
-      (st = dalloc_t(c, (size_t)Sx, &c->color_ents)) ||
+      (st = dalloc_t(c, std::max<size_t>(color_chunks.size(), 1), &c->color_chunks)) ||
       (st = dalloc_t(c, phk.size(), &d_phk)) || (st = dalloc_t(c, Sx, &d_phA)) ||
       (st = dalloc_t(c, Sx, &d_phAJ)) ||
       (st = dalloc_t(c, c->n_orb_tot * nA * kMaxProj, &d_Eu)) ||
@@ -1421,17 +1424,13 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   HIP_TRY(up(d_ent_atom, ent_atom.data(), S * sizeof(int)));
   HIP_TRY(up(d_pt_ptr, pt_ptr.data(), (N + 1) * sizeof(int)));
   HIP_TRY(up(d_pt_ent, pt_ent.data(), S * sizeof(int)));
-  HIP_TRY(up(d_ent_B, ent_B.data(), ent_B.size() * sizeof(double)));
   HIP_TRY(up(d_atom_E, atom_E.data(), atom_E.size() * sizeof(double)));
   HIP_TRY(up(d_ent_x, ent_x.data(), ent_x.size() * sizeof(double)));
-  std::vector<double> ent_beta((size_t)S * kMaxProj);
-  for (int e = 0; e < S; ++e)
-    for (int p = 0; p < kMaxProj; ++p) ent_beta[(size_t)e * kMaxProj + p] = ent_B[(size_t)e * kCols + p * kMoments];
   HIP_TRY(up(d_ent_beta, ent_beta.data(), ent_beta.size() * sizeof(double)));
   HIP_TRY(up(c->color_start, color_start.data(), color_start.size() * sizeof(int)));
   HIP_TRY(up(c->color_atoms, color_atoms.data(), color_atoms.size() * sizeof(int)));
-  HIP_TRY(up(c->color_ents, color_ents.data(), color_ents.size() * sizeof(int)));
-  c->color_ent_start = color_ent_start;
+  HIP_TRY(up(c->color_chunks, color_chunks.data(), color_chunks.size() * sizeof(int4)));
+  c->color_chunk_start = color_chunk_start;
   c->n_colors = n_colors;
   HIP_TRY(up(d_phk, phk.data(), (size_t)c->cfg.n_k * S * sizeof(double2)));
   HIP_TRY(up(c->Vloc, v_loc, N * sizeof(double)));
@@ -1440,7 +1439,6 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   c->nl.atom_start = d_atom_start;
   c->nl.ent_idx = d_ent_idx;
   c->nl.ent_atom = d_ent_atom;
-  c->nl.ent_B = d_ent_B;
   c->nl.atom_E = d_atom_E;
   c->nl.pt_ptr = d_pt_ptr;
   c->nl.pt_ent = d_pt_ent;

@@ -17,7 +17,7 @@ constexpr double kC = 137.035999084;   // speed of light, atomic units
 constexpr int kHalf = 4;               // stencil half width (9 points per axis)
 constexpr int kMaxProj = 4;            // projectors per atom
 constexpr int kMoments = 4;            // beta, x beta, y beta, z beta
-constexpr int kCols = kMaxProj * kMoments;  // MFMA B-matrix columns (16)
+constexpr int kCols = kMaxProj * kMoments;  // (projector, moment) pairs of an atom (16)
 // halo points a thread of a tiled stage or observe workgroup stages per plane
 // at most: 8 (TX + TY) points over ceil64(TX TY) threads
 constexpr int kHaloSlots = 3;
@@ -41,7 +41,6 @@ struct NLTables {
   const int* atom_start = nullptr;   // [n_atoms + 1]
   const int* ent_idx = nullptr;      // [S] flat grid index
   const int* ent_atom = nullptr;     // [S]
-  const double* ent_B = nullptr;     // [S][16]: column 4p+m = beta_p * (1, x, y, z)[m]
   const double* atom_E = nullptr;    // [n_atoms][4] KB energies (0 where absent)
   const int* pt_ptr = nullptr;       // [N + 1] per grid point: entries covering it
   const int* pt_ent = nullptr;       // [nnz]
@@ -87,6 +86,7 @@ struct StageArgs {
   const double* efield;    // [3] length gauge field, or nullptr
   const double2* Eu;       // [n_orb_tot][n_atoms][4] E_p u_p, or nullptr
   const double2* phA;      // [S] exp(i A.x/c) for this step
+  const double* ent_beta;  // [S][4] beta_p
   NLTables nl;
   Geometry g;
   double lap[3][5];        // -1/2 c_m / h_mu^2
@@ -130,7 +130,9 @@ struct ProjArgs {
   int N;
   int n_orb, n_orb_tot;
   double dV;
-  int moments;             // 0: stage projections -> Eu; 1: all 16 columns -> proj
+  const double* ent_beta;  // [S][4] beta_p
+  const double* ent_x;     // [S][3] positions (moments)
+  int moments;             // 0: stage projections -> Eu; 1: current and energy -> jnl
   double2* Eu;             // [n_orb_tot][n_atoms][4]
   double* jnl;             // moments: [n_orb_tot][4]: nonlocal current (3) and energy
   // stage mode with disjoint spheres: the nonlocal term of the stage that
@@ -138,7 +140,6 @@ struct ProjArgs {
   // is first added to u at the sphere points (in place) and the sum projected;
   // Eu_prev = nullptr: u is complete
   const double2* Eu_prev;  // [n_orb_tot][n_atoms][4]
-  const double* ent_beta;  // [S][4] beta_p
   double tau, tau_re;
 };
 
@@ -182,7 +183,7 @@ struct MggaArgs {
 template <typename T>
 hipError_t launch_stage(int mode, int bc, const StageArgs<T>& a, hipStream_t s);
 template <typename T>
-hipError_t launch_nl_addback(const StageArgs<T>& a, const int* ents, int n_ents, int n_orb_tot, hipStream_t s);
+hipError_t launch_nl_addback(const StageArgs<T>& a, const int4* chunks, int n_chunks, int n_orb_tot, hipStream_t s);
 template <typename T>
 hipError_t launch_observe(int bc, const ObserveArgs<T>& a, hipStream_t s);
 template <typename T>

@@ -1,283 +1,256 @@
-// Kleinman-Bylander projections on the matrix cores (Sec. 3.1, separable
-// nonlocal pseudopotential; Sec. 4.1, phase exp(-i kappa.x) for gauge
-// invariance):
+// Kleinman-Bylander projections (Sec. 3.1, separable nonlocal
+// pseudopotential; Sec. 4.1, phase exp(-i kappa.x) for gauge invariance):
 //
-//   u_{o,a,p}^{(m)} = h^3 sum_{e in sphere(a)} B[e][4p+m] exp(i kappa_k . x_e) t_o(idx_e)
+//   u_{o,a,p}^{(m)} = h^3 sum_{e in sphere(a)} beta_p(x_e) (1, x, y, z)[m] exp(i kappa_k . x_e) t_o(idx_e)
 //
-// with B[e][4p+m] = beta_p(x_e) * (1, x, y, z)[m]. For one atom and a group of
-// eight orbitals this is a real product D[16 x 16] = A[16 x K] B[K x 16]
-// where row 2j/2j+1 of A holds the real/imaginary part of the phase-shifted
-// gathered value of orbital j, K runs over the sphere entries in steps of 4,
-// and column 4p+m of B is the moment m of projector p. One wavefront
-// accumulates D with v_mfma_f64_16x16x4f64 (FP64 inputs: FP32 orbitals are
-// upcast, so the inner products stay FP64 in the mixed-precision path).
+// for every orbital o, atom a and projector p: m = 0 for the nonlocal term of
+// a stage (k_project_eu), all four for the current and energy (k_project).
 //
-// Lane layout of v_mfma_f64_16x16x4f64 (checked by a GPU unit test):
-//   A: lane l holds A[l % 16][l / 16];  B: lane l holds B[l / 16][l % 16];
-//   D: register r of lane l holds D[l / 16 + 4 r][l % 16], r = 0..3.
+// What bounds them is the vector memory path: a sphere is some fifty runs of
+// about seven points in each orbital, and every point needs its table row
+// (index, two phases, four beta) besides. So a lane holds one sphere entry:
+// its table row is loaded once for the kGroup orbitals of the wavefront, 64
+// consecutive entries are gathered per load, and each lane keeps FP64 sums of
+// its entries for every (orbital, projector) that one lane exchange per value
+// adds up at the end. Laid out as a product for the FP64 matrix unit, four
+// entries of eight orbitals at a time, the tables were loaded once per four
+// entries and half of the lanes held copies (1.48 M vector loads for the 96
+// orbitals and 256 atoms of a 96^3 cluster, each of 16 cycles: the whole of
+// its 74 us).
+//   96^3, 96 orbitals, 256 atoms, complex FP32: projection 74 -> 55 us, with the
+//   previous stage's term added 136 -> 84 us (its lines alone are 230 MB), moments
+//   69 -> 60 us. 36 x 40 x 27, 96 orbitals, 8 atoms, complex128: 6.3 -> 4.8, 13.1 ->
+//   6.4, 8.9 -> 6.0 us.
 //
-// Stage mode needs only m = 0, so it runs on the four-block FP64 MFMA
-// v_mfma_f64_4x4x4f64 instead (k_project_eu): block b holds orbitals 2b and
-// 2b + 1 of the group (rows: real and imaginary part of each), its four
-// columns are the four projectors, and every product it forms is used.
-// Lane layout of v_mfma_f64_4x4x4f64 (checked by a GPU unit test), with
-// b = (l >> 2) & 3:
-//   A: lane l holds A_b[l & 3][l >> 4];  B: lane l holds B_b[l >> 4][l & 3];
-//   D: lane l holds D_b[l >> 4][l & 3].
-// Moment mode writes, per orbital and atom, the nonlocal current
+// k_project writes, per orbital and atom, the nonlocal current
 // sum_p 2 E_p Im(conj(v_p) u_p) (v = moments 1..3) and the nonlocal energy
 // sum_p E_p |u_p|^2 into a partial table [orbital][atom][4]; k_moment_reduce
-// then sums the atoms of each orbital in a fixed order. Both modes run one wavefront
-// per (orbital group, atom).
+// then sums the atoms of each orbital in a fixed order.
 #include "internal.h"
+#include "lanes.h"
 
 namespace td {
 
-typedef double d4_t __attribute__((ext_vector_type(4)));
-
-// SPLIT = 1: four (group, atom) items per workgroup, one per wavefront.
-// SPLIT = 4 (few items: small cells, or few orbitals over many atoms): one
-// item per workgroup, its sphere entries dealt out to the four wavefronts in
-// turn, the four partial tiles summed in wavefront order through LDS, so a
-// wavefront's serial loop over the sphere is a quarter as long.
-template <typename T, int SPLIT>
-__global__ __launch_bounds__(256) void k_project(ProjArgs<T> a) {
-  using T2 = typename Vec2<T>::type;
-  __shared__ double dpart[SPLIT > 1 ? SPLIT : 1][4][64];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int n_groups = (a.n_orb_tot + 7) / 8;
-  const int n_atoms = a.nl.n_atoms;
-  const int item = SPLIT > 1 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
-  const int sub = SPLIT > 1 ? wave : 0;
-  const int total = n_groups * n_atoms;
-  if (item >= total) return;  // uniform over the wavefront (over the workgroup when split)
-  const int grp = item / n_atoms;
-  const int at0 = item - grp * n_atoms;
-  const int at1 = at0 + 1;
-  const int row = lane & 15;   // A row / B and D column
-  const int kk = lane >> 4;    // A column / B row / D row block
-  const int o_row = grp * 8 + (row >> 1);
-  const int part = row & 1;
-  const bool row_ok = o_row < a.n_orb_tot;
-  const int k_row = row_ok ? o_row / a.n_orb : 0;
-  const T2* __restrict__ urow = a.u + (size_t)(row_ok ? o_row : 0) * a.N;
-  const double2* __restrict__ phk = a.nl.phk + (size_t)k_row * a.nl.n_ent;
-
-  const int j = row;
-  const int p = j >> 2, m = j & 3;
-  double acc_moment[4] = {0.0, 0.0, 0.0, 0.0};  // moment mode: per owned orbital
-
-  for (int at = at0; at < at1; ++at) {
-    const int e0 = a.nl.atom_start[at], e1 = a.nl.atom_start[at + 1];
-    d4_t acc = {0.0, 0.0, 0.0, 0.0};
-    // kPipe k steps at a time, loads first (as in k_project_eu): steps past
-    // the sphere load its last entry and use 0
-    constexpr int kPipe = 4;
-    const int step = 4 * SPLIT;
-    for (int eb = e0 + 4 * sub; eb < e1; eb += step * kPipe) {
-      bool ein[kPipe];
-      int idx[kPipe];
-      double bv[kPipe];
-      double2 p1[kPipe], p2[kPipe];
-#pragma unroll
-      for (int u = 0; u < kPipe; ++u) {
-        const int e = eb + step * u + kk;
-        ein[u] = e < e1;
-        const int ec = min(e, e1 - 1);
-        bv[u] = a.nl.ent_B[(size_t)ec * kCols + j];
-        idx[u] = a.nl.ent_idx[ec];
-        p1[u] = phk[ec];
-        p2[u] = a.phA[ec];
-      }
-      T2 uv[kPipe];
-#pragma unroll
-      for (int u = 0; u < kPipe; ++u) uv[u] = urow[idx[u]];
-#pragma unroll
-      for (int u = 0; u < kPipe; ++u) {
-        const double pr = p1[u].x * p2[u].x - p1[u].y * p2[u].y;
-        const double pim = p1[u].x * p2[u].y + p1[u].y * p2[u].x;
-        const double ur = (double)uv[u].x, ui = (double)uv[u].y;
-        const double avv = part ? (pr * ui + pim * ur) : (pr * ur - pim * ui);
-        const double av = (ein[u] && row_ok) ? avv : 0.0;
-        const double b = ein[u] ? bv[u] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, b, acc, 0, 0, 0);
-      }
-    }
-    if (SPLIT > 1) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dpart[wave][r][lane] = acc[r];
-      __syncthreads();
-      if (wave != 0) return;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double v = dpart[0][r][lane];
-#pragma unroll
-        for (int w = 1; w < SPLIT; ++w) v += dpart[w][r][lane];
-        acc[r] = v;
-      }
-    }
-    // acc[r] = D[kk + 4r][j]: orbital (kk >> 1) + 2r of the group, real part
-    // for even kk, imaginary part for odd kk; the partner lane l ^ 16 holds
-    // the other part of the same orbital.
-    const double E = a.nl.atom_E[at * kMaxProj + p];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const double mine = a.dV * acc[r];
-      const double other = __shfl_xor(mine, 16, 64);
-      const double ure = (kk & 1) ? other : mine;
-      const double uim = (kk & 1) ? mine : other;
-      const int o = grp * 8 + (kk >> 1) + 2 * r;
-      if (!a.moments) {
-        if (m == 0 && (kk & 1) == 0 && o < a.n_orb_tot)
-          a.Eu[((size_t)o * n_atoms + at) * kMaxProj + p] = make_double2(E * ure, E * uim);
-      } else {
-        // u_p lives in the lane of column 4p (same row block): fetch it
-        const int src = kk * 16 + 4 * p;
-        const double u0r = __shfl(ure, src, 64);
-        const double u0i = __shfl(uim, src, 64);
-        if (m == 0)
-          acc_moment[r] += E * (u0r * u0r + u0i * u0i);           // E_p |u_p|^2
-        else
-          acc_moment[r] += 2.0 * E * (ure * u0i - uim * u0r);     // 2 E_p Im(conj(v) u)
-      }
-    }
-  }
-  if (a.moments) {
-    double* part = reinterpret_cast<double*>(a.Eu);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      // sum over p: lanes 4p+m of the same row block (xor over bits 2 and 3)
-      double v = acc_moment[r];
-      v += __shfl_xor(v, 4, 64);
-      v += __shfl_xor(v, 8, 64);
-      const int o = grp * 8 + (kk >> 1) + 2 * r;
-      if (p == 0 && (kk & 1) == 0 && o < a.n_orb_tot) {
-        const int slot = (m == 0) ? 3 : m - 1;
-        part[((size_t)o * n_atoms + at0) * 4 + slot] = v;
-      }
-    }
-  }
+// The work of one wavefront: atom at, kGroup orbitals o0 .. o0 + ng - 1 of one
+// k-point. SPLIT = 1: four items per workgroup, one per wavefront. SPLIT = 4
+// (few items: small cells, or few orbitals over many atoms): one item per
+// workgroup, its sphere entries dealt out to the four wavefronts in turn, so
+// that a wavefront's serial loop over the sphere is a quarter as long. Items
+// of one atom are neighbours and stay on one XCD: they share its table rows.
+struct ProjItem {
+  int at, k, o0, ng, sub;
+  bool valid;
+};
+template <int SPLIT, int G>
+__device__ __forceinline__ ProjItem proj_item(int n_orb, int n_orb_tot, int n_atoms) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int bid = xcd_block((int)blockIdx.x, (int)gridDim.x);
+  const int item = SPLIT > 1 ? bid : bid * 4 + wave;
+  const int per_k = (n_orb + G - 1) / G;
+  const int n_groups = n_orb_tot / n_orb * per_k;
+  ProjItem w;
+  w.valid = item < n_groups * n_atoms;
+  w.at = item / n_groups;
+  const int grp = item - w.at * n_groups;
+  w.k = grp / per_k;
+  const int j0 = (grp - w.k * per_k) * G;
+  w.o0 = w.k * n_orb + j0;
+  w.ng = min(G, n_orb - j0);
+  w.sub = SPLIT > 1 ? wave : 0;
+  return w;
 }
 
-// Stage mode: E_p u_p of every (orbital, atom, projector) on the four-block
-// MFMA. One wavefront per (group of eight orbitals, atom); SPLIT as in
-// k_project.
+constexpr int kGroup = 4;     // orbitals of a wavefront: 32 sums
+constexpr int kMomGroup = 2;  // with all four moments: 64 sums
+
+// Stage mode: E_p u_p of every (orbital, atom, projector). ADD: the previous
+// stage's nonlocal term is first added at the sphere points (in place), with
+// the arithmetic of k_nl_addback (FP64 sum, one rounding to the stage
+// precision); with disjoint spheres an (orbital, point) belongs to one lane.
 template <typename T, int SPLIT, bool ADD>
 __global__ __launch_bounds__(256) void k_project_eu(ProjArgs<T> a) {
   using T2 = typename Vec2<T>::type;
-  __shared__ double dpart[SPLIT > 1 ? SPLIT : 1][64];
+  constexpr int G = kGroup;
+  __shared__ double part[SPLIT][G * 8];
+  const ProjItem w = proj_item<SPLIT, G>(a.n_orb, a.n_orb_tot, a.nl.n_atoms);
+  if (!w.valid) return;  // uniform over the wavefront (over the workgroup when split)
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int n_groups = (a.n_orb_tot + 7) / 8;
   const int n_atoms = a.nl.n_atoms;
-  const int item = SPLIT > 1 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
-  const int sub = SPLIT > 1 ? wave : 0;
-  if (item >= n_groups * n_atoms) return;  // uniform over the wavefront (the workgroup when split)
-  const int grp = item / n_atoms;
-  const int at = item - grp * n_atoms;
-  const int blk = (lane >> 2) & 3;
-  // A operand: row i = lane & 3 of block blk is orbital 2 blk + (i >> 1),
-  // real (i even) or imaginary part; column k = lane >> 4 is entry eb + k
-  const int i_a = lane & 3, k_op = lane >> 4;
-  const int o_a = grp * 8 + 2 * blk + (i_a >> 1);
-  const int part = i_a & 1;
-  const bool row_ok = o_a < a.n_orb_tot;
-  const int k_a = row_ok ? o_a / a.n_orb : 0;
-  T2* __restrict__ urow = const_cast<T2*>(a.u) + (size_t)(row_ok ? o_a : 0) * a.N;
-  const double2* __restrict__ phk = a.nl.phk + (size_t)k_a * a.nl.n_ent;
-  // B operand: column j = lane & 3 is projector j (its m = 0 column), row k_op
-  const int j_b = lane & 3;
-  // the previous stage's E_p u_p of this lane's orbital and the wavefront's atom
-  // ADD: a.Eu_prev is set and the previous stage's nonlocal term is added
-  constexpr bool addback = ADD;
-  double2 ep[kMaxProj];
-#pragma unroll
-  for (int p = 0; p < kMaxProj; ++p) {
-    ep[p] = make_double2(0.0, 0.0);
-    if (addback && row_ok) ep[p] = a.Eu_prev[((size_t)o_a * n_atoms + at) * kMaxProj + p];
-  }
+  T2* __restrict__ u0 = const_cast<T2*>(a.u) + (size_t)w.o0 * a.N;
+  const double2* __restrict__ phk = a.nl.phk + (size_t)w.k * a.nl.n_ent;
+  const double2* __restrict__ beta = reinterpret_cast<const double2*>(a.ent_beta);
+  const uniform_ptr<int> start = (uniform_ptr<int>)a.nl.atom_start;
+  const int e0 = start[w.at], e1 = start[w.at + 1];
+  const uniform_ptr<double> ep =
+      (uniform_ptr<double>)(ADD ? reinterpret_cast<const double*>(a.Eu_prev) : nullptr);
 
-  const int e0 = a.nl.atom_start[at], e1 = a.nl.atom_start[at + 1];
-  double acc = 0.0;
-  // kPipe k steps at a time: their table and index loads are issued first,
-  // then their gathers, then their products, so the gathers of a group are in
-  // flight together. Steps past the sphere load its last entry and use 0 (the
-  // products then add exact zeros). With the add-back, the points of a group
-  // are distinct and the wavefront's own, so its loads may precede its stores.
-  constexpr int kPipe = 4;
-  const int step = 4 * SPLIT;
-  for (int eb = e0 + 4 * sub; eb < e1; eb += step * kPipe) {
-    bool ein[kPipe];
-    int ec[kPipe], idx[kPipe];
-    double bv[kPipe];
-    double2 p1[kPipe], p2[kPipe];
+  double acc[G][8];
 #pragma unroll
-    for (int u = 0; u < kPipe; ++u) {
-      const int e = eb + step * u + k_op;
-      ein[u] = e < e1;
-      ec[u] = min(e, e1 - 1);
-      bv[u] = a.nl.ent_B[(size_t)ec[u] * kCols + 4 * j_b];
-      idx[u] = a.nl.ent_idx[ec[u]];
-      p1[u] = phk[ec[u]];
-      p2[u] = a.phA[ec[u]];
-    }
-    T2 uv[kPipe];
+  for (int g = 0; g < G; ++g)
 #pragma unroll
-    for (int u = 0; u < kPipe; ++u) uv[u] = urow[idx[u]];
-    double bt[kPipe][kMaxProj];
+    for (int i = 0; i < 8; ++i) acc[g][i] = 0.0;
+
+  const int eb0 = e0 + 64 * w.sub;
+  // the next entries' index is loaded an iteration ahead of their gathers;
+  // lanes past the sphere repeat its last entry with beta = 0
+  int idx = eb0 < e1 ? a.nl.ent_idx[min(eb0 + lane, e1 - 1)] : 0;
+  for (int eb = eb0; eb < e1; eb += 64 * SPLIT) {
+    const int e = eb + lane;
+    const bool in = e < e1;
+    const int ec = min(e, e1 - 1);
+    T2 v[G];
 #pragma unroll
-    for (int u = 0; u < kPipe; ++u)
+    for (int g = 0; g < G; ++g) v[g] = u0[(size_t)min(g, w.ng - 1) * a.N + idx];
+    const int next = a.nl.ent_idx[min(e + 64 * SPLIT, e1 - 1)];
+    const double2 p1 = phk[ec], p2 = a.phA[ec];
+    const double2 b01 = beta[2 * (size_t)ec], b23 = beta[2 * (size_t)ec + 1];
+    const double b[kMaxProj] = {in ? b01.x : 0.0, in ? b01.y : 0.0, in ? b23.x : 0.0, in ? b23.y : 0.0};
+    const double pr = p1.x * p2.x - p1.y * p2.y;
+    const double pim = p1.x * p2.y + p1.y * p2.x;
 #pragma unroll
-      for (int p = 0; p < kMaxProj; ++p) bt[u][p] = addback ? a.ent_beta[(size_t)ec[u] * kMaxProj + p] : 0.0;
-#pragma unroll
-    for (int u = 0; u < kPipe; ++u) {
-      const bool use = ein[u] && row_ok;
-      const double pr = p1[u].x * p2[u].x - p1[u].y * p2[u].y;
-      const double pim = p1[u].x * p2[u].y + p1[u].y * p2[u].x;
-      T2 v = uv[u];
-      if (addback) {
-        // the previous stage's nonlocal term at this point, with the same
-        // arithmetic as k_nl_addback (FP64 sum, one rounding to the stage
-        // precision); with disjoint spheres this (orbital, point) belongs to
-        // this wavefront alone, and the lane holding the real part writes it
+    for (int g = 0; g < G; ++g) {
+      if (ADD) {
+        const uniform_ptr<double> eg = ep + ((size_t)(w.o0 + min(g, w.ng - 1)) * n_atoms + w.at) * (2 * kMaxProj);
         double sr = 0.0, si = 0.0;
 #pragma unroll
         for (int p = 0; p < kMaxProj; ++p) {
-          sr += bt[u][p] * ep[p].x;
-          si += bt[u][p] * ep[p].y;
+          sr += b[p] * eg[2 * p];
+          si += b[p] * eg[2 * p + 1];
         }
         const double hr = pr * sr + pim * si, hi = pr * si - pim * sr;
-        v.x += (T)(a.tau * hi + a.tau_re * hr);
-        v.y += (T)(-a.tau * hr + a.tau_re * hi);
-        if (use && part == 0) urow[idx[u]] = v;
+        v[g].x += (T)(a.tau * hi + a.tau_re * hr);
+        v[g].y += (T)(-a.tau * hr + a.tau_re * hi);
+        if (in && g < w.ng) u0[(size_t)g * a.N + idx] = v[g];
       }
-      const double ur = (double)v.x, ui = (double)v.y;
-      const double avv = part ? (pr * ui + pim * ur) : (pr * ur - pim * ui);
-      const double av = use ? avv : 0.0;
-      const double b = ein[u] ? bv[u] : 0.0;
-      acc = __builtin_amdgcn_mfma_f64_4x4x4f64(av, b, acc, 0, 0, 0);
+      const double ur = (double)v[g].x, ui = (double)v[g].y;
+      const double wr = pr * ur - pim * ui, wi = pr * ui + pim * ur;
+#pragma unroll
+      for (int p = 0; p < kMaxProj; ++p) {
+        acc[g][2 * p] += b[p] * wr;
+        acc[g][2 * p + 1] += b[p] * wi;
+      }
+    }
+    idx = next;
+  }
+  // lane l < 32 takes value l of the 32 (orbital l / 8, projector, part)
+  double s[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = acc[2 * h + (i >> 3)][i & 7];
+    s[h] = wave_sum16(v, lane);
+  }
+  int l = (lane >> 2) + 16 * (lane & 1);
+  double tot = (lane & 1) ? s[1] : s[0];
+  bool mine = (lane & 2) == 0;
+  if (SPLIT > 1) {
+    if (mine) part[w.sub][l] = tot;
+    __syncthreads();
+    l = threadIdx.x;
+    mine = l < G * 8;
+    if (!mine) return;
+    tot = part[0][l];
+#pragma unroll
+    for (int j = 1; j < SPLIT; ++j) tot += part[j][l];
+  }
+  const int g = l >> 3, i = l & 7;
+  if (mine && g < w.ng)
+    reinterpret_cast<double*>(a.Eu)[((size_t)(w.o0 + g) * n_atoms + w.at) * (2 * kMaxProj) + i] =
+        a.nl.atom_E[w.at * kMaxProj + (i >> 1)] * (a.dV * tot);
+}
+
+// Moment mode: the current and energy partials of every (orbital, atom)
+template <typename T, int SPLIT>
+__global__ __launch_bounds__(256) void k_project(ProjArgs<T> a) {
+  using T2 = typename Vec2<T>::type;
+  constexpr int G = kMomGroup;
+  constexpr int V = 2 * kCols;  // sums per orbital: (projector, moment, part)
+  __shared__ double part[4][G * V];
+  const ProjItem w = proj_item<SPLIT, G>(a.n_orb, a.n_orb_tot, a.nl.n_atoms);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n_atoms = a.nl.n_atoms;
+  if (w.valid) {
+    const T2* __restrict__ u0 = a.u + (size_t)w.o0 * a.N;
+    const double2* __restrict__ phk = a.nl.phk + (size_t)w.k * a.nl.n_ent;
+    const double2* __restrict__ beta = reinterpret_cast<const double2*>(a.ent_beta);
+    const uniform_ptr<int> start = (uniform_ptr<int>)a.nl.atom_start;
+    const int e0 = start[w.at], e1 = start[w.at + 1];
+    double acc[G][V];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int i = 0; i < V; ++i) acc[g][i] = 0.0;
+    const int eb0 = e0 + 64 * w.sub;
+    int idx = eb0 < e1 ? a.nl.ent_idx[min(eb0 + lane, e1 - 1)] : 0;
+    for (int eb = eb0; eb < e1; eb += 64 * SPLIT) {
+      const int e = eb + lane;
+      const bool in = e < e1;
+      const int ec = min(e, e1 - 1);
+      T2 v[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) v[g] = u0[(size_t)min(g, w.ng - 1) * a.N + idx];
+      const int next = a.nl.ent_idx[min(e + 64 * SPLIT, e1 - 1)];
+      const double2 p1 = phk[ec], p2 = a.phA[ec];
+      const double2 b01 = beta[2 * (size_t)ec], b23 = beta[2 * (size_t)ec + 1];
+      const double x[3] = {a.ent_x[3 * (size_t)ec], a.ent_x[3 * (size_t)ec + 1], a.ent_x[3 * (size_t)ec + 2]};
+      const double b[kMaxProj] = {in ? b01.x : 0.0, in ? b01.y : 0.0, in ? b23.x : 0.0, in ? b23.y : 0.0};
+      const double pr = p1.x * p2.x - p1.y * p2.y;
+      const double pim = p1.x * p2.y + p1.y * p2.x;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const double ur = (double)v[g].x, ui = (double)v[g].y;
+        const double wr = pr * ur - pim * ui, wi = pr * ui + pim * ur;
+#pragma unroll
+        for (int m = 0; m < kMoments; ++m) {
+          const double mr = m ? x[m - 1] * wr : wr, mi = m ? x[m - 1] * wi : wi;
+#pragma unroll
+          for (int p = 0; p < kMaxProj; ++p) {
+            acc[g][2 * (p * kMoments + m)] += b[p] * mr;
+            acc[g][2 * (p * kMoments + m) + 1] += b[p] * mi;
+          }
+        }
+      }
+      idx = next;
+    }
+    // lane l takes value l of the 64 (orbital, projector, moment, part)
+    double tot = 0.0;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      double v[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = acc[h >> 1][16 * (h & 1) + i];
+      const double s = wave_sum16(v, lane);
+      tot = (lane & 3) == h ? s : tot;
+    }
+    part[wave][16 * (lane & 3) + (lane >> 2)] = tot;
+  }
+  __syncthreads();
+  // thread (item, orbital, slot): the item's sums over its SPLIT wavefronts
+  constexpr int items = 4 / SPLIT;
+  const int t = threadIdx.x & 63;
+  if (!w.valid || t >= G * 4 || (SPLIT > 1 && wave != 0)) return;
+  const int g = t >> 2, slot = t & 3;
+  if (g >= w.ng) return;
+  const int first = items > 1 ? wave : 0;
+  auto sum = [&](int i) -> double {
+    double s = part[first][g * V + i];
+    for (int j = 1; j < SPLIT; ++j) s += part[j][g * V + i];
+    return a.dV * s;
+  };
+  double r = 0.0;
+#pragma unroll
+  for (int p = 0; p < kMaxProj; ++p) {
+    const double E = a.nl.atom_E[w.at * kMaxProj + p];
+    const double ur = sum(2 * p * kMoments), ui = sum(2 * p * kMoments + 1);
+    if (slot == 3) {
+      r += E * (ur * ur + ui * ui);
+    } else {
+      const double vr = sum(2 * (p * kMoments + slot + 1)), vi = sum(2 * (p * kMoments + slot + 1) + 1);
+      r += 2.0 * E * (vr * ui - vi * ur);  // 2 E_p Im(conj(v) u)
     }
   }
-  if (SPLIT > 1) {
-    dpart[wave][lane] = acc;
-    __syncthreads();
-    if (wave != 0) return;
-    double v = dpart[0][lane];
-#pragma unroll
-    for (int w = 1; w < SPLIT; ++w) v += dpart[w][lane];
-    acc = v;
-  }
-  // acc = D_blk[i][j], i = lane >> 4: orbital 2 blk + (i >> 1), real part for
-  // even i; lane ^ 16 holds the other part of the same orbital and projector
-  const double mine = a.dV * acc;
-  const double other = __shfl_xor(mine, 16, 64);
-  const int i_d = lane >> 4;
-  const int o = grp * 8 + 2 * blk + (i_d >> 1);
-  if ((i_d & 1) == 0 && o < a.n_orb_tot) {
-    const double E = a.nl.atom_E[at * kMaxProj + j_b];
-    a.Eu[((size_t)o * n_atoms + at) * kMaxProj + j_b] = make_double2(E * mine, E * other);
-  }
+  reinterpret_cast<double*>(a.Eu)[((size_t)(w.o0 + g) * n_atoms + w.at) * 4 + slot] = r;
 }
 
 // jnl[o][slot] = sum over atoms of the moment-mode partials: a wavefront per
@@ -310,36 +283,25 @@ __global__ __launch_bounds__(256) void k_moment_reduce(const double* __restrict_
 // projection) as its [orbital][atom][4] partial table.
 template <typename T>
 hipError_t launch_project(const ProjArgs<T>& a, hipStream_t s) {
-  const int n_groups = (a.n_orb_tot + 7) / 8;
-  const long total = (long)n_groups * a.nl.n_atoms;
+  const int G = a.moments ? kMomGroup : kGroup;
+  const long total = (long)(a.n_orb_tot / a.n_orb) * ((a.n_orb + G - 1) / G) * a.nl.n_atoms;
   if (total == 0) return hipSuccess;
-  // up to 64 items per CU: split each item over a workgroup, so that there
-  // are enough wavefronts to hide the latency of the sphere gathers and each
-  // serial chain is a quarter as long (the 96^3 cluster, 8 orbital groups x
-  // 256 atoms: 0.075 -> 0.048 ms per projection; the 20^3 cell with 512
-  // k-points on the per-stage path, 1024 groups x 8 atoms: 0.172 -> 0.140 ms)
+  // split an item over a workgroup while whole items would leave wavefront
+  // slots free (1024 SIMDs of at least four)
+  const bool split = total < 4096;
+  const dim3 grid((unsigned)(split ? total : (total + 3) / 4)), block(256);
   if (!a.moments) {
     const bool add = a.Eu_prev != nullptr;
-    if (total < 16384) {
-      if (add)
-        hipLaunchKernelGGL((k_project_eu<T, 4, true>), dim3((unsigned)total), dim3(256), 0, s, a);
-      else
-        hipLaunchKernelGGL((k_project_eu<T, 4, false>), dim3((unsigned)total), dim3(256), 0, s, a);
-    } else {
-      const dim3 grid((unsigned)((total + 3) / 4));
-      if (add)
-        hipLaunchKernelGGL((k_project_eu<T, 1, true>), grid, dim3(256), 0, s, a);
-      else
-        hipLaunchKernelGGL((k_project_eu<T, 1, false>), grid, dim3(256), 0, s, a);
-    }
+    if (split && add) hipLaunchKernelGGL((k_project_eu<T, 4, true>), grid, block, 0, s, a);
+    else if (split) hipLaunchKernelGGL((k_project_eu<T, 4, false>), grid, block, 0, s, a);
+    else if (add) hipLaunchKernelGGL((k_project_eu<T, 1, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_project_eu<T, 1, false>), grid, block, 0, s, a);
     return hipGetLastError();
   }
-  if (total < 16384)
-    hipLaunchKernelGGL((k_project<T, 4>), dim3((unsigned)total), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_project<T, 1>), dim3((unsigned)((total + 3) / 4)), dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !a.moments) return e;
+  if (split) hipLaunchKernelGGL((k_project<T, 4>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_project<T, 1>), grid, block, 0, s, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_moment_reduce, dim3((unsigned)((a.n_orb_tot + 3) / 4)), dim3(256), 0, s,
                      reinterpret_cast<const double*>(a.Eu), a.nl.n_atoms, a.n_orb_tot, a.jnl);
   return hipGetLastError();
@@ -348,9 +310,13 @@ hipError_t launch_project(const ProjArgs<T>& a, hipStream_t s) {
 template hipError_t launch_project<double>(const ProjArgs<double>&, hipStream_t);
 template hipError_t launch_project<float>(const ProjArgs<float>&, hipStream_t);
 
+typedef double d4_t __attribute__((ext_vector_type(4)));
+
 // ---------------------------------------------------------------------------
-// Unit check of the MFMA lane layout: D = A B for A [16 x 4], B [4 x 16]
-// given row-major on the device; used only by a test entry point.
+// Unit check of the lane layout of v_mfma_f64_16x16x4f64: D = A B for A [16 x 4],
+// B [4 x 16] given row-major on the device; used only by a test entry point.
+//   A: lane l holds A[l % 16][l / 16];  B: lane l holds B[l / 16][l % 16];
+//   D: register r of lane l holds D[l / 16 + 4 r][l % 16], r = 0..3.
 __global__ void k_mfma_layout(const double* A, const double* B, double* D) {
   const int l = threadIdx.x;
   const double av = A[(l % 16) * 4 + l / 16];
