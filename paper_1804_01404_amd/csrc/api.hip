@@ -324,15 +324,18 @@ tddft_status enqueue_density_potential(tddft_ctx* c, bool with_finish = false) {
   const int N = (int)c->N;
   const bool mgga = is_mgga(c);
   const bool one = c->rho_nchunks == 1;
-  const TailCell tail = tail_cell(c);
+  TailCell tail = tail_cell(c);
   const bool planes = c->potential_set && poisson_planes(c->g.periodic, c->cfg.hartree, c->g.n1, c->g.n2);
   if (mgga) {
-    if (with_finish) LAUNCH(launch_finish(tail, 1, c->stream), "finish");
     // rho and the kinetic energy density with kappa at the orbitals' time
     LAUNCH(launch_rho_tau_partial<T>(as2<T>(c->W), c->kw_d, c->kappaJ, mgga_args(c), c->rho_chunk,
                                      one ? c->rho : c->rho_part, one ? c->tau : c->tau_part, c->stream),
            "rho_tau_partial");
-    if (!one) LAUNCH(launch_rho_reduce(c->tau_part, c->rho_nchunks, N, c->tau, c->stream), "tau_reduce");
+    if (!one)
+      LAUNCH(launch_rho_tau_reduce(tail, N, c->tau_part, c->tau, with_finish ? 1 : 0, c->stream), "rho_tau_reduce");
+    else if (with_finish)
+      LAUNCH(launch_finish(tail, 1, c->stream), "finish");
+    tail.nchunks = 1;  // rho is complete
   } else {
     LAUNCH(launch_density<T>(tail, N, with_finish ? 1 : 0, c->stream), "density");
   }
@@ -349,7 +352,7 @@ tddft_status enqueue_density_potential(tddft_ctx* c, bool with_finish = false) {
     LAUNCH(launch_poisson_inverse(tail, n1, n2, n3, c->cfg.xc, c->vx_mgga, c->stream), "Poisson, inverse planes");
     return TDDFT_OK;
   }
-  if (!one) LAUNCH(launch_rho_reduce(c->rho_part, c->rho_nchunks, N, c->rho, c->stream), "rho_reduce");
+  if (!one && !mgga) LAUNCH(launch_rho_reduce(c->rho_part, c->rho_nchunks, N, c->rho, c->stream), "rho_reduce");
   if (!c->potential_set) return TDDFT_OK;
   if (c->cfg.hartree) {
     // rho fills the corner n1 x n2 x n3 of the M-box (all of it for a

@@ -306,6 +306,9 @@ hipError_t launch_poisson_inverse(const TailCell& t, int n1, int n2, int n3, int
 hipError_t launch_poisson_forward_group(const TailCell* tab, int ncells, int n1, int n2, int n3, hipStream_t s);
 hipError_t launch_poisson_inverse_group(const TailCell* tab, int ncells, int n1, int n2, int n3, int xc,
                                         hipStream_t s);
+// rho and tau from their chunks in one launch; with_finish: and the current
+hipError_t launch_rho_tau_reduce(const TailCell& t, int N, const double* tau_part, double* tau, int with_finish,
+                                 hipStream_t s);
 hipError_t launch_rho_reduce_group(const TailCell* tab, int ncells, int N, hipStream_t s);
 // as launch_fft_lines for every cell of tab (same box and lines)
 hipError_t launch_fft_lines_group(const TailCell* tab, int ncells, int M1, int M2, int M3, int axis, int sign,

@@ -148,7 +148,7 @@ hipError_t launch_batch_tables_out(const IOCell* io, int ncells, double* staged,
 }
 
 // ---------------------------------------------------------------- finish
-// One workgroup: I = -(1/Omega) sum_o f_o [p_o + kappaJ_k norm_o + jNL_o],
+// One workgroup (256 threads at work): I = -(1/Omega) sum_o f_o [p_o + kappaJ_k norm_o + jNL_o],
 // the orbital energy sum_o f_o [kin + kappaJ.p + 1/2 |kappaJ|^2 norm + vloc + E_NL],
 // and the occupied norm; f_o = 2 w_k. Thread t sums orbitals t, t + 256, ...
 // in order, then a fixed pairwise tree combines the threads. nanflag gets
@@ -161,7 +161,7 @@ __device__ __forceinline__ void finish_block(const TailCell& c, int bump, double
   const int n_tot = c.n_orb * c.n_k, tiles = c.tiles;
   double cx = 0, cy = 0, cz = 0, en = 0, nr = 0;
   int bad = 0;
-  for (int o = t; o < n_tot; o += kFinishThreads) {
+  for (int o = t < kFinishThreads ? t : n_tot; o < n_tot; o += kFinishThreads) {
     const int k = o / c.n_orb;
     double s[6] = {0, 0, 0, 0, 0, 0};
     for (int tl = 0; tl < tiles; ++tl)
@@ -185,11 +185,13 @@ __device__ __forceinline__ void finish_block(const TailCell& c, int bump, double
     if (!isfinite(s[0]) || !isfinite(s[1]) || !isfinite(s[2]) || !isfinite(s[3])) bad |= 1;
     else if (c.norm_tol > 0.0 && fabs(s[0] - 1.0) > c.norm_tol) bad |= 2;
   }
-  red[t][0] = cx;
-  red[t][1] = cy;
-  red[t][2] = cz;
-  red[t][3] = en;
-  red[t][4] = nr;
+  if (t < kFinishThreads) {
+    red[t][0] = cx;
+    red[t][1] = cy;
+    red[t][2] = cz;
+    red[t][3] = en;
+    red[t][4] = nr;
+  }
   __syncthreads();
   for (int w = kFinishThreads / 2; w > 0; w >>= 1) {
     if (t < w)
@@ -307,9 +309,9 @@ template hipError_t launch_density_group<float>(const TailCell*, int, int, int, 
 constexpr int kRedSlices = 16;
 
 __device__ __forceinline__ void rho_reduce_block(const double* __restrict__ part, int nchunks, int N,
-                                                 double* __restrict__ rho, double (*red)[64]) {
+                                                 double* __restrict__ rho, int b, double (*red)[64]) {
   const int i = threadIdx.x & 63, j = threadIdx.x >> 6;
-  const int p = blockIdx.x * 64 + i;
+  const int p = b * 64 + i;
   double acc = 0.0;
   if (p < N)
     for (int c = j; c < nchunks; c += kRedSlices) acc += part[(size_t)c * N + p];
@@ -325,7 +327,24 @@ __device__ __forceinline__ void rho_reduce_block(const double* __restrict__ part
 __global__ __launch_bounds__(64 * kRedSlices) void k_rho_reduce(const double* __restrict__ part, int nchunks,
                                                                 int N, double* __restrict__ rho) {
   __shared__ double red[kRedSlices][64];
-  rho_reduce_block(part, nchunks, N, rho, red);
+  rho_reduce_block(part, nchunks, N, rho, (int)blockIdx.x, red);
+}
+
+// rho and tau in one launch, with the current of the step on its first
+// workgroup (with_finish): three launches of 5 to 6 us on a 20^3 cell
+__global__ __launch_bounds__(64 * kRedSlices) void k_rho_tau_reduce(TailCell t, int N, const double* tau_part,
+                                                                    double* tau, int with_finish) {
+  __shared__ double red[kFinishThreads * 5];
+  int b = (int)blockIdx.x;
+  if (with_finish && b == 0) {
+    finish_block(t, 1, reinterpret_cast<double(*)[5]>(red));
+    return;
+  }
+  b -= with_finish;
+  const int nb = (N + 63) / 64;
+  const bool second = b >= nb;
+  rho_reduce_block(second ? tau_part : t.rho_part, t.nchunks, N, second ? tau : t.rho, second ? b - nb : b,
+                   reinterpret_cast<double(*)[64]>(red));
 }
 
 // the same for the cells of a group (cell blockIdx.y; cells with one chunk
@@ -334,7 +353,14 @@ __global__ __launch_bounds__(64 * kRedSlices) void k_rho_reduce_group(const Tail
   __shared__ double red[kRedSlices][64];
   const TailCell& t = tab[blockIdx.y];
   if (t.nchunks <= 1) return;
-  rho_reduce_block(t.rho_part, t.nchunks, N, t.rho, red);
+  rho_reduce_block(t.rho_part, t.nchunks, N, t.rho, (int)blockIdx.x, red);
+}
+
+hipError_t launch_rho_tau_reduce(const TailCell& t, int N, const double* tau_part, double* tau, int with_finish,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(k_rho_tau_reduce, dim3((unsigned)(with_finish + 2 * ((N + 63) / 64))), dim3(64 * kRedSlices), 0,
+                     s, t, N, tau_part, tau, with_finish);
+  return hipGetLastError();
 }
 
 hipError_t launch_rho_reduce_group(const TailCell* tab, int ncells, int N, hipStream_t s) {

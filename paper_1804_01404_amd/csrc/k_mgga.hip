@@ -34,60 +34,70 @@ __device__ __forceinline__ int nb(int j, int m, int n, int periodic) {
   return (q < 0 || q >= n) ? -1 : q;
 }
 
-// the 9-point first derivatives of a real grid field at (x, y, z)
-__device__ void grad_field(const double* f, const MggaArgs& a, int x, int y, int z, double out[3]) {
-  const Geometry& g = a.g;
-  const size_t row = (size_t)g.n1;
-  const size_t plane = (size_t)g.n1 * g.n2;
-  const size_t base_x = (size_t)z * plane + (size_t)y * row;
-  const size_t base_y = (size_t)z * plane + x;
-  const size_t base_z = (size_t)y * row + x;
-  double d[3] = {0.0, 0.0, 0.0};
-  for (int m = 1; m <= kHalf; ++m) {
-    const int xp = nb(x, m, g.n1, g.periodic), xm = nb(x, -m, g.n1, g.periodic);
-    const int yp = nb(y, m, g.n2, g.periodic), ym = nb(y, -m, g.n2, g.periodic);
-    const int zp = nb(z, m, g.n3, g.periodic), zm = nb(z, -m, g.n3, g.periodic);
-    const double fxp = xp >= 0 ? f[base_x + xp] : 0.0, fxm = xm >= 0 ? f[base_x + xm] : 0.0;
-    const double fyp = yp >= 0 ? f[base_y + yp * row] : 0.0, fym = ym >= 0 ? f[base_y + ym * row] : 0.0;
-    const double fzp = zp >= 0 ? f[base_z + zp * plane] : 0.0, fzm = zm >= 0 ? f[base_z + zm * plane] : 0.0;
-    d[0] += a.d1[0][m - 1] * (fxp - fxm);
-    d[1] += a.d1[1][m - 1] * (fyp - fym);
-    d[2] += a.d1[2][m - 1] * (fzp - fzm);
-  }
-  out[0] = d[0];
-  out[1] = d[1];
-  out[2] = d[2];
+// The 24 neighbours of a real grid field at (x, y, z), v[mu][m - 1][0 / 1] at
+// +m / -m: outside an isolated box the index points back at p and the value is
+// replaced by 0, so that no load hangs on a branch and they are all in flight
+// together.
+struct FieldNb {
+  double v[3][kHalf][2];
+};
+__device__ __forceinline__ FieldNb field_nb(const double* f, const Geometry& g, int x, int y, int z) {
+  const int n[3] = {g.n1, g.n2, g.n3}, js[3] = {x, y, z}, st[3] = {1, g.n1, g.n1 * g.n2};
+  const int p = (z * g.n2 + y) * g.n1 + x;
+  FieldNb r;
+  bool in[3][kHalf][2];
+#pragma unroll
+  for (int mu = 0; mu < 3; ++mu)
+#pragma unroll
+    for (int m = 1; m <= kHalf; ++m)
+#pragma unroll
+      for (int sgn = 0; sgn < 2; ++sgn) {
+        const int q = nb(js[mu], sgn ? -m : m, n[mu], g.periodic);
+        in[mu][m - 1][sgn] = q >= 0;
+        r.v[mu][m - 1][sgn] = f[q >= 0 ? p + (q - js[mu]) * st[mu] : p];
+      }
+#pragma unroll
+  for (int mu = 0; mu < 3; ++mu)
+#pragma unroll
+    for (int m = 0; m < kHalf; ++m)
+#pragma unroll
+      for (int sgn = 0; sgn < 2; ++sgn) r.v[mu][m][sgn] = in[mu][m][sgn] ? r.v[mu][m][sgn] : 0.0;
+  return r;
 }
 
-// the 9-point Laplacian of a real grid field at (x, y, z)
-__device__ double lap_field(const double* f, const MggaArgs& a, int x, int y, int z) {
-  const Geometry& g = a.g;
-  const size_t row = (size_t)g.n1;
-  const size_t plane = (size_t)g.n1 * g.n2;
-  const size_t p = (size_t)z * plane + (size_t)y * row + x;
-  const double f0 = f[p];
-  double s = (a.d2[0][0] + a.d2[1][0] + a.d2[2][0]) * f0;
-  const size_t base_x = (size_t)z * plane + (size_t)y * row;
-  const size_t base_y = (size_t)z * plane + x;
-  const size_t base_z = (size_t)y * row + x;
-  for (int m = 1; m <= kHalf; ++m) {
-    const int xp = nb(x, m, g.n1, g.periodic), xm = nb(x, -m, g.n1, g.periodic);
-    const int yp = nb(y, m, g.n2, g.periodic), ym = nb(y, -m, g.n2, g.periodic);
-    const int zp = nb(z, m, g.n3, g.periodic), zm = nb(z, -m, g.n3, g.periodic);
-    const double sx = (xp >= 0 ? f[base_x + xp] : 0.0) + (xm >= 0 ? f[base_x + xm] : 0.0);
-    const double sy = (yp >= 0 ? f[base_y + yp * row] : 0.0) + (ym >= 0 ? f[base_y + ym * row] : 0.0);
-    const double sz = (zp >= 0 ? f[base_z + zp * plane] : 0.0) + (zm >= 0 ? f[base_z + zm * plane] : 0.0);
-    s += a.d2[0][m] * sx + a.d2[1][m] * sy + a.d2[2][m] * sz;
+// the 9-point first derivatives
+__device__ __forceinline__ void grad_field(const FieldNb& f, const MggaArgs& a, double out[3]) {
+#pragma unroll
+  for (int mu = 0; mu < 3; ++mu) {
+    out[mu] = 0.0;
+#pragma unroll
+    for (int m = 0; m < kHalf; ++m) out[mu] += a.d1[mu][m] * (f.v[mu][m][0] - f.v[mu][m][1]);
   }
+}
+
+// the 9-point Laplacian (f0: the value at the point itself)
+__device__ __forceinline__ double lap_field(double f0, const FieldNb& f, const MggaArgs& a) {
+  double s = (a.d2[0][0] + a.d2[1][0] + a.d2[2][0]) * f0;
+#pragma unroll
+  for (int m = 0; m < kHalf; ++m)
+    s += a.d2[0][m + 1] * (f.v[0][m][0] + f.v[0][m][1]) + a.d2[1][m + 1] * (f.v[1][m][0] + f.v[1][m][1]) +
+         a.d2[2][m + 1] * (f.v[2][m][0] + f.v[2][m][1]);
   return s;
 }
 
 __device__ __forceinline__ double br_f(double x) { return x * exp(-2.0 * x / 3.0) / (x - 2.0); }
 
 // Root of x e^(-2x/3) / (x - 2) = y: (0, 2) for y < 0, (2, inf) for y > 0,
-// 2 for y = +-inf; bisection until the midpoint meets an end of the bracket.
+// 2 for y = +-inf. The function falls on both branches, so its value at a
+// trial point tells which end of the bracket to move; the trial point is
+// Newton's where that lies inside the bracket, of
+//   x e^(-2x/3) - y (x - 2)              for y of any but small positive value,
+//   ln(x / (x - 2)) - 2x/3 - ln y        below 1/10 (x > 3, nearly linear),
+// and the midpoint elsewhere and every eighth time, until Newton's step is so
+// short that the next is below the last bit. Some six rounds in place of bisection's fifty,
+// which were most of v_x's 18 us on a 20^3 grid.
 __device__ double br_root(double y) {
-  if (!isfinite(y)) return 2.0;
+  if (!(fabs(y) < 1e17)) return 2.0;  // x - 2 = 0.53 / y: below the last bit
   double lo, hi;
   if (y < 0.0) {
     lo = 0.0;
@@ -100,13 +110,21 @@ __device__ double br_root(double y) {
       hi *= 2.0;
     }
   }
-  for (int i = 0; i < 2200; ++i) {
-    const double mid = 0.5 * (lo + hi);
-    if (!(mid > lo && mid < hi)) break;
-    if (br_f(mid) > y)
-      lo = mid;
+  const bool tail = y > 0.0 && y < 0.1;
+  const double ly = tail ? log(y) : 0.0;
+  double x = 0.5 * (lo + hi);
+  for (int i = 1; i < 2200; ++i) {
+    if (!(x > lo && x < hi)) break;
+    const double e = exp(-2.0 * x / 3.0);
+    if (x * e / (x - 2.0) > y)
+      lo = x;
     else
-      hi = mid;
+      hi = x;
+    const double step = tail ? (log(x / (x - 2.0)) - 2.0 * x / 3.0 - ly) / (1.0 / x - 1.0 / (x - 2.0) - 2.0 / 3.0)
+                             : (x * e - y * (x - 2.0)) / ((1.0 - 2.0 * x / 3.0) * e - y);
+    const double xn = x - step;
+    if (fabs(step) <= 1e-9 * x && xn >= lo && xn <= hi) return xn;  // the next step would be its square
+    x = (i % 8 != 0 && xn > lo && xn < hi) ? xn : 0.5 * (lo + hi);
   }
   return 0.5 * (lo + hi);
 }
@@ -197,7 +215,14 @@ __global__ __launch_bounds__(256) void k_rho_tau_partial(const typename Vec2<T>:
 // orbital value is read once from memory (plus the 8 halo planes of the
 // slab) instead of 25 times. Per point the orbitals are summed in the same
 // order as above.
-constexpr int kTauSlab = 10;
+//
+// A workgroup waits for its plane's barrier and, at each orbital, for the
+// first loads of its queue, so what counts is how many share a compute unit:
+// slabs of at most five planes (as even as can be) put two workgroups of a
+// 20^3 cell of 1024 orbitals there, where ten planes left one: 59 -> 43 us
+// (complex FP32, 65 MB of orbitals).
+constexpr int kTauSlab = 5;
+__host__ __device__ inline int tau_slabs(int n3) { return (n3 + kTauSlab - 1) / kTauSlab; }
 
 template <typename T>
 __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::type* __restrict__ w,
@@ -211,9 +236,9 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
   const Geometry& g = a.g;
   const int n1 = g.n1, n2 = g.n2, n3 = g.n3, plane = n1 * n2;
   const size_t N = (size_t)plane * n3;
-  const int nsl = (n3 + kTauSlab - 1) / kTauSlab;
+  const int nsl = tau_slabs(n3), len = (n3 + nsl - 1) / nsl;
   const int cy = blockIdx.x / nsl, slab = blockIdx.x - cy * nsl;
-  const int z0 = slab * kTauSlab, z1 = min(n3, z0 + kTauSlab);
+  const int z0 = slab * len, z1 = min(n3, z0 + len);
   const int tid = threadIdx.x;
   const bool active = tid < plane;
   const int col = active ? tid : 0;
@@ -311,7 +336,7 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
 int rho_tau_chunk(const Geometry& g, int n_tot) {
   const int plane = g.n1 * g.n2;
   if (!(g.periodic && plane <= 1024)) return 64;
-  const int nsl = (g.n3 + kTauSlab - 1) / kTauSlab;
+  const int nsl = tau_slabs(g.n3);
   const long want = (long)n_tot * nsl / 1024;
   return (int)std::max(8L, std::min(64L, want));
 }
@@ -324,7 +349,7 @@ hipError_t launch_rho_tau_partial(const typename Vec2<T>::type* w, const double*
   const int nchunks = (a.g.n_orb * a.g.n_k + chunk - 1) / chunk;
   const int plane = a.g.n1 * a.g.n2;
   if (a.g.periodic && plane <= 1024) {
-    const int nsl = (a.g.n3 + kTauSlab - 1) / kTauSlab;
+    const int nsl = tau_slabs(a.g.n3);
     const size_t lds = (size_t)2 * plane * sizeof(typename Vec2<T>::type);
     hipLaunchKernelGGL((k_rho_tau_plane<T>), dim3((unsigned)(nchunks * nsl)), dim3(((plane + 63) / 64) * 64), lds,
                        s, w, kw, kappa, a, chunk, part_rho, part_tau);
@@ -357,7 +382,7 @@ __global__ __launch_bounds__(256) void k_mgga_gpart(const double* __restrict__ r
   if (p < N && rho[p] >= kRhoMin) {
     const int x = p % g.n1, y = (p / g.n1) % g.n2, z = p / (g.n1 * g.n2);
     double d[3];
-    grad_field(rho, a, x, y, z, d);
+    grad_field(field_nb(rho, g, x, y, z), a, d);
     v = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]) / rho[p];
   }
   red[threadIdx.x] = v;
@@ -369,11 +394,10 @@ __global__ __launch_bounds__(256) void k_mgga_gpart(const double* __restrict__ r
   if (threadIdx.x == 0) gpart[blockIdx.x] = red[0];
 }
 
-// one workgroup: g = dV / Omega * sum_b gpart[b] (thread t sums b = t, t + 256,
-// ... in order, then the tree); cval[0] = c, cval[1] = g
-__global__ __launch_bounds__(256) void k_mgga_c(const double* __restrict__ gpart, int nblocks, double scale,
-                                                int tb09, double* __restrict__ cval) {
-  __shared__ double red[256];
+// g = dV / Omega * sum_b gpart[b] by one workgroup (thread t sums b = t,
+// t + 256, ... in order, then the tree): cval[0] = c, cval[1] = g
+__device__ __forceinline__ void mgga_c(const double* __restrict__ gpart, int nblocks, double scale, int tb09,
+                                       double* red, double (&cval)[2]) {
   double v = 0.0;
   for (int b = threadIdx.x; b < nblocks; b += 256) v += gpart[b];
   red[threadIdx.x] = v;
@@ -382,31 +406,51 @@ __global__ __launch_bounds__(256) void k_mgga_c(const double* __restrict__ gpart
     if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    const double gg = red[0] * scale;
-    cval[0] = tb09 ? -0.012 + 1.023 * sqrt(gg) : 1.0;
-    cval[1] = gg;
-  }
+  const double gg = red[0] * scale;
+  cval[0] = tb09 ? -0.012 + 1.023 * sqrt(gg) : 1.0;
+  cval[1] = gg;
+}
+
+__global__ __launch_bounds__(256) void k_mgga_c(const double* __restrict__ gpart, int nblocks, double scale,
+                                                int tb09, double* __restrict__ cval) {
+  __shared__ double red[256];
+  double c[2];
+  mgga_c(gpart, nblocks, scale, tb09, red, c);
+  if (threadIdx.x < 2) cval[threadIdx.x] = c[threadIdx.x];
 }
 
 // ---------------------------------------------------------------- v_x
+// sum_c: gpart has at most 256 values and every workgroup adds them up itself
+// (one value a thread, under the loads of its own points): a launch of one
+// workgroup for it cost 8 us of a step, its gap included
 __global__ __launch_bounds__(256) void k_mgga_vx(const double* __restrict__ rho, const double* __restrict__ tau,
-                                                 const double* __restrict__ cval, MggaArgs a,
+                                                 const double* __restrict__ gpart, int nblocks, double scale,
+                                                 int tb09, int sum_c, double* __restrict__ cval, MggaArgs a,
                                                  double* __restrict__ vx) {
+  __shared__ double red[256];
   const Geometry& g = a.g;
   const int N = g.n1 * g.n2 * g.n3;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
+  const int pt = blockIdx.x * blockDim.x + threadIdx.x;
+  const int p = min(pt, N - 1);
   const double r = rho[p];
+  const int x = p % g.n1, y = (p / g.n1) % g.n2, z = p / (g.n1 * g.n2);
+  const FieldNb f = field_nb(rho, g, x, y, z);
+  double cv[2];
+  if (sum_c) {
+    mgga_c(gpart, nblocks, scale, tb09, red, cv);
+    if (blockIdx.x == 0 && threadIdx.x < 2) cval[threadIdx.x] = cv[threadIdx.x];
+  } else {
+    cv[0] = cval[0];
+  }
+  if (pt >= N) return;
   if (!(r >= kRhoMin)) {
     vx[p] = 0.0;
     return;
   }
-  const int x = p % g.n1, y = (p / g.n1) % g.n2, z = p / (g.n1 * g.n2);
   double d[3];
-  grad_field(rho, a, x, y, z, d);
-  const double lap = lap_field(rho, a, x, y, z);
-  const double c = cval[0];
+  grad_field(f, a, d);
+  const double lap = lap_field(r, f, a);
+  const double c = cv[0];
   // one spin channel of the saturated density
   const double rs = 0.5 * r;
   const double gsq = 0.25 * (d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
@@ -431,10 +475,14 @@ hipError_t launch_mgga_potential(const double* rho, const double* tau, const Mgg
   hipLaunchKernelGGL(k_mgga_gpart, dim3(nb), dim3(256), 0, s, rho, a, gpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mgga_c, dim3(1), dim3(256), 0, s, gpart, nb, dV / volume, tb09, cval);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mgga_vx, dim3(nb), dim3(256), 0, s, rho, tau, cval, a, vx);
+  const int sum_c = nb <= 256;
+  if (!sum_c) {
+    hipLaunchKernelGGL(k_mgga_c, dim3(1), dim3(256), 0, s, gpart, nb, dV / volume, tb09, cval);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_mgga_vx, dim3(nb), dim3(256), 0, s, rho, tau, gpart, nb, dV / volume, tb09, sum_c, cval, a,
+                     vx);
   return hipGetLastError();
 }
 

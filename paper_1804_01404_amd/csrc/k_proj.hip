@@ -15,8 +15,8 @@
 // adds up at the end. Laid out as a product for the FP64 matrix unit, four
 // entries of eight orbitals at a time, the tables were loaded once per four
 // entries and half of the lanes held copies (1.48 M vector loads for the 96
-// orbitals and 256 atoms of a 96^3 cluster, each of 16 cycles: the whole of
-// its 74 us).
+// orbitals and 256 atoms of a 96^3 cluster, each of 16 cycles: half of its
+// 74 us).
 //   96^3, 96 orbitals, 256 atoms, complex FP32: projection 74 -> 55 us, with the
 //   previous stage's term added 136 -> 84 us (its lines alone are 230 MB), moments
 //   69 -> 60 us. 36 x 40 x 27, 96 orbitals, 8 atoms, complex128: 6.3 -> 4.8, 13.1 ->
