@@ -355,7 +355,8 @@ hipError_t launch_copy8(const void* src, void* dst, size_t bytes, hipStream_t s)
 hipError_t launch_mid_potential(const double* Vn, double* Vd, float* Vf, size_t n, hipStream_t s);
 
 // ---- spectra and work from time series (k_spectra.hip) ----------------------
-constexpr int kSpecThreads = 256;    // frequencies per workgroup
+constexpr int kSpecSlices = 16;     // slices of a chunk, one per wavefront
+constexpr int kSpecThreads = 64 * kSpecSlices;
 constexpr int kSpecChunksMax = 64;   // sample chunks summed in a fixed order
 int spec_chunks(int n_t);
 // scratch: 1 + spec_chunks(n_t) * n_w double2 (the mean, then the chunk partials)
