@@ -39,6 +39,39 @@ struct DevBuf {
 
 }  // namespace
 
+// The captured step, alone and several in one graph. Between two graph launches
+// of a stream the GPU idles 8 us (nothing between the kernels of one), a
+// seventh of a step of a 16^3 Gamma cell; a node costs some two microseconds to
+// capture and instantiate, so with more than four steps a graph a first call of
+// twenty steps pays more than it saves. 16^3 Gamma cell 1.515 -> 1.422 ms a pass,
+// sixteen 12^3 cells of a slab 21.3 -> 20.7 ms.
+constexpr int kGraphSteps = 4;
+struct StepGraphs {
+  hipGraphExec_t one = nullptr, many = nullptr;
+  int steps = 0;  // of many (0: not planned)
+  // the steps of the larger graph: as many as a call has, up to kGraphSteps (a
+  // shorter call's graph gives way to a longer one's)
+  void plan(int nsteps) {
+    const int k = std::min(nsteps, kGraphSteps);
+    if (k < 2 || k <= steps) return;
+    if (many) (void)hipGraphExecDestroy(many);
+    many = nullptr;
+    steps = k;
+  }
+  // the graph for the next of `left` steps, and the steps it holds
+  hipGraphExec_t* next(int left, int* k) {
+    const bool m = steps > 1 && left >= steps;
+    *k = m ? steps : 1;
+    return m ? &many : &one;
+  }
+  void drop() {
+    if (one) (void)hipGraphExecDestroy(one);
+    if (many) (void)hipGraphExecDestroy(many);
+    one = many = nullptr;
+    steps = 0;
+  }
+};
+
 struct tddft_ctx {
   tddft_config cfg{};
   std::vector<double> kpt, kw;
@@ -116,7 +149,7 @@ struct tddft_ctx {
   // (the bound grows with each; -1: none since the potential was set)
   double bound_amax[3] = {-1.0, -1.0, -1.0};
 
-  hipGraphExec_t graph = nullptr;
+  StepGraphs graphs;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   double last_ms = 0;
 };
@@ -639,12 +672,7 @@ tddft_status observe_now(tddft_ctx* c) {
   return TDDFT_OK;
 }
 
-void invalidate_graph(tddft_ctx* c) {
-  if (c->graph) {
-    (void)hipGraphExecDestroy(c->graph);
-    c->graph = nullptr;
-  }
-}
+void invalidate_graph(tddft_ctx* c) { c->graphs.drop(); }
 
 tddft_status upload_orbitals(tddft_ctx* c, const double* psi) {
   const size_t total = c->n_orb_tot * c->N;
@@ -1521,25 +1549,37 @@ tddft_status tddft_propagate(tddft_ctx* c, int32_t nsteps, const double* A, doub
   tddft_status st = prepare_propagate(c, nsteps, A);
   if (st != TDDFT_OK) return st;
   const bool use_graph = !(c->cfg.flags & (TDDFT_FLAG_NO_GRAPH | TDDFT_FLAG_DEBUG_SYNC));
-  if (use_graph && !c->graph) {
-    hipGraph_t gr;
-    HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    st = step_dispatch(c);
-    hipError_t e = hipStreamEndCapture(c->stream, &gr);
-    if (st != TDDFT_OK) return st;
-    if (e != hipSuccess) return fail(c, TDDFT_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-    e = hipGraphInstantiate(&c->graph, gr, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(gr);
-    if (e != hipSuccess) return fail(c, TDDFT_EDEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
-  }
-  HIP_TRY(hipEventRecord(c->ev0, c->stream));
-  for (int n = 0; n < nsteps; ++n) {
+  // a step of the per-stage path is long for its gap and has half as many nodes
+  // again: 3226 -> 3208 us a pass of a 36 x 40 x 27 cell, 234 us more for a first one
+  if (use_graph) c->graphs.plan(c->fused ? nsteps : 1);
+  bool started = false;
+  for (int n = 0; n < nsteps;) {
+    int k = 1;
     if (use_graph) {
-      HIP_TRY(hipGraphLaunch(c->graph, c->stream));
+      hipGraphExec_t* g = c->graphs.next(nsteps - n, &k);
+      if (!*g) {
+        hipGraph_t gr;
+        HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+        for (int i = 0; i < k && st == TDDFT_OK; ++i) st = step_dispatch(c);
+        hipError_t e = hipStreamEndCapture(c->stream, &gr);
+        if (st != TDDFT_OK) return st;
+        if (e != hipSuccess) return fail(c, TDDFT_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
+        e = hipGraphInstantiate(g, gr, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(gr);
+        if (e != hipSuccess) {
+          *g = nullptr;
+          return fail(c, TDDFT_EDEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
+        }
+      }
+      if (!started) HIP_TRY(hipEventRecord(c->ev0, c->stream));
+      HIP_TRY(hipGraphLaunch(*g, c->stream));
     } else {
+      if (!started) HIP_TRY(hipEventRecord(c->ev0, c->stream));
       st = step_dispatch(c);
       if (st != TDDFT_OK) return st;
     }
+    started = true;
+    n += k;
   }
   HIP_TRY(hipEventRecord(c->ev1, c->stream));
   st = collect_propagate(c, nsteps, A, J_out);
@@ -1849,7 +1889,7 @@ struct tddft_batch {
   std::vector<hipStream_t> side;
   std::vector<hipEvent_t> side_done;
   hipEvent_t fork = nullptr, ev0 = nullptr, ev1 = nullptr;
-  hipGraphExec_t graph = nullptr;
+  StepGraphs graphs;
   double last_ms = 0;
   std::vector<void*> allocs;
   // one staging area each way for the cells' A and J tables: the IOCell
@@ -2144,25 +2184,38 @@ tddft_status batch_propagate(tddft_batch* b, int32_t nsteps) {
   }
   if (done >= nsteps) return TDDFT_OK;
   const bool use_graph = !(b->flags & (TDDFT_FLAG_NO_GRAPH | TDDFT_FLAG_DEBUG_SYNC));
-  if (use_graph && !b->graph) {
-    hipGraph_t gr;
-    BHIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    tddft_status st = batch_step<T>(b, false);
-    hipError_t e = hipStreamEndCapture(b->stream, &gr);
-    if (st != TDDFT_OK) return st;
-    if (e != hipSuccess) return bfail(b, TDDFT_EDEVICE, std::string("batch graph capture: ") + hipGetErrorString(e));
-    e = hipGraphInstantiate(&b->graph, gr, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(gr);
-    if (e != hipSuccess) return bfail(b, TDDFT_EDEVICE, std::string("batch graph: ") + hipGetErrorString(e));
-  }
-  BHIP(hipEventRecord(b->ev0, b->stream));
-  for (int n = done; n < nsteps; ++n) {
+  // a step with per-stage lanes is long (and has some hundred nodes): one a graph
+  if (use_graph) b->graphs.plan(b->lanes.empty() ? nsteps - done : 1);
+  bool started = false;
+  for (int n = done; n < nsteps;) {
+    int k = 1;
     if (use_graph) {
-      BHIP(hipGraphLaunch(b->graph, b->stream));
+      hipGraphExec_t* g = b->graphs.next(nsteps - n, &k);
+      if (!*g) {
+        hipGraph_t gr;
+        BHIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+        tddft_status st = TDDFT_OK;
+        for (int i = 0; i < k && st == TDDFT_OK; ++i) st = batch_step<T>(b, false);
+        hipError_t e = hipStreamEndCapture(b->stream, &gr);
+        if (st != TDDFT_OK) return st;
+        if (e != hipSuccess)
+          return bfail(b, TDDFT_EDEVICE, std::string("batch graph capture: ") + hipGetErrorString(e));
+        e = hipGraphInstantiate(g, gr, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(gr);
+        if (e != hipSuccess) {
+          *g = nullptr;
+          return bfail(b, TDDFT_EDEVICE, std::string("batch graph: ") + hipGetErrorString(e));
+        }
+      }
+      if (!started) BHIP(hipEventRecord(b->ev0, b->stream));
+      BHIP(hipGraphLaunch(*g, b->stream));
     } else {
+      if (!started) BHIP(hipEventRecord(b->ev0, b->stream));
       tddft_status st = batch_step<T>(b, false);
       if (st != TDDFT_OK) return st;
     }
+    started = true;
+    n += k;
   }
   BHIP(hipEventRecord(b->ev1, b->stream));
   BHIP(hipStreamSynchronize(b->stream));
@@ -2238,10 +2291,7 @@ tddft_status tddft_batch_propagate(tddft_batch* b, int32_t nsteps, const double*
     const bool had = c->cap_steps >= nsteps;
     tddft_status st = prepare_propagate(c, nsteps, A[i], false);
     if (st != TDDFT_OK) return bcell(b, st, i);
-    if (!had && b->graph) {  // a cell's A/J tables moved: the captured step must be rebuilt
-      (void)hipGraphExecDestroy(b->graph);
-      b->graph = nullptr;
-    }
+    if (!had) b->graphs.drop();  // a cell's A/J tables moved: the captured steps must be rebuilt
   }
   // the A tables of every cell with one copy: the IOCell table and the tables
   // staged in pinned memory, scattered on the device (counters reset there)
@@ -2352,7 +2402,7 @@ const char* tddft_batch_last_error(const tddft_batch* b) { return b ? b->err.c_s
 void tddft_batch_free(tddft_batch* b) {
   if (!b) return;
   if (b->stream) (void)hipStreamSynchronize(b->stream);
-  if (b->graph) (void)hipGraphExecDestroy(b->graph);
+  b->graphs.drop();
   for (auto* c : b->cells) {
     c->stream = b->stream;
     tddft_free(c);
