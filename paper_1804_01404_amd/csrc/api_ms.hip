@@ -371,6 +371,7 @@ struct tddft_ms {
   // copied to the caller once at its end ([out_cap][n_x] each)
   double *dAout = nullptr, *dIout = nullptr;
   int out_cap = 0;
+  double* pinned = nullptr;  // [2][n_x] pinned: A down and I up in each step of the cells
   std::string err;
 };
 
@@ -662,7 +663,9 @@ tddft_status tddft_ms_step(tddft_ms* ms, int32_t n_macro, const double* inc, dou
       return ms_fail(ms, TDDFT_ENOMEM, "device allocation failed (output rows)");
     ms->out_cap = n_macro;
   }
-  std::vector<double> Anew(nx), Inew(nx);
+  if (!ms->pinned)  // (a run on the network may fall back to the cells on the way)
+    MHIP(hipHostMalloc(reinterpret_cast<void**>(&ms->pinned), 2 * (size_t)nx * sizeof(double)));
+  double *Anew = ms->pinned, *Inew = ms->pinned + nx;
   const std::vector<int> all = [&] {
     std::vector<int> v(nm);
     for (int m = 0; m < nm; ++m) v[m] = m;
@@ -671,40 +674,34 @@ tddft_status tddft_ms_step(tddft_ms* ms, int32_t n_macro, const double* inc, dou
   for (int n = 0; n < n_macro; ++n) {
     const double iv[4] = {inc ? inc[2 * n] : 0.0, inc ? inc[2 * n + 1] : 0.0, inc ? inc[2 * n + 2] : 0.0,
                           inc ? inc[2 * n + 3] : 0.0};
-    MHIP(launch_fdtd_step(ms->A[1], ms->A[0], ms->I, ms->A[2], nx, S2, src, q, iv, ms->stream));
-    MHIP(hipMemcpyAsync(ms->Iold, ms->I, nx * sizeof(double), hipMemcpyDeviceToDevice, ms->stream));
+    MHIP(launch_fdtd_step(ms->A[1], ms->A[0], ms->I, ms->A[2], ms->Iold, nx, S2, src, q, iv, ms->stream));
+    double *hA = nullptr, *hI = nullptr;  // the medium's history rows (network)
     if (ms->mode == 0) {
-      MHIP(hipMemcpyAsync(Anew.data(), ms->A[2], nx * sizeof(double), hipMemcpyDeviceToHost, ms->stream));
-      MHIP(hipStreamSynchronize(ms->stream));
+      MHIP(hipMemcpyAsync(Anew, ms->A[2], nx * sizeof(double), hipMemcpyDeviceToHost, ms->stream));
+      MHIP(hipStreamSynchronize(ms->stream));  // and the last step's copy out of Inew is over
       const size_t row = ms->hist.size();
       ms->hist.resize(row + nm);
       for (int m = 0; m < nm; ++m) ms->hist[row + m] = Anew[g.x0 + m];
       std::vector<double> Ic;
       st = ms_run_cells(ms, ms->full, all, ms->hist, ms->steps, ms->steps + 1, Ic);
       if (st != TDDFT_OK) return st;
-      std::fill(Inew.begin(), Inew.end(), 0.0);
+      std::fill(Inew, Inew + nx, 0.0);
       for (int m = 0; m < nm; ++m) Inew[g.x0 + m] = Ic[m];
-      MHIP(hipMemcpyAsync(ms->I, Inew.data(), nx * sizeof(double), hipMemcpyHostToDevice, ms->stream));
+      MHIP(hipMemcpyAsync(ms->I, Inew, nx * sizeof(double), hipMemcpyHostToDevice, ms->stream));
     } else {
       const int slot = (ms->steps + 1) % ms->nn->sh.W;
       if ((st = ms_reserve_hist(ms, ms->steps + 2)) != TDDFT_OK) return st;
       MHIP(launch_ms_gate(ms->A[2], g.x0, nm, ms->a_max, ms->flag, ms->stream));
-      MHIP(hipMemcpyAsync(ms->dhist + (size_t)(ms->steps + 1) * nm, ms->A[2] + g.x0, nm * sizeof(double),
-                          hipMemcpyDeviceToDevice, ms->stream));
+      hA = ms->dhist + (size_t)(ms->steps + 1) * nm;
+      hI = ms->dIhist + (size_t)(ms->steps + 1) * nm;
       MHIP(launch_ring_push(ms->A[2], g.x0, nm, ms->ring, ms->nn->sh.W, slot, 1.0 / ms->nn->cfg.a_scale, ms->stream));
       MHIP(launch_ring_windows(ms->ring, nm, ms->nn->sh.W, slot, ms->Xw, ms->stream));
       MHIP(nn_forward(ms->nn->sh, ms->nn->theta, ms->Xw, nm, ms->wk, ms->stream));
       MHIP(launch_scatter_current(ms->wk.y, g.x0, nm, nx, ms->nn->cfg.j_scale, ms->I, ms->stream));
-      MHIP(hipMemcpyAsync(ms->dIhist + (size_t)(ms->steps + 1) * nm, ms->I + g.x0, nm * sizeof(double),
-                          hipMemcpyDeviceToDevice, ms->stream));
     }
-    MHIP(launch_ms_work_step(ms->A[2], ms->A[1], ms->Iold, ms->I, g.x0, nm, g.dx, g.dt, ms->energy, ms->stream));
-    if (A_out)
-      MHIP(hipMemcpyAsync(ms->dAout + (size_t)n * nx, ms->A[2], nx * sizeof(double), hipMemcpyDeviceToDevice,
-                          ms->stream));
-    if (I_out)
-      MHIP(hipMemcpyAsync(ms->dIout + (size_t)n * nx, ms->I, nx * sizeof(double), hipMemcpyDeviceToDevice,
-                          ms->stream));
+    MHIP(launch_ms_work_step(ms->A[2], ms->A[1], ms->Iold, ms->I, nx, g.x0, nm, g.dx, g.dt, ms->energy,
+                             A_out ? ms->dAout + (size_t)n * nx : nullptr,
+                             I_out ? ms->dIout + (size_t)n * nx : nullptr, hA, hI, ms->stream));
     double* t = ms->A[0];
     ms->A[0] = ms->A[1];
     ms->A[1] = ms->A[2];
@@ -763,6 +760,7 @@ void tddft_ms_free(tddft_ms* ms) {
   for (float* p : {ms->ring, ms->Xw, ms->wk.h1, ms->wk.h2, ms->wk.y})
     if (p) (void)hipFree(p);
   if (ms->flag) (void)hipFree(ms->flag);
+  if (ms->pinned) (void)hipHostFree(ms->pinned);
   if (ms->stream) (void)hipStreamDestroy(ms->stream);
   delete ms;
 }

@@ -372,8 +372,9 @@ void set_stateless_error(const char* msg);
 const char* stateless_error();
 
 // ---- multiscale Maxwell (k_maxwell.hip) -----------------------------------
-hipError_t launch_fdtd_step(const double* A_now, const double* A_prev, const double* I, double* A_new, int n,
-                            double S2, double src, double q, const double inc[4], hipStream_t s);
+hipError_t launch_fdtd_step(const double* A_now, const double* A_prev, const double* I, double* A_new,
+                            double* I_old, int n, double S2, double src, double q, const double inc[4],
+                            hipStream_t s);
 hipError_t launch_ring_push(const double* A, int x0, int n_mat, float* ring, int W, int slot, double inv_scale,
                             hipStream_t s);
 hipError_t launch_ring_windows(const float* ring, int n_mat, int W, int head, float* X, hipStream_t s);
@@ -383,7 +384,8 @@ hipError_t launch_ms_gate(const double* A, int x0, int n_mat, double a_max, int*
 hipError_t launch_em_energy(const double* A_now, const double* A_prev, int n, double dx, double dt, double* out,
                             hipStream_t s);
 hipError_t launch_ms_work_step(const double* A_new, const double* A_now, const double* I_now, const double* I_new,
-                               int x0, int n_mat, double dx, double dt, double* W, hipStream_t s);
+                               int n, int x0, int n_mat, double dx, double dt, double* W, double* A_row,
+                               double* I_row, double* hA, double* hI, hipStream_t s);
 hipError_t launch_ms_work_history(const double* A, const double* I, int steps, int n_mat, double dx, double dt,
                                   double* W, hipStream_t s);
 

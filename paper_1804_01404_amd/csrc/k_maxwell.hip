@@ -15,12 +15,14 @@ __device__ __forceinline__ double leap(const double* __restrict__ A_now, const d
 
 // One macroscopic step for all points. inc = (A_inc(X_0, t_n), A_inc(X_1, t_n),
 // A_inc(X_0, t_{n+1}), A_inc(X_1, t_{n+1})). The end points recompute their
-// inner neighbour's new value, so one launch suffices.
+// inner neighbour's new value, so one launch suffices; I_old keeps this step's
+// current for the work integral.
 __global__ void k_fdtd_step(const double* __restrict__ A_now, const double* __restrict__ A_prev,
-                            const double* __restrict__ I, double* __restrict__ A_new, int n, double S2,
-                            double src, double q, double4 inc) {
+                            const double* __restrict__ I, double* __restrict__ A_new, double* __restrict__ I_old,
+                            int n, double S2, double src, double q, double4 inc) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
+  I_old[j] = I[j];
   if (j > 0 && j < n - 1) {
     A_new[j] = leap(A_now, A_prev, I, j, S2, src);
   } else if (j == 0) {
@@ -74,11 +76,11 @@ hipError_t launch_ms_gate(const double* A, int x0, int n_mat, double a_max, int*
   return hipGetLastError();
 }
 
-hipError_t launch_fdtd_step(const double* A_now, const double* A_prev, const double* I, double* A_new, int n,
-                            double S2, double src, double q, const double inc[4], hipStream_t s) {
+hipError_t launch_fdtd_step(const double* A_now, const double* A_prev, const double* I, double* A_new,
+                            double* I_old, int n, double S2, double src, double q, const double inc[4], hipStream_t s) {
   const double4 iv = make_double4(inc[0], inc[1], inc[2], inc[3]);
-  hipLaunchKernelGGL(k_fdtd_step, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A_now, A_prev, I, A_new, n,
-                     S2, src, q, iv);
+  hipLaunchKernelGGL(k_fdtd_step, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A_now, A_prev, I, A_new,
+                     I_old, n, S2, src, q, iv);
   return hipGetLastError();
 }
 
@@ -142,17 +144,29 @@ __global__ __launch_bounds__(1024) void k_em_energy(const double* __restrict__ A
   if (t == 0) *out = (se + sb) * dx / (8.0 * M_PI);
 }
 
-// one macroscopic step's work over the medium points x0 .. x0 + n_mat - 1
+// one macroscopic step's work over the medium points x0 .. x0 + n_mat - 1, and
+// the step's records (each may be null): the rows A_row, I_row of all n points,
+// the medium points' histories hA, hI. A copy of its own for each was some
+// 10 us of a step, its gap included.
 __global__ __launch_bounds__(1024) void k_ms_work_step(const double* __restrict__ A_new, const double* __restrict__ A_now,
                                                        const double* __restrict__ I_now, const double* __restrict__ I_new,
-                                                       int x0, int n_mat, double dx, double dt, double* __restrict__ W) {
+                                                       int n, int x0, int n_mat, double dx, double dt,
+                                                       double* __restrict__ W, double* __restrict__ A_row,
+                                                       double* __restrict__ I_row, double* __restrict__ hA,
+                                                       double* __restrict__ hI) {
   __shared__ double red[1024];
   double s = 0.0;
   for (int m = threadIdx.x; m < n_mat; m += 1024) {
     const int j = x0 + m;
     const double E = -(A_new[j] - A_now[j]) / (kC * dt);
     s += 0.5 * (I_now[j] + I_new[j]) * E;
+    if (hA) hA[m] = A_new[j];
+    if (hI) hI[m] = I_new[j];
   }
+  if (A_row)
+    for (int j = threadIdx.x; j < n; j += 1024) A_row[j] = A_new[j];
+  if (I_row)
+    for (int j = threadIdx.x; j < n; j += 1024) I_row[j] = I_new[j];
   const double tot = block_sum_1024(s, red);
   if (threadIdx.x == 0) *W += dt * dx * tot;
 }
@@ -183,8 +197,10 @@ hipError_t launch_em_energy(const double* A_now, const double* A_prev, int n, do
 }
 
 hipError_t launch_ms_work_step(const double* A_new, const double* A_now, const double* I_now, const double* I_new,
-                               int x0, int n_mat, double dx, double dt, double* W, hipStream_t s) {
-  hipLaunchKernelGGL(k_ms_work_step, dim3(1), dim3(1024), 0, s, A_new, A_now, I_now, I_new, x0, n_mat, dx, dt, W);
+                               int n, int x0, int n_mat, double dx, double dt, double* W, double* A_row,
+                               double* I_row, double* hA, double* hI, hipStream_t s) {
+  hipLaunchKernelGGL(k_ms_work_step, dim3(1), dim3(1024), 0, s, A_new, A_now, I_now, I_new, n, x0, n_mat, dx, dt, W,
+                     A_row, I_row, hA, hI);
   return hipGetLastError();
 }
 
