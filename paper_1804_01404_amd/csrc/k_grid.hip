@@ -525,9 +525,12 @@ __device__ __forceinline__ void stockham_stage(const double2* in, double2* out, 
   }
 }
 
-// the M roots exp(2 pi i k / M)
-__device__ __forceinline__ void fft_roots(int M, double2* w) {
-  for (int k = threadIdx.x; k < M; k += blockDim.x) {
+// the M roots exp(2 pi i k / M), by the workgroup's last wavefronts (all but
+// the last `skip`): the first ones have the pass's loads to wait for
+__device__ __forceinline__ void fft_roots(int M, double2* w, int skip = 0) {
+  int k0 = (int)blockDim.x - 1 - (int)threadIdx.x - 64 * skip;
+  if (k0 < 0) k0 += blockDim.x;
+  for (int k = k0; k < M; k += blockDim.x) {
     double sn, cs;
     sincospi(2.0 * (double)k / (double)M, &sn, &cs);
     w[k] = make_double2(cs, sn);
@@ -600,14 +603,32 @@ __device__ __forceinline__ void fft_axis_block(double2* data, int M1, int M2, in
     }
     buf0[line * ls.sl + e * ls.se] = v;
   }
+  // the kernel's values are in flight under the forward transform (a thread has
+  // at most kKeep of them, but for lines beyond 2048)
+  constexpr int kKeep = 4;
+  double kv[kKeep];
+  if (ln.ends == kKernel) {
+#pragma unroll
+    for (int u = 0; u < kKeep; ++u) {
+      const int i = min((int)threadIdx.x + u * (int)blockDim.x, total - 1), e = quot(i, inv_d);
+      kv[u] = K[base + (i - e * d) + e * ge];
+    }
+  }
   __syncthreads();
   double2* res = fft_lines_lds(plan, buf0, buf1, ls, (double)sign, w);
   if (ln.ends == kKernel) {
-    for (int i = threadIdx.x; i < total; i += blockDim.x) {
-      const int e = quot(i, inv_d), line = i - e * d;
-      const double k = K[base + line + e * ge];
-      double2* r = res + line + e * B;
+    auto times = [&](int i, double k, int e) {
+      double2* r = res + (i - e * d) + e * B;
       *r = make_double2(r->x * k, r->y * k);
+    };
+#pragma unroll
+    for (int u = 0; u < kKeep; ++u) {
+      const int i = (int)threadIdx.x + u * (int)blockDim.x;
+      if (i < total) times(i, kv[u], quot(i, inv_d));
+    }
+    for (int i = (int)threadIdx.x + kKeep * (int)blockDim.x; i < total; i += blockDim.x) {
+      const int e = quot(i, inv_d);
+      times(i, K[base + (i - e * d) + e * ge], e);
     }
     __syncthreads();
     res = fft_lines_lds(plan, res, res == buf0 ? buf1 : buf0, ls, -(double)sign, w);
@@ -748,15 +769,14 @@ __device__ void pz81(double rho, int exchange_too, double* v, double* e) {
 }
 
 // xc: 0 none, 1 PZ81, 2 and 3 the exchange in vx_mgga plus PZ81 correlation
-__device__ __forceinline__ void xc_value(double vh, const double* rho, const double* Vloc, int xc,
-                                         const double* vx_mgga, double* Vd, float* Vf, double* vh_out, double* exc,
-                                         size_t p) {
+__device__ __forceinline__ void xc_value(double vh, double rho, double Vloc, int xc, double vx_mgga, double* Vd,
+                                         float* Vf, double* vh_out, double* exc, size_t p) {
   double vxc = 0.0, e = 0.0;
   if (xc) {
-    pz81(rho[p], xc == 1, &vxc, &e);
-    if (xc >= 2) vxc += vx_mgga[p];
+    pz81(rho, xc == 1, &vxc, &e);
+    if (xc >= 2) vxc += vx_mgga;
   }
-  const double v = Vloc[p] + vh + vxc;
+  const double v = Vloc + vh + vxc;
   Vd[p] = v;
   Vf[p] = (float)v;
   vh_out[p] = vh;
@@ -772,7 +792,7 @@ __device__ __forceinline__ void xc_point(const double2* data, int n1, int n2, in
   const int z = (int)(p / ((size_t)n1 * n2));
   double vh = 0.0;
   if (hartree) vh = data[((size_t)z * M2 + y) * M1 + x].x * vh_scale;
-  xc_value(vh, rho, Vloc, xc, vx_mgga, Vd, Vf, vh_out, exc, p);
+  xc_value(vh, rho[p], Vloc[p], xc, xc >= 2 ? vx_mgga[p] : 0.0, Vd, Vf, vh_out, exc, p);
 }
 
 // ---------------------------------------------------------------- Poisson by planes
@@ -785,11 +805,14 @@ __device__ __forceinline__ void xc_point(const double2* data, int n1, int n2, in
 // that form's reduction, five passes and assembly are seven launches of 4 to
 // 7 us each, half of a small cell's step. The plane stays [y][x] in LDS for
 // both directions (the stages take the stride), and only kx <= n1 / 2 goes
-// through the y transforms and memory.
+// through the y transforms and memory. What is left is latency: loads go out
+// before they are needed and the roots are formed by wavefronts that wait for
+// none (16^3, one chunk of orbitals: 21 -> 15 us for the three launches).
 struct PlanePlan {
   int n1, n2, n3;
   FFTPlan x, y;
 };
+constexpr int kPlaneThreads = 1024;  // every launch's
 
 bool poisson_planes(int periodic, int hartree, int n1, int n2) {
   return periodic && hartree && n1 * n2 <= kPlaneMax;
@@ -799,7 +822,7 @@ bool poisson_planes(int periodic, int hartree, int n1, int n2) {
 __device__ __forceinline__ const double2* plane_roots(const PlanePlan& pl, double2* wx) {
   fft_roots(pl.n1, wx);
   if (pl.n1 == pl.n2) return wx;
-  fft_roots(pl.n2, wx + pl.n1);
+  fft_roots(pl.n2, wx + pl.n1, 1);
   return wx + pl.n1;
 }
 
@@ -873,6 +896,16 @@ __device__ __forceinline__ void poisson_inverse_plane(const TailCell& t, const P
     const int y = quot(i, inv), p = y * pl.n1 + i - y * H;
     a[p] = in[p];
   }
+  // what the potential needs besides is in flight under the transforms
+  constexpr int kKeep = kPlaneMax / kPlaneThreads;
+  double rho[kKeep], vloc[kKeep], vx[kKeep];
+#pragma unroll
+  for (int u = 0; u < kKeep; ++u) {
+    const size_t p = (size_t)z * P + min((int)threadIdx.x + u * kPlaneThreads, P - 1);
+    rho[u] = t.rho[p];
+    vloc[u] = t.Vloc[p];
+    vx[u] = xc >= 2 ? vx_mgga[p] : 0.0;
+  }
   __syncthreads();
   double2* r = fft_lines_lds(pl.y, a, b, LineSet{H, pl.n1, 1}, +1.0, wy);
   // kx > n1 / 2 from its conjugate
@@ -885,11 +918,13 @@ __device__ __forceinline__ void poisson_inverse_plane(const TailCell& t, const P
   }
   __syncthreads();
   r = fft_lines_lds(pl.x, r, r == a ? b : a, LineSet{pl.n2, 1, pl.n1}, +1.0, wx);
-  for (int i = threadIdx.x; i < P; i += blockDim.x)
-    xc_value(r[i].x * t.vh_scale, t.rho, t.Vloc, xc, vx_mgga, t.Vd, t.Vf, t.vh, t.exc, (size_t)z * P + i);
+#pragma unroll
+  for (int u = 0; u < kKeep; ++u) {
+    const int i = (int)threadIdx.x + u * kPlaneThreads;
+    if (i < P)
+      xc_value(r[i].x * t.vh_scale, rho[u], vloc[u], xc, vx[u], t.Vd, t.Vf, t.vh, t.exc, (size_t)z * P + i);
+  }
 }
-
-constexpr int kPlaneThreads = 1024;
 
 __global__ __launch_bounds__(kPlaneThreads) void k_poisson_forward(TailCell t, PlanePlan pl) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
