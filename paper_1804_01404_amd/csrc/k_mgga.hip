@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void k_rho_tau_partial(const typename Vec2<T>:
 }
 
 // The same partial sums for periodic cells whose xy plane fits one workgroup:
-// a thread owns one column of a z slab (kTauSlab planes), the x/y
+// a thread owns one column of a z slab (SLAB planes at most), the x/y
 // neighbours of the current plane come from LDS (double-buffered, one
 // barrier per plane) and the z neighbours from a queue in registers, so each
 // orbital value is read once from memory (plus the 8 halo planes of the
@@ -217,14 +217,20 @@ __global__ __launch_bounds__(256) void k_rho_tau_partial(const typename Vec2<T>:
 // order as above.
 //
 // A workgroup waits for its plane's barrier and, at each orbital, for the
-// first loads of its queue, so what counts is how many share a compute unit:
-// slabs of at most five planes (as even as can be) put two workgroups of a
-// 20^3 cell of 1024 orbitals there, where ten planes left one: 59 -> 43 us
-// (complex FP32, 65 MB of orbitals).
-constexpr int kTauSlab = 5;
-__host__ __device__ inline int tau_slabs(int n3) { return (n3 + kTauSlab - 1) / kTauSlab; }
+// first loads of its queue, so what counts is how many share a compute unit.
+// Slabs of at most ten planes read least; where those leave fewer than 1024
+// workgroups of eight orbitals, slabs of at most five (as even as can be)
+// double them. 20^3, long against
+// short slabs, whole step: 1024 orbitals 266 / 259 us, 3456 703 / 701, 5488
+// 1073 / 1077, 8192 1546 / 1553 (complex FP32); complex128 8192 2800 / 2897.
+constexpr int kTauLong = 10, kTauShort = 5;
+int tau_slab(const Geometry& g, long n_tot) {
+  const int nl = (g.n3 + kTauLong - 1) / kTauLong;
+  return n_tot * nl >= 8 * 1024 ? kTauLong : kTauShort;
+}
+__host__ __device__ inline int tau_slabs(int n3, int slab) { return (n3 + slab - 1) / slab; }
 
-template <typename T>
+template <typename T, int SLAB>
 __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::type* __restrict__ w,
                                                         const double* __restrict__ kw,
                                                         const double* __restrict__ kappa, MggaArgs a, int chunk,
@@ -236,7 +242,7 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
   const Geometry& g = a.g;
   const int n1 = g.n1, n2 = g.n2, n3 = g.n3, plane = n1 * n2;
   const size_t N = (size_t)plane * n3;
-  const int nsl = tau_slabs(n3), len = (n3 + nsl - 1) / nsl;
+  const int nsl = tau_slabs(n3, SLAB), len = (n3 + nsl - 1) / nsl;
   const int cy = blockIdx.x / nsl, slab = blockIdx.x - cy * nsl;
   const int z0 = slab * len, z1 = min(n3, z0 + len);
   const int tid = threadIdx.x;
@@ -250,9 +256,9 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
     oy[2 * (m - 1)] = ((y + m) % n2) * n1 + x;
     oy[2 * (m - 1) + 1] = ((y - m + n2) % n2) * n1 + x;
   }
-  double ar[kTauSlab], at[kTauSlab];
+  double ar[SLAB], at[SLAB];
 #pragma unroll
-  for (int i = 0; i < kTauSlab; ++i) ar[i] = at[i] = 0.0;
+  for (int i = 0; i < SLAB; ++i) ar[i] = at[i] = 0.0;
   const int n_tot = g.n_orb * g.n_k;
   const int o0 = cy * chunk;
   const int o1 = min(n_tot, o0 + chunk);
@@ -269,7 +275,7 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
     for (int i = 0; i < 8; ++i) q[i] = ld(z0 + i - 4);
     T2 nxt = ld(z0 + 4);
 #pragma unroll
-    for (int zz = 0; zz < kTauSlab; ++zz) {
+    for (int zz = 0; zz < SLAB; ++zz) {
       const int z = z0 + zz;
       if (z < z1) {  // uniform over the workgroup
         q[8] = nxt;
@@ -318,7 +324,7 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
   }
   if (active) {
 #pragma unroll
-    for (int zz = 0; zz < kTauSlab; ++zz) {
+    for (int zz = 0; zz < SLAB; ++zz) {
       const int z = z0 + zz;
       if (z < z1) {
         part_rho[(size_t)cy * N + (size_t)z * plane + tid] = ar[zz];
@@ -336,7 +342,7 @@ __global__ __launch_bounds__(1024) void k_rho_tau_plane(const typename Vec2<T>::
 int rho_tau_chunk(const Geometry& g, int n_tot) {
   const int plane = g.n1 * g.n2;
   if (!(g.periodic && plane <= 1024)) return 64;
-  const int nsl = tau_slabs(g.n3);
+  const int nsl = tau_slabs(g.n3, tau_slab(g, n_tot));
   const long want = (long)n_tot * nsl / 1024;
   return (int)std::max(8L, std::min(64L, want));
 }
@@ -349,10 +355,15 @@ hipError_t launch_rho_tau_partial(const typename Vec2<T>::type* w, const double*
   const int nchunks = (a.g.n_orb * a.g.n_k + chunk - 1) / chunk;
   const int plane = a.g.n1 * a.g.n2;
   if (a.g.periodic && plane <= 1024) {
-    const int nsl = tau_slabs(a.g.n3);
+    const int slab = tau_slab(a.g, (long)a.g.n_orb * a.g.n_k);
+    const dim3 grid((unsigned)(nchunks * tau_slabs(a.g.n3, slab))), block(((plane + 63) / 64) * 64);
     const size_t lds = (size_t)2 * plane * sizeof(typename Vec2<T>::type);
-    hipLaunchKernelGGL((k_rho_tau_plane<T>), dim3((unsigned)(nchunks * nsl)), dim3(((plane + 63) / 64) * 64), lds,
-                       s, w, kw, kappa, a, chunk, part_rho, part_tau);
+    if (slab == kTauLong)
+      hipLaunchKernelGGL((k_rho_tau_plane<T, kTauLong>), grid, block, lds, s, w, kw, kappa, a, chunk, part_rho,
+                         part_tau);
+    else
+      hipLaunchKernelGGL((k_rho_tau_plane<T, kTauShort>), grid, block, lds, s, w, kw, kappa, a, chunk, part_rho,
+                         part_tau);
     return hipGetLastError();
   }
   const dim3 grid(((N + 255) / 256) * nchunks);
