@@ -34,7 +34,6 @@ sys.path.insert(0, ROOT)
 
 METRIC = "orbital·gridpoint Taylor steps/s (FP64 vs mixed/batched), % HBM peak"
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
-FP64_MFMA_PEAK_TFLOPS = 78.6   # MI355X dense FP64 matrix
 FP32_VALU_PACKED_TFLOPS = 157.3  # MI355X FP32 vector as published: 256 CU x 2.4 GHz x 256 flop/clk,
                                  # which counts two packed FP32 FMAs per lane and clock
 # 256 CU x 4 SIMD x 16 lanes x 2 flop (one FMA per lane and clock) x 2.4 GHz: the FP32
@@ -315,24 +314,16 @@ def bench_mgga(system, precision, lda_ms, steps=60, warmup=10):
             "fused_ms": kern["fused_ms"], "current_finite": bool(np.all(np.isfinite(J)))}
 
 
-def mfma_projection(system, project_ms, esz):
-    """MFMA work of one stage-mode projection launch (per-stage path): one
-    four-block 4x4x4 FP64 MFMA (512 flops) per four sphere entries, per atom
-    and group of eight orbitals; every product is used except the padding of
-    the last orbital group and of the last four entries of a sphere. The
-    launch is bound by the sphere gathers (one orbital value per entry and
-    orbital, esz bytes), reported as gather_GBs."""
+def projection_figures(system, project_ms, esz):
+    """One stage-mode projection launch (per-stage path): four complex sums per
+    atom and orbital over its sphere entries, in FP64. The launch is bound by
+    the sphere gathers (one orbital value per entry and orbital, esz bytes),
+    reported as gather_GBs."""
     n_tot = system.n_orb * system.n_k
-    n_groups = (n_tot + 7) // 8
-    issued = sum(n_groups * -(-p.npts // 4) * 512 for p in system.projectors)
-    useful = sum(n_tot * 2 * kmax * p.npts * 2 for p in system.projectors for kmax in (4,))
+    flops = sum(n_tot * 2 * 4 * p.npts * 2 for p in system.projectors)
     gathered = sum(n_tot * p.npts * esz for p in system.projectors)
     t = project_ms * 1e-3
-    return {"instruction": "v_mfma_f64_4x4x4f64", "issued_tflops": issued / t / 1e12,
-            "useful_tflops": useful / t / 1e12, "peak": FP64_MFMA_PEAK_TFLOPS,
-            "frac_issued": issued / t / 1e12 / FP64_MFMA_PEAK_TFLOPS,
-            "frac_useful": useful / t / 1e12 / FP64_MFMA_PEAK_TFLOPS,
-            "gather_GBs": gathered / t / 1e9, "ms_per_launch": project_ms}
+    return {"tflops": flops / t / 1e12, "gather_GBs": gathered / t / 1e9, "ms_per_launch": project_ms}
 
 
 def per_stage_figures(system, kern, esz, traffic_workload=None):
@@ -374,7 +365,7 @@ def bench_cluster(steps=5, warmup=2, n_orb=512):
            "steps": steps, "warmup": warmup, "input_generation_s": t_gen,
            "current_finite": bool(np.all(np.isfinite(J)))}
     out.update(per_stage_figures(s, kern, 8, "cluster96_orb512" if n_orb == 512 else None))
-    out["mfma_projection"] = mfma_projection(s, kern["project_ms"], 8)
+    out["projection"] = projection_figures(s, kern["project_ms"], 8)
     # the complex128 twin of the same cell (three timed steps)
     log("  cluster complex128 twin")
     ms64, dev64, kern64, _ = time_path(s, "c128", 3, 1)
@@ -696,7 +687,7 @@ def main():
         "flops_per_og_step": step_flops_per_og(s),
         "kernels_ms": kern,
         "per_stage_path": per_stage_figures(s, kern, esz),
-        "mfma_projection": mfma_projection(s, kern["project_ms"], esz),
+        "projection": projection_figures(s, kern["project_ms"], esz),
         "current_finite": bool(np.all(np.isfinite(J))),
     }
     log("copy bandwidth")

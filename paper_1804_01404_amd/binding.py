@@ -458,7 +458,7 @@ def work(I, A, dt: float, volume: float):
 
 
 def mfma_layout_check(A: np.ndarray, B: np.ndarray) -> np.ndarray:
-    """Run one v_mfma_f64_16x16x4f64 with the lane layout the projector
+    """Run one v_mfma_f64_16x16x4f64 with the lane layout the Gram-matrix
     kernel assumes; returns D (16 x 16) for comparison with A @ B."""
     lib = load_library()
     fn = lib.tddft_test_mfma_layout
@@ -473,9 +473,8 @@ def mfma_layout_check(A: np.ndarray, B: np.ndarray) -> np.ndarray:
 
 
 def mfma44_layout_check(A: np.ndarray, B: np.ndarray) -> np.ndarray:
-    """Run one v_mfma_f64_4x4x4f64 (four blocks) with the lane layout the
-    stage projection assumes; A, B [4][4][4]; returns D [4][4][4] for
-    comparison with A[b] @ B[b]."""
+    """Run one v_mfma_f64_4x4x4f64 (four blocks) and check its lane layout;
+    A, B [4][4][4]; returns D [4][4][4] for comparison with A[b] @ B[b]."""
     lib = load_library()
     fn = lib.tddft_test_mfma44_layout
     fn.argtypes = [_dp, _dp, _dp]

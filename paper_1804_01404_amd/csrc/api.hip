@@ -1,14 +1,17 @@
 // C ABI of the TDKS time step (declared in include/tddft.h).
 //
-// One step, enqueued on the context's stream and captured once as a hipGraph:
+// One step, enqueued on the context's stream and captured once as a hipGraph
+// (alone and, where steps are short, several in one):
 //   1. per-step parameters: kappa_k, sphere phases, length-gauge field (from
 //      the A table indexed by a device step counter);
 //   2. four Horner stages s = 4, 3, 2, 1, each preceded (when projectors are
-//      present) by the MFMA projection of its input for the nonlocal add-back;
-//   3. observables of the new orbitals (norms, momentum, kinetic and local
-//      energy sums) and the moment projections for the nonlocal current;
-//   4. density (two fixed-order passes), Hartree by FFT, LDA, new V;
-//   5. current reduction into the device J table, counter + 1.
+//      present) by the projections of its input for the nonlocal add-back; one
+//      launch for all of it where an orbital fits in LDS;
+//   3. observables of the new orbitals (norms, momentum) and the moment
+//      projections for the nonlocal current;
+//   4. density (fixed order) and beside it the current's reduction into the
+//      device J table, counter + 1;
+//   5. Hartree by FFT, LDA, new V.
 // The potential stays frozen at rho(t_n) during a step.
 #include <algorithm>
 #include <cmath>

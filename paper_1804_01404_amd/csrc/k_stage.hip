@@ -159,11 +159,12 @@ __device__ __forceinline__ HaloSlots halo_slots(int tid, int B, int TX, int TY, 
 // The z loop in rounds of kRound planes, plane z + S of a round with the
 // compile-time index S: its prefetch slot is S mod PF and its column queue
 // starts at place S of a ring of nine, so that every value stays in the register
-// it was loaded into (a shift of the queue is sixteen moves a plane in complex
-// FP32 and thirty-two in complex128, of some 130 vector instructions). A round
-// may end at any plane; the code of a plane is there once per place. 36 x 40 x 27
-// with 96 orbitals in complex128: 47 -> 42 us a stage; 96^3 with 96 orbitals in
-// complex FP32 stays at 470 us, 4.3 TB/s, waiting for memory and barriers.
+// it was loaded into (a shift of the queue is thirty-two register moves a plane
+// in complex128, of some 130 vector instructions; in complex FP32, unrolled by
+// two, it was eight). A round may end at any plane; the code of a plane is there
+// once per place. 36 x 40 x 27 with 96 orbitals in complex128: 47 -> 42 us a
+// stage; 96^3 with 96 orbitals in complex FP32 stays at 470 us, 4.3 TB/s, with
+// 130 vector instructions a point either way, waiting for memory and barriers.
 constexpr int kRing = 9;
 template <class F, int... S>
 __device__ __forceinline__ bool round_steps(F& f, int z, int z1, std::integer_sequence<int, S...>) {
