@@ -1431,15 +1431,13 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   invalidate_graph(c);
   HIP_TRY(hipStreamSynchronize(c->stream));
   tddft_status st;
-  int *d_atom_start, *d_ent_idx, *d_ent_atom, *d_pt_ptr, *d_pt_ent;
+  int *d_atom_start, *d_ent_idx;
   double *d_atom_E, *d_ent_x, *d_ent_beta;
   double2 *d_phk, *d_phA, *d_phAJ, *d_Eu, *d_Eu2;
   double* d_jnl;
   const int nA = std::max(n_atoms, 1);
   const int Sx = std::max(S, 1);
   if ((st = dalloc_t(c, atom_start.size(), &d_atom_start)) || (st = dalloc_t(c, Sx, &d_ent_idx)) ||
-      (st = dalloc_t(c, Sx, &d_ent_atom)) || (st = dalloc_t(c, N + 1, &d_pt_ptr)) ||
-      (st = dalloc_t(c, pt_ent.size(), &d_pt_ent)) ||
       (st = dalloc_t(c, (size_t)nA * kMaxProj, &d_atom_E)) || (st = dalloc_t(c, (size_t)Sx * 3, &d_ent_x)) ||
       (st = dalloc_t(c, (size_t)Sx * kMaxProj, &d_ent_beta)) ||
       (st = dalloc_t(c, (size_t)n_colors + 1, &c->color_start)) || (st = dalloc_t(c, (size_t)nA, &c->color_atoms)) ||
@@ -1455,9 +1453,6 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   };
   HIP_TRY(up(d_atom_start, atom_start.data(), atom_start.size() * sizeof(int)));
   HIP_TRY(up(d_ent_idx, ent_idx.data(), S * sizeof(int)));
-  HIP_TRY(up(d_ent_atom, ent_atom.data(), S * sizeof(int)));
-  HIP_TRY(up(d_pt_ptr, pt_ptr.data(), (N + 1) * sizeof(int)));
-  HIP_TRY(up(d_pt_ent, pt_ent.data(), S * sizeof(int)));
   HIP_TRY(up(d_atom_E, atom_E.data(), atom_E.size() * sizeof(double)));
   HIP_TRY(up(d_ent_x, ent_x.data(), ent_x.size() * sizeof(double)));
   HIP_TRY(up(d_ent_beta, ent_beta.data(), ent_beta.size() * sizeof(double)));
@@ -1472,10 +1467,7 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   c->nl.n_ent = S;
   c->nl.atom_start = d_atom_start;
   c->nl.ent_idx = d_ent_idx;
-  c->nl.ent_atom = d_ent_atom;
   c->nl.atom_E = d_atom_E;
-  c->nl.pt_ptr = d_pt_ptr;
-  c->nl.pt_ent = d_pt_ent;
   c->nl.phk = d_phk;
   c->ent_x = d_ent_x;
   c->ent_beta = d_ent_beta;

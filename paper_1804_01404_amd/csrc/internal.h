@@ -40,10 +40,7 @@ struct NLTables {
   int n_ent = 0;
   const int* atom_start = nullptr;   // [n_atoms + 1]
   const int* ent_idx = nullptr;      // [S] flat grid index
-  const int* ent_atom = nullptr;     // [S]
   const double* atom_E = nullptr;    // [n_atoms][4] KB energies (0 where absent)
-  const int* pt_ptr = nullptr;       // [N + 1] per grid point: entries covering it
-  const int* pt_ent = nullptr;       // [nnz]
   const double2* phk = nullptr;      // [n_k][S] exp(i k . x_e)
 };
 
