@@ -1738,12 +1738,12 @@ tddft_status tddft_ground_state(tddft_ctx* c, int32_t n_iter, double tau, double
   if (tau * lam > 1.59)
     return fail(c, TDDFT_EUNSTABLE, "tau * lambda_max > 1.59: the damping polynomial is not monotone there");
   const int n = c->cfg.n_orb;
-  if (!c->gram) {
-    tddft_status st = dalloc_t(c, (size_t)2 * c->cfg.n_k * n * n, &c->gram);
-    if (st != TDDFT_OK) return st;
-    if ((st = dalloc_t(c, gram_part_doubles(n, c->cfg.n_k, (int)c->N), &c->gram_part)) != TDDFT_OK) return st;
-    if ((st = dalloc_t(c, 1, &c->chol_bad)) != TDDFT_OK) return st;
-  }
+  // each on its own: a call that ran out of memory may be repeated
+  tddft_status st;
+  if (!c->gram && (st = dalloc_t(c, (size_t)2 * c->cfg.n_k * n * n, &c->gram)) != TDDFT_OK) return st;
+  if (!c->gram_part && (st = dalloc_t(c, gram_part_doubles(n, c->cfg.n_k, (int)c->N), &c->gram_part)) != TDDFT_OK)
+    return st;
+  if (!c->chol_bad && (st = dalloc_t(c, 1, &c->chol_bad)) != TDDFT_OK) return st;
   LAUNCH(launch_set_int(c->chol_bad, 0, c->stream), "flag reset");
   invalidate_graph(c);
   for (int i = 0; i < 3; ++i) c->A_last[i] = 0.0;
@@ -1751,7 +1751,7 @@ tddft_status tddft_ground_state(tddft_ctx* c, int32_t n_iter, double tau, double
   HIP_TRY(hipMemcpyAsync(c->Aobs, Ab, sizeof(Ab), hipMemcpyHostToDevice, c->stream));
   for (int it = 0; it < n_iter; ++it) {
     LAUNCH(step_begin(c, param_cell(c, c->Aobs, nullptr)), "step begin");
-    tddft_status st = c->mixed ? ground_state_iteration<float>(c, tau) : ground_state_iteration<double>(c, tau);
+    st = c->mixed ? ground_state_iteration<float>(c, tau) : ground_state_iteration<double>(c, tau);
     if (st != TDDFT_OK) return st;
     if (energies) {
       st = tddft_energy(c, &energies[it]);

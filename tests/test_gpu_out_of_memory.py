@@ -1,0 +1,57 @@
+"""Calls on a live context that run out of device memory: they return ENOMEM
+without poisoning the context, and the context is as it was, so that the call
+can be repeated and the results are a run's that never failed, bit for bit."""
+import numpy as np
+import pytest
+
+from gpu_helpers import announce
+from oracle_helpers import tiny_periodic
+from paper_1804_01404_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+class Refuser:
+    """Device allocations by torch, of which number `at` (from the last arm()
+    on) is refused once."""
+
+    def __init__(self, monkeypatch):
+        self.at, self.count = None, 0
+        real = binding._TorchMemory._alloc
+
+        def alloc(mem, nbytes, user):
+            self.count += 1
+            if self.at is not None and self.count - 1 == self.at:
+                self.at = None
+                return None
+            return real(mem, nbytes, user)
+        monkeypatch.setattr(binding._TorchMemory, "_alloc", alloc)
+
+    def arm(self, at):
+        self.at, self.count = at, 0
+
+    def refused(self):
+        return self.at is None
+
+
+def _enomem(call):
+    with pytest.raises(binding.TDDFTError) as e:
+        call()
+    assert e.value.status == binding.ENOMEM
+
+
+@pytest.mark.parametrize("fail_at", [0, 1, 2])
+def test_ground_state(fail_at, monkeypatch):
+    s = tiny_periodic(n=12, nsteps=1)
+    announce(f"ground state, allocation {fail_at} refused")
+    with binding.TDDFT(s) as t:
+        t.set_potential()
+        E0, psi0 = t.ground_state(2, 0.01), t.orbitals()
+    mem = Refuser(monkeypatch)
+    with binding.TDDFT(s) as t:
+        t.set_potential()
+        mem.arm(fail_at)
+        _enomem(lambda: t.ground_state(2, 0.01))
+        assert mem.refused()
+        assert np.array_equal(t.ground_state(2, 0.01), E0)
+        assert np.array_equal(t.orbitals(), psi0)
