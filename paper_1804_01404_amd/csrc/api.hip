@@ -200,14 +200,15 @@ tddft_status dalloc_t(tddft_ctx* c, size_t count, P** out) {
   return st;
 }
 
-void dfree_all(tddft_ctx* c) {
-  for (auto& b : c->owned) {
+// gives back the buffers taken since there were `keep` of them (0: all)
+void dfree_from(tddft_ctx* c, size_t keep) {
+  for (size_t i = keep; i < c->owned.size(); ++i) {
     if (c->cfg.dev_free)
-      c->cfg.dev_free(b.p, c->cfg.alloc_user);
+      c->cfg.dev_free(c->owned[i].p, c->cfg.alloc_user);
     else
-      (void)hipFree(b.p);
+      (void)hipFree(c->owned[i].p);
   }
-  c->owned.clear();
+  c->owned.resize(keep);
 }
 
 bool debug_sync(const tddft_ctx* c) { return (c->cfg.flags & TDDFT_FLAG_DEBUG_SYNC) != 0; }
@@ -1060,9 +1061,16 @@ tddft_status prepare_propagate(tddft_ctx* c, int32_t nsteps, const double* A, bo
     invalidate_graph(c);
     HIP_TRY(hipStreamSynchronize(c->stream));
     int cap = std::max(nsteps, 2 * c->cap_steps);
+    // both or neither: a shorter call may follow one that ran out of memory
     tddft_status st;
-    if ((st = dalloc_t(c, 3 * (size_t)(cap + 1), &c->Atab)) || (st = dalloc_t(c, 3 * (size_t)cap, &c->Jtab)))
+    const size_t had = c->owned.size();
+    double *At, *Jt;
+    if ((st = dalloc_t(c, 3 * (size_t)(cap + 1), &At)) || (st = dalloc_t(c, 3 * (size_t)cap, &Jt))) {
+      dfree_from(c, had);
       return st;
+    }
+    c->Atab = At;
+    c->Jtab = Jt;
     c->cap_steps = cap;
   }
   if (upload) {
@@ -1129,7 +1137,7 @@ void tddft_free(tddft_ctx* ctx) {
   invalidate_graph(ctx);
   if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
   if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
-  dfree_all(ctx);
+  dfree_from(ctx, 0);
   if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
 }

@@ -55,3 +55,25 @@ def test_ground_state(fail_at, monkeypatch):
         assert mem.refused()
         assert np.array_equal(t.ground_state(2, 0.01), E0)
         assert np.array_equal(t.orbitals(), psi0)
+
+
+@pytest.mark.parametrize("fail_at", [0, 1])
+def test_longer_propagate(fail_at, monkeypatch):
+    """The A and J tables of a call longer than any before it; shorter calls go
+    on with the old ones."""
+    s = tiny_periodic(n=12, nsteps=16, A=np.cumsum(np.full((17, 3), 0.1), axis=0))
+    calls = [s.A[:3], s.A[2:5], s.A[4:16]]
+    announce(f"longer propagate, allocation {fail_at} refused")
+    with binding.TDDFT(s) as t:
+        t.set_potential()
+        J0, psi0 = [t.propagate(A) for A in calls], t.orbitals()
+    mem = Refuser(monkeypatch)
+    with binding.TDDFT(s) as t:
+        t.set_potential()
+        J = [t.propagate(calls[0])]
+        mem.arm(fail_at)
+        _enomem(lambda: t.propagate(calls[2]))
+        assert mem.refused()
+        J += [t.propagate(A) for A in calls[1:]]
+        assert all(np.array_equal(a, b) for a, b in zip(J, J0))
+        assert np.array_equal(t.orbitals(), psi0)
