@@ -708,7 +708,7 @@ tddft_status upload_orbitals(tddft_ctx* c, const double* psi) {
 // bound.
 const double kNoField[3] = {0.0, 0.0, 0.0};
 
-double spectral_bound(const tddft_ctx* c, const double amax[3], double vmin, double vmax) {
+double spectral_bound(const tddft_ctx* c, const double amax[3], double vabs, double nl_bound) {
   constexpr int kTheta = 4096;
   static const std::vector<double> k2tab = [] {
     std::vector<double> t(kTheta + 1);
@@ -745,8 +745,7 @@ double spectral_bound(const tddft_ctx* c, const double amax[3], double vmin, dou
     for (int j = 0; j <= kTheta; ++j) g = std::max(g, a2 * k2tab[j] + a1 * k1tab[j]);
     lam += g + (a2 * lip2 + a1 * lip1) * (0.5 * M_PI / kTheta) + 0.5 * kap * kap;
   }
-  const double vabs = std::max(std::fabs(vmin), std::fabs(vmax));
-  return lam + vabs + c->nl_bound;
+  return lam + vabs + nl_bound;
 }
 
 template <typename T>
@@ -1047,7 +1046,7 @@ tddft_status prepare_propagate(tddft_ctx* c, int32_t nsteps, const double* A, bo
   const bool known = amax[0] <= c->bound_amax[0] && amax[1] <= c->bound_amax[1] && amax[2] <= c->bound_amax[2];
   if (c->cfg.gauge == TDDFT_VELOCITY && !(c->cfg.flags & TDDFT_FLAG_ALLOW_UNSTABLE) && !known) {
     // the potential part was checked in set_potential; recheck the kinetic part with |A|
-    const double lam = spectral_bound(c, amax, -c->vabs, c->vabs);
+    const double lam = spectral_bound(c, amax, c->vabs, c->nl_bound);
     if (std::fabs(c->cfg.dt) * lam > 2.0 * std::sqrt(2.0)) {
       char buf[200];
       std::snprintf(buf, sizeof buf,
@@ -1382,7 +1381,7 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   }
   std::vector<int> pt_ent(std::max(S, 1)), fillpos(pt_ptr.begin(), pt_ptr.end() - 1);
   for (int e = 0; e < S; ++e) pt_ent[fillpos[ent_idx[e]]++] = e;
-  c->nl_bound = nl_bound * std::max(1, max_overlap);
+  nl_bound *= std::max(1, max_overlap);
   // greedy colouring: atoms sharing a grid point get different colours
   std::vector<int> color(n_atoms, -1);
   int n_colors = 0;
@@ -1416,7 +1415,6 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
         color_chunks.push_back(make_int4(e, std::min(e + 64, e1), at, 0));
     color_chunk_start[cl + 1] = (int)color_chunks.size();
   }
-  c->max_overlap = max_overlap;
   // exp(i k . x_e)
   std::vector<double2> phk((size_t)c->cfg.n_k * std::max(S, 1));
   for (int k = 0; k < c->cfg.n_k; ++k)
@@ -1426,35 +1424,47 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
       phk[(size_t)k * S + e] = make_double2(std::cos(arg), std::sin(arg));
     }
   // stability: |lambda| dt <= 2 sqrt 2 for the truncated fourth-order Taylor step
-  c->vabs = std::max(std::fabs(vmin), std::fabs(vmax));
-  for (int i = 0; i < 3; ++i) c->bound_amax[i] = -1.0;
-  const double lam = spectral_bound(c, kNoField, vmin, vmax);
+  const double vabs = std::max(std::fabs(vmin), std::fabs(vmax));
+  const double lam = spectral_bound(c, kNoField, vabs, nl_bound);
   if (std::fabs(c->cfg.dt) * lam > 2.0 * std::sqrt(2.0) && !(c->cfg.flags & TDDFT_FLAG_ALLOW_UNSTABLE)) {
     char buf[200];
     std::snprintf(buf, sizeof buf, "unstable: |dt| * lambda_max = %.4g > 2 sqrt 2 (lambda_max <= %.6g Ha)",
                   std::fabs(c->cfg.dt) * lam, lam);
     return fail(c, TDDFT_EUNSTABLE, buf);
   }
-  // ---- device copies (replace any previous tables)
-  invalidate_graph(c);
+  // ---- device copies (replace any previous tables). All of them are taken
+  // before anything of the context changes: after a call that ran out of
+  // memory the previous potential, if any, is still in place.
   HIP_TRY(hipStreamSynchronize(c->stream));
   tddft_status st;
-  int *d_atom_start, *d_ent_idx;
+  const size_t had = c->owned.size();
+  int *d_atom_start, *d_ent_idx, *d_color_start, *d_color_atoms;
+  int4* d_color_chunks;
   double *d_atom_E, *d_ent_x, *d_ent_beta;
-  double2 *d_phk, *d_phA, *d_phAJ, *d_Eu, *d_Eu2;
+  double2 *d_phk, *d_phA, *d_phAJ, *d_Eu, *d_Eu2, *d_phkA = nullptr;
   double* d_jnl;
   const int nA = std::max(n_atoms, 1);
   const int Sx = std::max(S, 1);
+  const bool fused = !(c->cfg.flags & TDDFT_FLAG_STREAMING) &&
+                     fused_supported(c->g, n_atoms, c->mixed ? sizeof(float2) : sizeof(double2));
   if ((st = dalloc_t(c, atom_start.size(), &d_atom_start)) || (st = dalloc_t(c, Sx, &d_ent_idx)) ||
       (st = dalloc_t(c, (size_t)nA * kMaxProj, &d_atom_E)) || (st = dalloc_t(c, (size_t)Sx * 3, &d_ent_x)) ||
       (st = dalloc_t(c, (size_t)Sx * kMaxProj, &d_ent_beta)) ||
-      (st = dalloc_t(c, (size_t)n_colors + 1, &c->color_start)) || (st = dalloc_t(c, (size_t)nA, &c->color_atoms)) ||
-      (st = dalloc_t(c, std::max<size_t>(color_chunks.size(), 1), &c->color_chunks)) ||
+      (st = dalloc_t(c, (size_t)n_colors + 1, &d_color_start)) || (st = dalloc_t(c, (size_t)nA, &d_color_atoms)) ||
+      (st = dalloc_t(c, std::max<size_t>(color_chunks.size(), 1), &d_color_chunks)) ||
       (st = dalloc_t(c, phk.size(), &d_phk)) || (st = dalloc_t(c, Sx, &d_phA)) ||
       (st = dalloc_t(c, Sx, &d_phAJ)) ||
       (st = dalloc_t(c, c->n_orb_tot * nA * kMaxProj, &d_Eu)) ||
-      (st = dalloc_t(c, c->n_orb_tot * nA * kMaxProj, &d_Eu2)) || (st = dalloc_t(c, c->n_orb_tot * 4, &d_jnl)))
+      (st = dalloc_t(c, c->n_orb_tot * nA * kMaxProj, &d_Eu2)) || (st = dalloc_t(c, c->n_orb_tot * 4, &d_jnl)) ||
+      (fused && (st = dalloc_t(c, (size_t)c->cfg.n_k * Sx, &d_phkA)))) {
+    dfree_from(c, had);
     return st;
+  }
+  invalidate_graph(c);
+  c->vabs = vabs;
+  c->nl_bound = nl_bound;
+  c->max_overlap = max_overlap;
+  for (int i = 0; i < 3; ++i) c->bound_amax[i] = -1.0;
   auto up = [&](void* dst, const void* src, size_t bytes) -> hipError_t {
     if (bytes == 0) return hipSuccess;
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream);
@@ -1464,9 +1474,12 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   HIP_TRY(up(d_atom_E, atom_E.data(), atom_E.size() * sizeof(double)));
   HIP_TRY(up(d_ent_x, ent_x.data(), ent_x.size() * sizeof(double)));
   HIP_TRY(up(d_ent_beta, ent_beta.data(), ent_beta.size() * sizeof(double)));
-  HIP_TRY(up(c->color_start, color_start.data(), color_start.size() * sizeof(int)));
-  HIP_TRY(up(c->color_atoms, color_atoms.data(), color_atoms.size() * sizeof(int)));
-  HIP_TRY(up(c->color_chunks, color_chunks.data(), color_chunks.size() * sizeof(int4)));
+  HIP_TRY(up(d_color_start, color_start.data(), color_start.size() * sizeof(int)));
+  HIP_TRY(up(d_color_atoms, color_atoms.data(), color_atoms.size() * sizeof(int)));
+  HIP_TRY(up(d_color_chunks, color_chunks.data(), color_chunks.size() * sizeof(int4)));
+  c->color_start = d_color_start;
+  c->color_atoms = d_color_atoms;
+  c->color_chunks = d_color_chunks;
   c->color_chunk_start = color_chunk_start;
   c->n_colors = n_colors;
   HIP_TRY(up(d_phk, phk.data(), (size_t)c->cfg.n_k * S * sizeof(double2)));
@@ -1479,9 +1492,8 @@ tddft_status tddft_set_potential(tddft_ctx* c, const double* v_loc, int32_t n_at
   c->nl.phk = d_phk;
   c->ent_x = d_ent_x;
   c->ent_beta = d_ent_beta;
-  c->fused = !(c->cfg.flags & TDDFT_FLAG_STREAMING) &&
-             fused_supported(c->g, n_atoms, c->mixed ? sizeof(float2) : sizeof(double2));
-  if (c->fused && (st = dalloc_t(c, (size_t)c->cfg.n_k * Sx, &c->phkA)) != TDDFT_OK) return st;
+  c->fused = fused;
+  c->phkA = d_phkA;
   c->phA = d_phA;
   c->phAJ = d_phAJ;
   c->Eu = d_Eu;
@@ -1739,7 +1751,7 @@ tddft_status tddft_ground_state(tddft_ctx* c, int32_t n_iter, double tau, double
   if (c->poisoned) return fail(c, TDDFT_ESTATE, "context poisoned: " + c->err);
   if (!c->potential_set) return fail(c, TDDFT_ESTATE, "ground_state before set_potential");
   if (n_iter < 0 || !(tau > 0.0) || !std::isfinite(tau)) return fail(c, TDDFT_EINVAL, "bad ground-state arguments");
-  const double lam = spectral_bound(c, kNoField, -c->vabs, c->vabs);
+  const double lam = spectral_bound(c, kNoField, c->vabs, c->nl_bound);
   // P4(-x) = 1 - x + x^2/2 - x^3/6 + x^4/24 decreases monotonically only up to
   // x = 1.596 (where P4'(-x) = 0); beyond it high modes are damped less than
   // lower ones and the iteration can settle on the wrong subspace

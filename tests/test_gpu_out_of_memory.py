@@ -77,3 +77,44 @@ def test_longer_propagate(fail_at, monkeypatch):
         J += [t.propagate(A) for A in calls[1:]]
         assert all(np.array_equal(a, b) for a, b in zip(J, J0))
         assert np.array_equal(t.orbitals(), psi0)
+
+
+@pytest.mark.parametrize("flags,fail_at", [(0, 0), (0, 5), (0, 7), (0, 12), (0, 14), (8, 6), (8, 7), (8, 13)])
+def test_replaced_potential(flags, fail_at, monkeypatch):
+    """A second potential that is refused (no memory, or unstable at this dt)
+    leaves the first one in place: on the LDS-resident step and on the
+    per-stage kernels (flags 8), with more atoms than before and less."""
+    nsteps = 6
+    A = np.cumsum(np.full((nsteps + 1, 3), 0.2), axis=0)
+    s = tiny_periodic(n=12, nsteps=nsteps, A=A)
+    other = tiny_periodic(n=12, n_atoms=1 if fail_at % 2 else 5, seed=103)
+    announce(f"second potential, flags {flags}, allocation {fail_at} refused")
+
+    def second(t):
+        t.set_potential(other.v_loc, other.projectors)
+    with binding.TDDFT(s, flags=flags) as t:
+        t.set_potential()
+        J0 = [t.propagate(A[:3]), t.propagate(A[2:5])]
+        second(t)
+        J0.append(t.propagate(A[4:]))
+        psi0 = t.orbitals()
+    mem = Refuser(monkeypatch)
+    with binding.TDDFT(s, flags=flags) as t:
+        mem.arm(fail_at)
+        _enomem(lambda: second(t))
+        with pytest.raises(binding.TDDFTError) as e:  # still without a potential
+            t.propagate(A[:3])
+        assert e.value.status == binding.ESTATE
+        t.set_potential()
+        J = [t.propagate(A[:3])]
+        mem.arm(fail_at)
+        _enomem(lambda: second(t))
+        assert mem.refused()
+        with pytest.raises(binding.TDDFTError) as e:
+            t.set_potential(other.v_loc - 1e4, other.projectors)
+        assert e.value.status == binding.EUNSTABLE
+        J.append(t.propagate(A[2:5]))
+        second(t)
+        J.append(t.propagate(A[4:]))
+        assert all(np.array_equal(a, b) for a, b in zip(J, J0))
+        assert np.array_equal(t.orbitals(), psi0)
