@@ -518,10 +518,9 @@ __global__ __launch_bounds__(1024) void k_lin_trace_scale(double* __restrict__ G
 // is W^2 T / 2 of them, 2.4 ms for W = 512 and 13200 samples). One workgroup
 // per lag; d = W: the column of the constant, with a(s) alone. Only the lower
 // triangle G[i + d][i] is written; row n of G is the right-hand side.
-__global__ __launch_bounds__(256) void k_lin_lags(const double* __restrict__ A, int n_traj, int T, int W,
-                                                  double* __restrict__ G) {
-  __shared__ double sc[256];
-  const int n = W + 1, d = blockIdx.x, tid = threadIdx.x;
+__device__ __forceinline__ void lin_lag(const double* __restrict__ A, int n_traj, int T, int W,
+                                        double* __restrict__ G, int d, double (&sc)[256]) {
+  const int n = W + 1, tid = threadIdx.x;
   const bool one = d == W;
   const int cnt = one ? W : W - d;      // entries i = 0 .. cnt - 1
   const int shift = T - W;              // entry i is the running sum at s = shift + i
@@ -554,10 +553,9 @@ __global__ __launch_bounds__(256) void k_lin_lags(const double* __restrict__ A, 
 
 // the right-hand side b[i] = sum x_i y (row n of G): one workgroup per entry,
 // thread t sums samples t, t + 256, ... in order, then a fixed pairwise tree
-__global__ __launch_bounds__(256) void k_lin_rhs(const double* __restrict__ A, const double* __restrict__ Y,
-                                                 int n_traj, int T, int W, double* __restrict__ G) {
-  __shared__ double red[256];
-  const int n = W + 1, i = blockIdx.x, tid = threadIdx.x;
+__device__ __forceinline__ void lin_rhs(const double* __restrict__ A, const double* __restrict__ Y, int n_traj, int T,
+                                        int W, double* __restrict__ G, int i, double (&red)[256]) {
+  const int n = W + 1, tid = threadIdx.x;
   const int t0 = i == W ? 0 : max(0, W - 1 - i);  // first sample whose window entry i is inside
   double acc = 0.0;
   for (int k = 0; k < n_traj; ++k)
@@ -574,6 +572,17 @@ __global__ __launch_bounds__(256) void k_lin_rhs(const double* __restrict__ A, c
   if (tid == 0) G[(size_t)n * n + i] = red[0];
 }
 
+// the lags by workgroups 0 .. W, the right-hand side by W + 1 .. 2 W + 1
+__global__ __launch_bounds__(256) void k_lin_sums(const double* __restrict__ A, const double* __restrict__ Y,
+                                                  int n_traj, int T, int W, double* __restrict__ G) {
+  __shared__ double buf[256];
+  const int b = blockIdx.x;
+  if (b <= W)
+    lin_lag(A, n_traj, T, W, G, b, buf);
+  else
+    lin_rhs(A, Y, n_traj, T, W, G, b - W - 1, buf);
+}
+
 // Cholesky G = L L^T by panels of kPanel columns, rows 0 .. n (the last is the
 // right-hand side, whose row of L is the forward substitution's result), then
 // the back substitution. In one workgroup, column by column, the 513 columns
@@ -588,16 +597,31 @@ __device__ __forceinline__ double lane_read(double v, int l) {
 
 // The panel at column j: every workgroup factors the diagonal block (kept in
 // Ld, so that G's is not overwritten while others read it) and solves 64 rows
-// below it. *ok = 0 if a pivot is not positive.
+// below it. *ok = 0 if a pivot is not positive. A matrix of one panel (one
+// workgroup then) gets its lambda here, by k_lin_trace_scale's tree: with that
+// launch, one of its own for the right-hand side and padded columns factored
+// too, a call with a window of one sample took 85 us (everything in one
+// workgroup 75), now 73; a window of 64 is 136 -> 125 us.
+// PART: the last columns, fewer than a panel's (that test in a full panel's
+// code costs a window of 64 its gain).
+template <bool PART>
 __global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ G, double* __restrict__ Ld, int n, int j,
-                                                   int* __restrict__ ok) {
+                                                   double lambda_rel, int* __restrict__ ok) {
   __shared__ double D[kPanel][kPanel + 1];
-  const int lane = threadIdx.x, nb = min(kPanel, n - j);
+  const int lane = threadIdx.x, nb = PART ? n - j : kPanel;
   for (int i = lane; i < kPanel * kPanel; i += 64) {
     const int r = i / kPanel, c = i % kPanel;
     D[r][c] = r < nb && c <= r ? G[(size_t)(j + r) * n + j + c] : (r == c ? 1.0 : 0.0);
   }
   __syncthreads();
+  if (n <= kPanel) {
+    double s = lane < n ? D[lane][lane] : 0.0;
+#pragma unroll
+    for (int h = kPanel / 2; h > 0; h >>= 1) s += __shfl_xor(s, h, 64);
+    if (lane < n) D[lane][lane] += lambda_rel * s / n;
+    if (lane == 0) *ok = 1;
+    __syncthreads();
+  }
   // the block's row lane & 31 in registers; the values of other rows come by
   // lane reads
   const int r = lane & 31;
@@ -607,6 +631,7 @@ __global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ G, doubl
   bool good = true;
 #pragma unroll
   for (int c = 0; c < kPanel; ++c) {
+    if (PART && c >= nb) continue;  // uniform; the padding is its own factor
     double d = lane_read(a[c], c);
     if (!(d > 0.0)) {
       good = false;
@@ -633,8 +658,8 @@ __global__ __launch_bounds__(64) void k_chol_panel(double* __restrict__ G, doubl
     for (int i = lane; i < kPanel * kPanel; i += 64)
       Ld[(size_t)(j / kPanel) * kPanel * kPanel + i] = D[i / kPanel][i % kPanel];
   const int row = j + kPanel + blockIdx.x * 64 + lane;
-  if (nb < kPanel) {
-    // the last panel: only the right-hand side (row n) is left below it
+  if (PART) {
+    // only the right-hand side (row n) is left below it
     if (blockIdx.x > 0 || lane > 0) return;
     for (int c = 0; c < nb; ++c) {
       double x = G[(size_t)n * n + j + c];
@@ -699,6 +724,7 @@ __global__ __launch_bounds__(1024) void k_chol_back(double* __restrict__ G, cons
       double x = k < nb ? z[j + k] : 0.0;
 #pragma unroll
       for (int c = kPanel - 1; c >= 0; --c) {
+        if (c >= nb) continue;
         const double wc = lane_read(x, c) / lane_read(d[c], c);
         if (k == c) x = wc;
         if (k < c) x -= d[c] * wc;
@@ -729,13 +755,16 @@ hipError_t nn_fit_linear(const double* A, const double* Y, int n_traj, int T, in
                          float* ws, float* b3, int* ok, hipStream_t s) {
   const int n = W + 1;
   double* Ld = G + (size_t)(n + 1) * n;
-  hipLaunchKernelGGL(k_lin_lags, dim3((unsigned)n), dim3(256), 0, s, A, n_traj, T, W, G);
-  hipLaunchKernelGGL(k_lin_rhs, dim3((unsigned)n), dim3(256), 0, s, A, Y, n_traj, T, W, G);
+  hipLaunchKernelGGL(k_lin_sums, dim3((unsigned)(2 * n)), dim3(256), 0, s, A, Y, n_traj, T, W, G);
   // lambda relative to the mean diagonal of G
-  hipLaunchKernelGGL(k_lin_trace_scale, dim3(1), dim3(1024), 0, s, G, n, lambda_rel, ok);
+  if (n > kPanel) hipLaunchKernelGGL(k_lin_trace_scale, dim3(1), dim3(1024), 0, s, G, n, lambda_rel, ok);
   for (int j = 0; j < n; j += kPanel) {
     const int below = n + 1 - j - kPanel;  // rows under the panel, the right-hand side among them
-    hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)max(1, (below + 63) / 64)), dim3(64), 0, s, G, Ld, n, j, ok);
+    const dim3 grid((unsigned)max(1, (below + 63) / 64));
+    if (n - j < kPanel)
+      hipLaunchKernelGGL(k_chol_panel<true>, grid, dim3(64), 0, s, G, Ld, n, j, lambda_rel, ok);
+    else
+      hipLaunchKernelGGL(k_chol_panel<false>, grid, dim3(64), 0, s, G, Ld, n, j, lambda_rel, ok);
     if (below > 0) {
       const unsigned tr = (unsigned)((below + 31) / 32), tc = (unsigned)((n - j - kPanel + 31) / 32);
       if (tc > 0) hipLaunchKernelGGL(k_chol_update, dim3(tc, tr), dim3(256), 0, s, G, n, j);
