@@ -145,9 +145,11 @@ __global__ __launch_bounds__(1024) void k_em_energy(const double* __restrict__ A
 }
 
 // one macroscopic step's work over the medium points x0 .. x0 + n_mat - 1, and
-// the step's records (each may be null): the rows A_row, I_row of all n points,
-// the medium points' histories hA, hI. A copy of its own for each was some
-// 10 us of a step, its gap included.
+// the step's records (each may be null): the medium points' histories hA, hI
+// beside the sum, the rows A_row, I_row of all n points by the workgroups after
+// the first, 1024 points each. A copy of its own for each was some 10 us of a
+// step, its gap included; all by one workgroup, rows of 100000 points took
+// longer than the copies (a step of the network 160 -> 196 us).
 __global__ __launch_bounds__(1024) void k_ms_work_step(const double* __restrict__ A_new, const double* __restrict__ A_now,
                                                        const double* __restrict__ I_now, const double* __restrict__ I_new,
                                                        int n, int x0, int n_mat, double dx, double dt,
@@ -155,6 +157,12 @@ __global__ __launch_bounds__(1024) void k_ms_work_step(const double* __restrict_
                                                        double* __restrict__ I_row, double* __restrict__ hA,
                                                        double* __restrict__ hI) {
   __shared__ double red[1024];
+  if (blockIdx.x > 0) {
+    const int j = ((int)blockIdx.x - 1) * 1024 + (int)threadIdx.x;
+    if (j < n && A_row) A_row[j] = A_new[j];
+    if (j < n && I_row) I_row[j] = I_new[j];
+    return;
+  }
   double s = 0.0;
   for (int m = threadIdx.x; m < n_mat; m += 1024) {
     const int j = x0 + m;
@@ -163,10 +171,6 @@ __global__ __launch_bounds__(1024) void k_ms_work_step(const double* __restrict_
     if (hA) hA[m] = A_new[j];
     if (hI) hI[m] = I_new[j];
   }
-  if (A_row)
-    for (int j = threadIdx.x; j < n; j += 1024) A_row[j] = A_new[j];
-  if (I_row)
-    for (int j = threadIdx.x; j < n; j += 1024) I_row[j] = I_new[j];
   const double tot = block_sum_1024(s, red);
   if (threadIdx.x == 0) *W += dt * dx * tot;
 }
@@ -199,7 +203,8 @@ hipError_t launch_em_energy(const double* A_now, const double* A_prev, int n, do
 hipError_t launch_ms_work_step(const double* A_new, const double* A_now, const double* I_now, const double* I_new,
                                int n, int x0, int n_mat, double dx, double dt, double* W, double* A_row,
                                double* I_row, double* hA, double* hI, hipStream_t s) {
-  hipLaunchKernelGGL(k_ms_work_step, dim3(1), dim3(1024), 0, s, A_new, A_now, I_now, I_new, n, x0, n_mat, dx, dt, W,
+  const unsigned rows = A_row || I_row ? (unsigned)((n + 1023) / 1024) : 0;
+  hipLaunchKernelGGL(k_ms_work_step, dim3(1 + rows), dim3(1024), 0, s, A_new, A_now, I_now, I_new, n, x0, n_mat, dx, dt, W,
                      A_row, I_row, hA, hI);
   return hipGetLastError();
 }
