@@ -220,9 +220,11 @@ __global__ __launch_bounds__(256) void k_rho_tau_partial(const typename Vec2<T>:
 // first loads of its queue, so what counts is how many share a compute unit.
 // Slabs of at most ten planes read least; where those leave fewer than 1024
 // workgroups of eight orbitals, slabs of at most five (as even as can be)
-// double them. 20^3, long against
-// short slabs, whole step: 1024 orbitals 266 / 259 us, 3456 703 / 701, 5488
-// 1073 / 1077, 8192 1546 / 1553 (complex FP32); complex128 8192 2800 / 2897.
+// double them. Whole step of 20^3, long against short slabs: 1024 orbitals
+// 266 / 259 us, 3456 703 / 701, 5488 1073 / 1077, 8192 1546 / 1553 (complex
+// FP32); complex128 8192 2800 / 2897. So the ends are 3 % apart, and between
+// 3000 and 6000 orbitals of that grid the two are alike: the line could lie
+// anywhere there.
 constexpr int kTauLong = 10, kTauShort = 5;
 int tau_slab(const Geometry& g, long n_tot) {
   const int nl = (g.n3 + kTauLong - 1) / kTauLong;

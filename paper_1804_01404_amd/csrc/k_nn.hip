@@ -193,9 +193,15 @@ __global__ void k_accum(const float* __restrict__ src, float* __restrict__ dst) 
 // ---------------------------------------------------------------- training step
 // One Adam step on a batch in two launches, for hidden widths up to 64,
 // windows up to 1024 and batches up to 4096. As seventeen launches (window
-// gather, three products, sums, Adam) a batch of 256 with W = 512, H = 16 took
-// 0.19 ms, all of it launch latency and serial column sums; as two it is 21 us
-// (14.5 and 6.3 us: dependent loads and eight barriers on 16 workgroups).
+// gather, three products, sums, Adam) a batch of 256 with W = 512, H = 16 takes
+// 62 us, nearly all launch latency; as two it is 28 us (kernels of 14.5 and
+// 6.3 us: dependent loads and eight barriers on 16 workgroups).
+// Width: the hidden layers are H products a thread in order, which catches up
+// with the launches at 64 (us a batch, seventeen launches / two: W = 512, H = 64,
+// B = 256 64 / 51; W = 1024 74 / 69; B = 64 60 / 62). Window and batch: what the
+// LDS of the two kernels holds at that width with room to spare (116 of 160 KB,
+// 32 KB), not where two launches stop gaining (W = 1024, H = 64, B = 4096
+// 401 / 161).
 //
 // k_nn_tile: sixteen samples per workgroup, forward and backward down to dz1,
 // with their windows read from the trajectories into LDS; writes dz1, dy and

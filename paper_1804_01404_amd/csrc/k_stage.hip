@@ -156,7 +156,7 @@ __device__ __forceinline__ HaloSlots halo_slots(int tid, int B, int TX, int TY, 
   return h;
 }
 
-// The z loop in rounds of kRound planes, plane z + S of a round with the
+// The z loop in rounds of kRing planes, plane z + S of a round with the
 // compile-time index S: its prefetch slot is S mod PF and its column queue
 // starts at place S of a ring of nine, so that every value stays in the register
 // it was loaded into (a shift of the queue is thirty-two register moves a plane
