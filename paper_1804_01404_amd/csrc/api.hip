@@ -1928,7 +1928,10 @@ tddft_status bfail(tddft_batch* b, tddft_status st, const std::string& m) {
 #define BHIP(expr)                                                                          \
   do {                                                                                      \
     hipError_t e_ = (expr);                                                                 \
-    if (e_ != hipSuccess) return bfail(b, TDDFT_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
+    if (e_ != hipSuccess) {                                                                 \
+      (void)hipGetLastError(); /* not to be reported by the thread's next launch */         \
+      return bfail(b, TDDFT_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_));    \
+    }                                                                                       \
   } while (0)
 
 tddft_status bcell(tddft_batch* b, tddft_status st, int i) {

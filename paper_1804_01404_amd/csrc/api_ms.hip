@@ -46,9 +46,16 @@ tddft_status nn_fail(tddft_nn* n, tddft_status st, const std::string& msg) {
     if (e_ != hipSuccess) return nn_fail(n, TDDFT_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// (a refusal is cleared: the next launch of the thread, of whatever context,
+// would otherwise report it as its own)
 template <typename P>
 hipError_t nalloc(P** p, size_t count) {
-  return hipMalloc(reinterpret_cast<void**>(p), std::max<size_t>(count, 1) * sizeof(P));
+  const hipError_t e = hipMalloc(reinterpret_cast<void**>(p), std::max<size_t>(count, 1) * sizeof(P));
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+  }
+  return e;
 }
 
 void nn_release_work(tddft_nn* n) {
@@ -663,8 +670,12 @@ tddft_status tddft_ms_step(tddft_ms* ms, int32_t n_macro, const double* inc, dou
       return ms_fail(ms, TDDFT_ENOMEM, "device allocation failed (output rows)");
     ms->out_cap = n_macro;
   }
-  if (!ms->pinned)  // (a run on the network may fall back to the cells on the way)
-    MHIP(hipHostMalloc(reinterpret_cast<void**>(&ms->pinned), 2 * (size_t)nx * sizeof(double)));
+  // (a run on the network may fall back to the cells on the way)
+  if (!ms->pinned && hipHostMalloc(reinterpret_cast<void**>(&ms->pinned), 2 * (size_t)nx * sizeof(double))) {
+    (void)hipGetLastError();
+    ms->pinned = nullptr;
+    return ms_fail(ms, TDDFT_ENOMEM, "pinned allocation failed (rows of the cells)");
+  }
   double *Anew = ms->pinned, *Inew = ms->pinned + nx;
   const std::vector<int> all = [&] {
     std::vector<int> v(nm);

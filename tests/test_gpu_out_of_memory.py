@@ -118,3 +118,24 @@ def test_replaced_potential(flags, fail_at, monkeypatch):
         J.append(t.propagate(A[4:]))
         assert all(np.array_equal(a, b) for a, b in zip(J, J0))
         assert np.array_equal(t.orbitals(), psi0)
+
+
+def test_refused_network_workspace():
+    """A batch whose workspace exceeds the device (35 TB) is ENOMEM, and the
+    refusal is not reported by what the thread launches next."""
+    W, H = 4096, 2
+    rng = np.random.default_rng(5)
+    x = rng.normal(size=(3, W)).astype(np.float32)
+    s = tiny_periodic(n=8, nsteps=1)
+    announce("network workspace beyond the device")
+    with binding.Surrogate(W, H, 0.01 * rng.normal(size=binding.nn_num_params(W, H))) as nn, binding.TDDFT(s) as t:
+        t.set_potential()
+        y0 = nn.forward(x)
+        out = np.empty(3, dtype=np.float32)
+
+        def huge():
+            nn._check(nn.lib.tddft_nn_forward(nn.h, 2**31 - 1, binding._fptr(x), binding._fptr(out)))
+        _enomem(huge)
+        assert np.all(np.isfinite(t.propagate(s.A)))
+        _enomem(huge)
+        assert np.array_equal(nn.forward(x), y0)
